@@ -17,6 +17,8 @@ constexpr uint32_t kDomMoveU = 5;   // trimer model: uniform word of a main-phas
 constexpr uint32_t kDomWalkinU = 6; // trimer model: uniform word of a walk-in attempt
 constexpr uint32_t kDomBoot = 7;    // bootstrap: run indices drawn for the resamples
 
+constexpr size_t kLdsBytes = 160 * 1024;   // LDS of one gfx950 compute unit
+
 constexpr int kModelPotts2D = 0;
 constexpr int kModelTrimer3D = 1;
 constexpr int kModelLipid3D = 2;

@@ -32,7 +32,7 @@
 // Mapping: one walker per workgroup (the attempt kernel: up to 16 wavefronts
 // sharing the 64-partner chunks; walk-in and set-up: one wavefront), its
 // state, ln g and H in LDS.  Attempts are sequential.
-#include "rewl_device.h"
+#include "rewl_moves.h"
 
 namespace rewl_gpu {
 
@@ -71,47 +71,30 @@ __device__ __forceinline__ double log_basic(double x) {
     return (double)k * kLn2C1 + ((double)k * kLn2C2 + lm);
 }
 
-__device__ __forceinline__ double lip_min_image(float a, float b, float box, float half) {
-#pragma clang fp contract(off)
-    float x = b - a;
-    if (x > half) x = x - box;
-    else if (x < -half) x = x + box;
-    return (double)x;
-}
-
 __device__ __forceinline__ double lip_r2(const float *a, const float *b, float box, float half) {
-#pragma clang fp contract(off)
-    const double dx = lip_min_image(a[0], b[0], box, half);
-    const double dy = lip_min_image(a[1], b[1], box, half);
-    const double dz = lip_min_image(a[2], b[2], box, half);
-    return (dx * dx + dy * dy) + dz * dz;
+    return move_r2(a, b, box, half);
 }
 
-// Pair energy of types ti, tj at squared distance r2 (Eqs. 3-5).
+// Pair energy of types ti, tj at squared distance r2 (Eqs. 3-5).  One
+// division serves every kind (1.05 / r for the repulsion, 1 / r^2 for
+// Lennard-Jones and the WCA part of a bond), the kinds differ by selects: the
+// lanes of a wavefront nearly always hold several.
 __device__ __forceinline__ double lip_pair(int ti, int tj, bool bonded, double r2, double eps_ww) {
 #pragma clang fp contract(off)
-    if (bonded) {
-        if (r2 >= kLipR2) return __builtin_inf();
-        const double fene = -(0.5 * 30.0 * 1.69) * log_basic(1.0 - r2 / kLipR2);
-        double wca = 0.0;
-        if (r2 < kLipWcaRc2) {
-            const double s2 = 1.0 / r2;
-            const double s6 = (s2 * s2) * s2;
-            wca = 4.0 * ((s6 * s6) - s6) + 1.0;
-        }
-        return fene + wca;
+    const bool rep = !bonded && (ti == kH) != (tj == kH);
+    double den = r2;
+    if (rep) den = __builtin_sqrt(r2);
+    const double q = (rep ? 1.05 : 1.0) / den;
+    const double q3 = (q * q) * q;
+    const double q6 = q3 * q3;
+    double v = 4.0 * (rep ? q6 * q3 : q6 - q3);
+    if (!bonded) {
+        v = ti == kW && tj == kW ? eps_ww * v : v;
+        return r2 >= kLipRc2 ? 0.0 : v;
     }
-    if (r2 >= kLipRc2) return 0.0;
-    const bool rep = (ti == kH && tj != kH) || (tj == kH && ti != kH);
-    if (rep) {
-        const double q = 1.05 / __builtin_sqrt(r2);
-        const double q3 = (q * q) * q;
-        return 4.0 * ((q3 * q3) * q3);
-    }
-    const double s2 = 1.0 / r2;
-    const double s6 = (s2 * s2) * s2;
-    const double v = 4.0 * ((s6 * s6) - s6);
-    return (ti == kW && tj == kW) ? eps_ww * v : v;
+    if (r2 >= kLipR2) return __builtin_inf();
+    const double fene = -(0.5 * 30.0 * 1.69) * log_basic(1.0 - r2 / kLipR2);
+    return fene + (r2 < kLipWcaRc2 ? v + 1.0 : 0.0);
 }
 
 __device__ __forceinline__ bool lip_bonded(int a, int b) {
@@ -127,17 +110,6 @@ __device__ __forceinline__ bool lip_term(double vn, double vo, int64_t &t) {
     const bool ok = fx_term(vn, a) & fx_term(vo, b);
     t = a - b;
     return ok;
-}
-
-__device__ __forceinline__ float lip_disp(uint32_t r) {
-#pragma clang fp contract(off)
-    return 0.1f * ((float)(r >> 9) * 0x1p-22f - 1.0f);
-}
-__device__ __forceinline__ float lip_wrap(float v, float box) {
-#pragma clang fp contract(off)
-    if (v < 0.0f) v = v + box;
-    if (v >= box) v = v - box;
-    return v;
 }
 
 // One walker's state in LDS.
@@ -214,9 +186,9 @@ __device__ __forceinline__ void lip_propose(const DevState &st, const LipView &v
         const int b = (int)mul_shift(a.x, (uint32_t)st.nb);
         p.b = b;
         const float o[3] = {v.x[3 * b], v.x[3 * b + 1], v.x[3 * b + 2]};
-        p.xn[0] = lip_wrap(o[0] + lip_disp(a.y), box);
-        p.xn[1] = lip_wrap(o[1] + lip_disp(a.z), box);
-        p.xn[2] = lip_wrap(o[2] + lip_disp(a.w), box);
+        p.xn[0] = move_wrap(o[0] + move_disp(a.y), box);
+        p.xn[1] = move_wrap(o[1] + move_disp(a.z), box);
+        p.xn[2] = move_wrap(o[2] + move_disp(a.w), box);
         const int tb = v.type[b], wb = v.where[b];
         for (int c0 = 0; c0 < st.nb; c0 += 64) {
             const int j = c0 + lane;
@@ -425,28 +397,212 @@ __global__ __launch_bounds__(64) void k_lipid_walkin(DevState st, int64_t chunk,
 // min[1, g(old)/g(new)] (times n_c / n_r for a reptation); then
 // ln g += ln f and H += 1 at the bin after the decision.
 //
-// One workgroup per walker with up to 16 wavefronts: wave v takes the
-// 64-partner chunks c = v, v + nwave, ...; the fixed-point partner terms go
-// to LDS (tbuf[c][lane]) and wave 0 adds them up (exact, any order), decides
-// and applies the move.  Reptation candidates are
-// found with one ballot mask per chunk, written to LDS and read by every
-// wave.  All branches that contain a barrier depend only on the attempt's
+// One workgroup of 16 wavefronts per walker.  Displacements: an attempt per
+// wavefront, blocks of consecutive attempts evaluated side by side and decided
+// in order (rewl_moves.h).  A reptation ends the block before it and is done
+// by the whole workgroup: candidates by one ballot mask per 64 particles, then
+// the partner terms of the four changed particles, wave v taking the chunks
+// v, v + waves, ...; the waves' exact sums are added by wavefront 0, which
+// decides.  All branches that contain a barrier depend only on the attempt's
 // random words or on values every wave reads from LDS, so the waves agree.
-__global__ __launch_bounds__(1024) void k_lipid_sweep(DevState st, int64_t s0, int64_t n) {
-#pragma clang fp contract(off)
-    const int w = blockIdx.x;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int nwave = (int)(blockDim.x >> 6);
+struct LipidMoves {
+    static constexpr bool kReptation = true;
+    static constexpr bool kHeads = false;
+    float *x;
+    MoveGrid *grid;
+    LipView v;
+    float box, half, scale;
+    double eps_ww;
+    unsigned long long *mask1, *mask2;   // [nch] candidates for the capture, solvent near the released particle
+    int64_t *wsum;                       // [waves] partner sums of a reptation, kFxBad for a hard overlap
+    __device__ __forceinline__ int bonds(int b, int &p0, int &p1) const {
+        const int at = __builtin_amdgcn_readfirstlane(v.where[b]);
+        if (at < 0) return 0;
+        const int bead = at % 3;
+        const int32_t *l = v.lip + (at - bead);
+        p0 = __builtin_amdgcn_readfirstlane(l[1]);
+        if (bead != 1) return 1;
+        p0 = __builtin_amdgcn_readfirstlane(l[0]);
+        p1 = __builtin_amdgcn_readfirstlane(l[2]);
+        return 2;
+    }
+    __device__ __forceinline__ double pair(int b, int j, const float *p, const float *r, bool bond) const {
+        return lip_pair(v.type[b], v.type[j], bond, lip_r2(p, r, box, half), eps_ww);
+    }
+    __device__ void reptation(const DevState &st, uint32_t ax, uint32_t ux, uint32_t uz, uint32_t uw, double *g,
+                              uint32_t *H, uint16_t *list, int lo, double lnf, int &E, int64_t &Ef) const {
+        const int lane = threadIdx.x & 63;
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const int nwave = (int)(blockDim.x >> 6);
+        const int nch = (st.nb + 63) / 64;
+        LipProp p;
+        p.ok = true;
+        p.rep = true;
+        const int lipid = (int)mul_shift(ax, (uint32_t)st.nmol);
+        p.lipid = lipid;
+        const int end = (int)(uz >> 31);
+        const int l0 = v.lip[3 * lipid], l1 = v.lip[3 * lipid + 1], l2 = v.lip[3 * lipid + 2];
+        const int e = end == 0 ? l0 : l2;
+        const float xe[3] = {v.x[3 * e], v.x[3 * e + 1], v.x[3 * e + 2]};
+        for (int c = wave; c < nch; c += nwave) {
+            const int j = c * 64 + lane;
+            bool hit = false;
+            if (j < st.nb && j != e && v.type[j] == kW) hit = lip_r2(xe, v.x + 3 * j, box, half) < kLipR2;
+            const unsigned long long m = __ballot(hit);
+            if (lane == 0) mask1[c] = m;
+        }
+        __syncthreads();
+        int nc = 0;
+        for (int c = 0; c < nch; ++c) nc += __builtin_popcountll(mask1[c]);
+        if (nc == 0) {
+            p.ok = false;
+        } else {
+            int pick = (int)mul_shift(uw, (uint32_t)nc);
+            int cap = -1;
+            for (int c = 0; c < nch && cap < 0; ++c) {
+                unsigned long long m = mask1[c];
+                const int cnt = __builtin_popcountll(m);
+                if (pick < cnt) {
+                    for (int r = pick; r > 0; --r) m &= m - 1ull;
+                    cap = c * 64 + (int)__builtin_ctzll(m);
+                } else {
+                    pick -= cnt;
+                }
+            }
+            int rel;
+            if (end == 0) { p.nl[0] = cap; p.nl[1] = l0; p.nl[2] = l1; rel = l2; }
+            else { p.nl[0] = l1; p.nl[1] = l2; p.nl[2] = cap; rel = l0; }
+            int all[4] = {cap, l0, l1, l2};
+            for (int i = 1; i < 4; ++i)
+                for (int q = i; q > 0 && all[q - 1] > all[q]; --q) {
+                    const int tq = all[q]; all[q] = all[q - 1]; all[q - 1] = tq;
+                }
+            for (int i = 0; i < 4; ++i) {
+                const int q = all[i];
+                p.c[i] = q;
+                if (q == rel) { p.nt[i] = kW; p.nwh[i] = -1; }
+                else {
+                    const int pos = q == p.nl[0] ? 0 : (q == p.nl[1] ? 1 : 2);
+                    p.nt[i] = pos == 0 ? kP : kH;
+                    p.nwh[i] = 3 * lipid + pos;
+                }
+            }
+            p.nc = nc;
+            // n_r: solvent within R of l1 under the new types
+            const float x1[3] = {v.x[3 * l1], v.x[3 * l1 + 1], v.x[3 * l1 + 2]};
+            for (int c = wave; c < nch; c += nwave) {
+                const int j = c * 64 + lane;
+                bool hit = false;
+                if (j < st.nb && j != l1) {
+                    int tj = v.type[j];
+                    for (int i = 0; i < 4; ++i)
+                        if (p.c[i] == j) tj = p.nt[i];
+                    if (tj == kW) hit = lip_r2(x1, v.x + 3 * j, box, half) < kLipR2;
+                }
+                const unsigned long long m = __ballot(hit);
+                if (lane == 0) mask2[c] = m;
+            }
+            // fx(V_new) - fx(V_old) over the pairs holding one of the four
+            // changed particles, each pair once (see lip_propose): 16 tasks,
+            // particle i = task mod 4 against every fourth chunk; partners
+            // within the cut-off (bonds are shorter) go to the wavefront's
+            // list, evaluated 32 partners x (new, old) per pass.
+            int64_t acc = 0;
+            bool bad = false;
+            const uint32_t lim = move_grid_limit(2.5f + 1e-3f + box * 1e-6f, scale);
+            for (int task = wave; task < 16; task += nwave) {
+                const int i = task & 3;
+                const int ci = p.c[0] * (i == 0) + p.c[1] * (i == 1) + p.c[2] * (i == 2) + p.c[3] * (i == 3);
+                const int nti = p.nt[0] * (i == 0) + p.nt[1] * (i == 1) + p.nt[2] * (i == 2) + p.nt[3] * (i == 3);
+                const int nwi = p.nwh[0] * (i == 0) + p.nwh[1] * (i == 1) + p.nwh[2] * (i == 2) + p.nwh[3] * (i == 3);
+                const int oti = v.type[ci], owi = v.where[ci];
+                const float xc[3] = {v.x[3 * ci], v.x[3 * ci + 1], v.x[3 * ci + 2]};
+                const MoveGrid gc = move_grid(xc, scale);
+                int cnt = 0;
+                auto pass = [&](int n) {
+                    move_wave_sync();
+                    if ((lane >> 1) < n) {
+                        const int j = list[cnt - n + (lane >> 1)];
+                        const bool old = lane & 1;
+                        int tj = v.type[j], wj = v.where[j];
+                        for (int a = 0; a < 4; ++a)
+                            if (!old && p.c[a] == j) { tj = p.nt[a]; wj = p.nwh[a]; }
+                        int64_t t = 0;
+                        bad |= !fx_term(lip_pair(old ? oti : nti, tj, lip_bonded(old ? owi : nwi, wj),
+                                                 lip_r2(xc, v.x + 3 * j, box, half), eps_ww), t);
+                        acc += old ? -t : t;
+                    }
+                    cnt -= n;
+                    move_wave_sync();
+                };
+                for (int c = task >> 2; c < nch; c += 4) {
+                    const int j = c * 64 + lane;
+                    const int jj = j < st.nb ? j : 0;
+                    bool near = j < st.nb && j != ci &&
+                                move_grid2(grid ? grid[jj] : move_grid(v.x + 3 * jj, scale), gc) <= lim;
+                    for (int a = 0; a < 4; ++a) near = near && !(p.c[a] == j && ci > j);
+                    const unsigned long long m = __ballot(near);
+                    if (near) list[cnt + move_mbcnt(m)] = (uint16_t)j;
+                    cnt += __builtin_popcountll(m);
+                    while (cnt >= 32) pass(32);
+                }
+                if (cnt) pass(cnt);
+            }
+            acc = wave_sum64(acc);
+            if (__ballot(bad)) acc = kFxBad;
+            if (lane == 0) wsum[wave] = acc;
+        }
+        __syncthreads();
+        if (wave != 0) return;
+        if (p.ok) {
+            p.de = 0;
+            for (int a = 0; a < nwave; ++a) {
+                const int64_t part = wsum[a];
+                p.ok = p.ok && part != kFxBad;
+                p.de += part != kFxBad ? part : 0;
+            }
+            int nr = 0;
+            for (int c = 0; c < nch; ++c) nr += __builtin_popcountll(mask2[c]);
+            p.nr = nr;
+            int64_t e_new = 0;
+            if (p.ok && fx_add(Ef, p.de, e_new)) {
+                const int bn = lip_bin(st, e_new);
+                if (bn >= lo && bn < lo + st.W && lip_accept(p, g[E - lo] - g[bn - lo], ux)) {
+                    lip_apply(st, v, p, lane);
+                    Ef = e_new;
+                    E = bn;
+                }
+            }
+        }
+        E = __builtin_amdgcn_readfirstlane(E);
+        Ef = move_uniform64(Ef);
+        if (lane == 0) {
+            g[E - lo] = g[E - lo] + lnf;
+            H[E - lo] += 1u;
+        }
+        move_wave_sync();
+    }
+};
+
+// Bytes of LDS a run of nch 64-particle chunks needs for its reptations: the
+// masks, and per wavefront a partial sum.
+static __host__ __device__ inline size_t lip_rep_bytes(int nch) { return (size_t)nch * 16; }
+constexpr size_t kLipRepPerWave = 8;
+
+__global__ __launch_bounds__(1024) void k_lipid_sweep(DevState st, int64_t s0, int64_t n, int has_grid) {
     if (*st.converged) return;
-    extern __shared__ __align__(16) unsigned char smem[];
+    const int w = blockIdx.x;
+    const int k = w / st.m;
     const int W = st.W, Wpad = st.Wpad;
+    const int E = st.E[w];
+    if (E < st.start[k] || E >= st.start[k] + W) return;   // not walked in (every wave reads the same E)
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int nwave = (int)(blockDim.x >> 6);
     const int nch = (st.nb + 63) / 64;
     double *g = (double *)(smem + st.Npad);
     uint32_t *H = (uint32_t *)(smem + st.Npad + (size_t)Wpad * 8);
-    int64_t *tbuf = (int64_t *)(smem + st.Npad + (size_t)Wpad * 12);
-    unsigned long long *mask1 = (unsigned long long *)(tbuf + (size_t)nch * 64);
-    unsigned long long *mask2 = mask1 + nch;
+    unsigned char *mv = smem + st.Npad + (size_t)Wpad * 12;
+    unsigned char *rep = mv + move_lds_bytes(nwave);
     const uint32_t *gx = (const uint32_t *)(st.spins + (size_t)w * st.Npad);
     for (int i = threadIdx.x; i < st.Npad / 4; i += blockDim.x) ((uint32_t *)smem)[i] = gx[i];
     const size_t row = (size_t)w * Wpad;
@@ -455,183 +611,24 @@ __global__ __launch_bounds__(1024) void k_lipid_sweep(DevState st, int64_t s0, i
         H[b] = st.H[row + b];
     }
     __syncthreads();
-    const LipView v = lip_view(st, smem);
-    const float box = st.box, half = 0.5f * st.box;
-    const int k = w / st.m;
-    const int lo = st.start[k], hi = lo + W - 1;
-    const double lnf = st.lnf[k];
-    int E = st.E[w];
-    int64_t Ef = st.Efx[w];
-    if (E < lo || E > hi) return;   // not walked in (every wave reads the same E)
-    U4 la, lu;   // random words of attempt t0 + lane, drawn 64 attempts at a time
-    for (int64_t t = 0; t < n; ++t) {
-        const int j64 = (int)(t & 63);
-        if (j64 == 0) lip_words(st, (uint64_t)(s0 + t + lane), (uint32_t)w, kDomMove, kDomMoveU, la, lu);
-        U4 a, u;
-        a.x = __builtin_amdgcn_readlane(la.x, j64); a.y = __builtin_amdgcn_readlane(la.y, j64);
-        a.z = __builtin_amdgcn_readlane(la.z, j64); a.w = __builtin_amdgcn_readlane(la.w, j64);
-        u.x = __builtin_amdgcn_readlane(lu.x, j64); u.y = __builtin_amdgcn_readlane(lu.y, j64);
-        u.z = __builtin_amdgcn_readlane(lu.z, j64); u.w = __builtin_amdgcn_readlane(lu.w, j64);
-        LipProp p;
-        p.ok = true;
-        p.rep = u.y < st.lip_rep_thr;
-        if (!p.rep) {
-            const int b = (int)mul_shift(a.x, (uint32_t)st.nb);
-            p.b = b;
-            const float o[3] = {v.x[3 * b], v.x[3 * b + 1], v.x[3 * b + 2]};
-            p.xn[0] = lip_wrap(o[0] + lip_disp(a.y), box);
-            p.xn[1] = lip_wrap(o[1] + lip_disp(a.z), box);
-            p.xn[2] = lip_wrap(o[2] + lip_disp(a.w), box);
-            const int tb = v.type[b], wb = v.where[b];
-            for (int c = wave; c < nch; c += nwave) {
-                const int j = c * 64 + lane;
-                int64_t tj = 0;
-                if (j < st.nb && j != b) {
-                    const float *xj = v.x + 3 * j;
-                    const int tjt = v.type[j];
-                    const bool bd = lip_bonded(wb, v.where[j]);
-                    if (!lip_term(lip_pair(tb, tjt, bd, lip_r2(p.xn, xj, box, half), st.lip_eps_ww),
-                                  lip_pair(tb, tjt, bd, lip_r2(o, xj, box, half), st.lip_eps_ww), tj))
-                        tj = kFxBad;
-                }
-                tbuf[c * 64 + lane] = tj;
-            }
-        } else {
-            const int lipid = (int)mul_shift(a.x, (uint32_t)st.nmol);
-            p.lipid = lipid;
-            const int end = (int)(u.z >> 31);
-            const int l0 = v.lip[3 * lipid], l1 = v.lip[3 * lipid + 1], l2 = v.lip[3 * lipid + 2];
-            const int e = end == 0 ? l0 : l2;
-            const float xe[3] = {v.x[3 * e], v.x[3 * e + 1], v.x[3 * e + 2]};
-            for (int c = wave; c < nch; c += nwave) {
-                const int j = c * 64 + lane;
-                bool hit = false;
-                if (j < st.nb && j != e && v.type[j] == kW) hit = lip_r2(xe, v.x + 3 * j, box, half) < kLipR2;
-                const unsigned long long m = __ballot(hit);
-                if (lane == 0) mask1[c] = m;
-            }
-            __syncthreads();
-            int nc = 0;
-            for (int c = 0; c < nch; ++c) nc += __builtin_popcountll(mask1[c]);
-            if (nc == 0) {
-                p.ok = false;
-            } else {
-                int pick = (int)mul_shift(u.w, (uint32_t)nc);
-                int cap = -1;
-                for (int c = 0; c < nch && cap < 0; ++c) {
-                    unsigned long long m = mask1[c];
-                    const int cnt = __builtin_popcountll(m);
-                    if (pick < cnt) {
-                        for (int r = pick; r > 0; --r) m &= m - 1ull;
-                        cap = c * 64 + (int)__builtin_ctzll(m);
-                    } else {
-                        pick -= cnt;
-                    }
-                }
-                int rel;
-                if (end == 0) { p.nl[0] = cap; p.nl[1] = l0; p.nl[2] = l1; rel = l2; }
-                else { p.nl[0] = l1; p.nl[1] = l2; p.nl[2] = cap; rel = l0; }
-                int all[4] = {cap, l0, l1, l2};
-                for (int i = 1; i < 4; ++i)
-                    for (int q = i; q > 0 && all[q - 1] > all[q]; --q) {
-                        const int tq = all[q]; all[q] = all[q - 1]; all[q - 1] = tq;
-                    }
-                for (int i = 0; i < 4; ++i) {
-                    const int q = all[i];
-                    p.c[i] = q;
-                    if (q == rel) { p.nt[i] = kW; p.nwh[i] = -1; }
-                    else {
-                        const int pos = q == p.nl[0] ? 0 : (q == p.nl[1] ? 1 : 2);
-                        p.nt[i] = pos == 0 ? kP : kH;
-                        p.nwh[i] = 3 * lipid + pos;
-                    }
-                }
-                p.nc = nc;
-                // n_r: solvent within R of l1 under the new types
-                const float x1[3] = {v.x[3 * l1], v.x[3 * l1 + 1], v.x[3 * l1 + 2]};
-                for (int c = wave; c < nch; c += nwave) {
-                    const int j = c * 64 + lane;
-                    bool hit = false;
-                    if (j < st.nb && j != l1) {
-                        int tj = v.type[j];
-                        for (int i = 0; i < 4; ++i)
-                            if (p.c[i] == j) tj = p.nt[i];
-                        if (tj == kW) hit = lip_r2(x1, v.x + 3 * j, box, half) < kLipR2;
-                    }
-                    const unsigned long long m = __ballot(hit);
-                    if (lane == 0) mask2[c] = m;
-                }
-                // partner terms of the reptation (see lip_propose)
-                for (int c = wave; c < nch; c += nwave) {
-                    const int j = c * 64 + lane;
-                    int64_t tj = 0;
-                    bool bad = false;
-                    if (j < st.nb) {
-                        const int tjo = v.type[j], wjo = v.where[j];
-                        int tjn = tjo, wjn = wjo;
-                        bool jin = false;
-                        for (int i = 0; i < 4; ++i)
-                            if (p.c[i] == j) { jin = true; tjn = p.nt[i]; wjn = p.nwh[i]; }
-                        for (int i = 0; i < 4; ++i) {
-                            const int ci = p.c[i];
-                            if (ci == j || (jin && ci > j)) continue;
-                            const double r2 = lip_r2(v.x + 3 * ci, v.x + 3 * j, box, half);
-                            int64_t d = 0;
-                            bad |= !lip_term(lip_pair(p.nt[i], tjn, lip_bonded(p.nwh[i], wjn), r2, st.lip_eps_ww),
-                                             lip_pair(v.type[ci], tjo, lip_bonded(v.where[ci], wjo), r2,
-                                                      st.lip_eps_ww),
-                                             d);
-                            tj += d;
-                        }
-                    }
-                    tbuf[c * 64 + lane] = bad ? kFxBad : tj;
-                }
-            }
-        }
-        __syncthreads();
-        if (wave == 0) {
-            if (p.ok) {
-                int64_t acc = 0;
-                bool bad = false;
-                for (int c = 0; c < nch; ++c) {
-                    const int64_t tj = tbuf[c * 64 + lane];
-                    if (tj == kFxBad) bad = true;
-                    else acc += tj;
-                }
-                p.de = wave_sum64(acc);
-                p.ok = __ballot(bad) == 0ull;
-                if (p.rep) {
-                    int nr = 0;
-                    for (int c = 0; c < nch; ++c) nr += __builtin_popcountll(mask2[c]);
-                    p.nr = nr;
-                }
-                int64_t e_new = 0;
-                if (p.ok && fx_add(Ef, p.de, e_new)) {
-                    const int bn = lip_bin(st, e_new);
-                    if (bn >= lo && bn <= hi && lip_accept(p, g[E - lo] - g[bn - lo], u.x)) {
-                        lip_apply(st, v, p, lane);
-                        Ef = e_new;
-                        E = bn;
-                    }
-                }
-            }
-            if (lane == 0) {
-                g[E - lo] = g[E - lo] + lnf;
-                H[E - lo] += 1u;
-            }
-        }
-        __syncthreads();
-    }
+    LipidMoves md;
+    md.v = lip_view(st, smem);
+    md.x = md.v.x;
+    md.box = st.box;
+    md.half = 0.5f * st.box;
+    md.scale = 65536.0f / st.box;
+    md.eps_ww = st.lip_eps_ww;
+    md.mask1 = (unsigned long long *)rep;
+    md.mask2 = md.mask1 + nch;
+    md.wsum = (int64_t *)(md.mask2 + nch);
+    md.grid = has_grid ? (MoveGrid *)(md.wsum + nwave) : nullptr;
+    move_sweep<LipidMoves, 0>(st, md, w, s0, n, g, nullptr, nullptr, H, mv);
     const uint32_t *sx = (const uint32_t *)smem;
     uint32_t *ox = (uint32_t *)(st.spins + (size_t)w * st.Npad);
     for (int i = threadIdx.x; i < st.Npad / 4; i += blockDim.x) ox[i] = sx[i];
     for (int b = threadIdx.x; b < W; b += blockDim.x) {
         st.lng[row + b] = g[b];
         st.H[row + b] = H[b];
-    }
-    if (threadIdx.x == 0) {
-        st.E[w] = E;
-        st.Efx[w] = Ef;
     }
 }
 
@@ -642,14 +639,10 @@ hipError_t lip_allow(const void *fn, size_t bytes) {
 
 }  // namespace
 
-static int lipid_waves(const DevState &st) {
-    const int nch = (st.nb + 63) / 64;
-    return nch < 16 ? nch : 16;
+static MovePlan lipid_plan(const DevState &st) {
+    return move_plan((size_t)st.Npad + (size_t)st.Wpad * 12 + lip_rep_bytes((st.nb + 63) / 64), kLipRepPerWave, st.nb);
 }
-size_t lipid_sweep_lds_bytes(const DevState &st) {
-    const int nch = (st.nb + 63) / 64;
-    return (size_t)st.Npad + (size_t)st.Wpad * 12 + (size_t)nch * 64 * 8 + (size_t)nch * 16;
-}
+size_t lipid_sweep_lds_bytes(const DevState &st) { return lipid_plan(st).lds; }
 size_t lipid_walkin_lds_bytes(const DevState &st) { return (size_t)st.Npad + (size_t)st.Bpad * 4; }
 
 hipError_t launch_lipid_init(const DevState &st, hipStream_t s) {
@@ -666,10 +659,10 @@ hipError_t launch_lipid_walkin(const DevState &st, int64_t chunk, int64_t budget
 }
 
 hipError_t launch_lipid_sweep(const DevState &st, int64_t s0, int64_t n, hipStream_t s) {
-    const size_t lds = lipid_sweep_lds_bytes(st);
-    hipError_t e = lip_allow((const void *)k_lipid_sweep, lds);
+    const MovePlan p = lipid_plan(st);
+    const hipError_t e = lip_allow((const void *)k_lipid_sweep, p.lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_lipid_sweep, dim3(st.nw), dim3(64 * lipid_waves(st)), lds, s, st, s0, n);
+    hipLaunchKernelGGL(k_lipid_sweep, dim3(st.nw), dim3(64 * p.waves), p.lds, s, st, s0, n, p.grid);
     return hipGetLastError();
 }
 

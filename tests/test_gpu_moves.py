@@ -1,0 +1,80 @@
+"""GPU parity of the block-wise displacement attempts (rewl_moves.h) where
+their launch or their arithmetic takes another path: workgroups cut down by the
+LDS, places without their 16-bit copies, boxes smaller than the cut-off or far
+larger than it, particles drawn several times in a block, weights of minus
+infinity, energies more than 2^20 bins away.  Integers and binary64 bits equal
+the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from statecmp import assert_same_state
+from test_gpu_lipid import assert_same_lipids
+from test_gpu_lipid import make_pair as lipid_pair
+from test_gpu_trimer import assert_same_energies
+from test_gpu_trimer import make_pair as trimer_pair
+
+pytestmark = pytest.mark.gpu
+
+TRIMERS = [
+    # (nmol, box, e_min, bin_w, bins, h, m, attempts, precision)
+    (16, 7.0, -40.0, 0.05, 13440, 1, 2, 1500, 0),   # two or four wavefronts beside 158 KiB of window
+    (16, 7.0, -40.0, 0.05, 12800, 1, 2, 1500, 1),   # sixteen wavefronts, no room for the 16-bit places
+    (2, 2.6, -10.0, 0.5, 400, 1, 3, 2000, 0),       # half the box below the cut-off, six beads for sixteen attempts
+    (21, 60.0, -40.0, 0.5, 600, 2, 2, 1500, 0),     # 63 beads: one partner short of a chunk
+    (43, 9.0, -60.0, 0.5, 600, 2, 2, 1200, 1),      # 129 beads: one partner in the third chunk
+]
+
+
+@pytest.mark.parametrize("nmol,box,e_min,bin_w,bins,h,m,attempts,precision", TRIMERS)
+def test_trimer_blocks(nmol, box, e_min, bin_w, bins, h, m, attempts, precision):
+    g, o = trimer_pair(nmol, box, e_min, bin_w, bins, h, m, lnf_init=0.05, fixed_lnf=1, sync_attempts=499,
+                       precision=precision, seed=5)
+    g.run(attempts)
+    o.run(attempts)
+    assert_same_state(g, o)
+    assert_same_energies(g, o)
+
+
+LIPIDS = [
+    # (nlip, nsol, box, e_min, bin_w, bins, h, m, attempts, rep_prob)
+    (4, 20, 4.3, 150.0, 0.05, 13440, 1, 1, 600, 0.2),       # two or four wavefronts
+    (125, 625, None, 7000.0, 0.1, 11200, 1, 1, 300, 0.2),   # sixteen wavefronts, no 16-bit places
+]
+
+
+@pytest.mark.parametrize("nlip,nsol,box,e_min,bin_w,bins,h,m,attempts,rep_prob", LIPIDS)
+def test_lipid_blocks(nlip, nsol, box, e_min, bin_w, bins, h, m, attempts, rep_prob):
+    g, o = lipid_pair(nlip, nsol, box or workloads.LIPID["box"], e_min, bin_w, bins, h, m, rep_prob=rep_prob,
+                      lnf_init=0.05, fixed_lnf=1, sync_attempts=199, seed=6)
+    g.run(attempts)
+    o.run(attempts)
+    assert_same_state(g, o)
+    assert_same_lipids(g, o)
+
+
+def test_weights_of_minus_infinity():
+    # unvisited bins of a finished piece, read back and set as weights
+    g, o = trimer_pair(8, 5.0, -30.0, 0.5, 160, 1, 2, lnf_init=0.25, fixed_lnf=1, sync_attempts=300, seed=3)
+    g.run(600)
+    o.run(600)
+    for w in range(2):
+        lng = np.where(g.walker(w)["H"] > 0, g.walker(w)["lng"], -np.inf)
+        g.set_lng(w, lng)
+        o.set_lng(w, lng)
+    g.run(900)
+    o.run(900)
+    assert_same_state(g, o)
+    assert_same_energies(g, o)
+
+
+def test_moves_beyond_a_million_bins():
+    x = workloads.init_trimers(8, 5.0, 1, 1)
+    o = oracle.Rewl.trimer(8, 5.0, -1000.0, 1.0, 4000, 1, 0.75, 1, x)
+    args = (8, 5.0, o.energy(0) - 0.006, 1e-6, 12000, 1, 1)
+    g, o = trimer_pair(*args, lnf_init=0.05, fixed_lnf=1, sync_attempts=1000, seed=3)
+    g.run(3000)
+    o.run(3000)
+    assert_same_state(g, o)
+    assert_same_energies(g, o)
