@@ -218,13 +218,13 @@ __global__ __launch_bounds__(64) void k_walkin(DevState st, int64_t chunk, int64
 // energy after the decision.
 //
 // The attempts of one walker are a strict sequence.  The kernel processes
-// them in blocks of 64 with a lane-parallel phase and a serial phase that
+// them in blocks of 64 with a lane-parallel phase and a decision phase that
 // reproduces the sequential result exactly:
 //  * lanes draw the 64 proposals and compute their energy changes from the
 //    lattice at block start.  A proposal whose site or neighbours were hit by
 //    an earlier proposal of the same block carries a conflict mask (built by
 //    OR-ing lane bits into an LDS tag table); if any of those earlier
-//    proposals was accepted, its energy change is recomputed from LDS;
+//    proposals was accepted, its energy change is computed anew;
 //  * lanes compute ln u of their uniform word; u < exp(d) is then settled by
 //    comparing d with ln u up to a margin that covers the error of exp_neg
 //    and log; attempts inside the margin evaluate exp_neg exactly, as the
@@ -232,11 +232,13 @@ __global__ __launch_bounds__(64) void k_walkin(DevState st, int64_t chunk, int64
 //  * ln g of 64 consecutive energies around the walker sit in VGPRs (lane b
 //    holds energy ebase + b; energies outside the window hold +inf, which
 //    makes any move there a certain reject).
-// The serial phase carries the walker's current ln g through every attempt
-// and compares it with the cached ln g of the proposed energy.
-// H(E) increments and accepted spins are applied to LDS once per block (no
-// two pending spin writes share a site: a repeat hit is a conflict and is
-// written at once).
+// Decisions at large ln f go from event to event (an accepted change of
+// energy, a proposal to be made again), all lanes in between being refused at
+// once; at small ln f the lanes guess and refine (see the two phases below).
+// 32 x 32 sites, 16 windows x 4 walkers, ln f = 1, ns per attempt of the
+// slowest walker: 174 with one attempt after the other, 149 from event to
+// event (31 events a block in the disordered windows, 6 in the ordered ones);
+// 8,192 walkers of mixed sizes, 32 waves a CU: 80 -> 60 ms a step.
 constexpr double kMargin64 = 1e-10;   // log-domain slack of the exact-mode test (binary64)
 constexpr double kMargin32 = 1e-5;    // log-domain slack of the exact-mode test (binary32)
 // Blocks of a window whose ln f is at most this run the speculative phase:
@@ -396,6 +398,9 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     if (spec) margins(0, M0b, Mrb);
     PhaseClock pc;
 
+    // one loop for each decision phase, so that neither carries the other's registers
+    auto blocks = [&](auto phase) {
+    constexpr bool kSpec = decltype(phase)::value;
     for (int64_t base = 0; base < n; base += 64) {
         const long long pc0 = pc.now();
         const int todo = (int)((n - base) < 64 ? (n - base) : 64);
@@ -517,7 +522,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
 
         const long long pc1 = pc.now();
         pc.add(kPcLaneCycles, pc1 - pc0);
-        if (spec) {
+        if constexpr (kSpec) {
             // ---- speculative phase (small ln f): every lane evaluates its own
             // attempt from a guess of the earlier attempts of its segment (their
             // decisions and new values); the guesses are refined until they
@@ -799,81 +804,145 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 pc.add(kPcExactCycles, pc.now() - pce);
             }
         } else {
-            // ---- serial phase: runs of attempts with no possible conflict take the
-            // inline path; the others go through slow_attempt (which settles the
-            // conflict first)
-            int j = 0;
-            while (j < todo) {
-                const unsigned long long later = anyconf & (~0ull << j);
-                const int jstop = later ? min(todo, (int)__builtin_ctzll(later)) : todo;
-                for (; j < jstop; ++j) {
-                    const int dEj = __builtin_amdgcn_readlane(dE, j);
-                    const double luj = readlane_d(lnu, j);
-                    int idx = erel + dEj;
-                    // rare: the proposed energy lies outside the register cache
-                    // (laid out of line, the common case falls through)
-                    if (__builtin_expect((unsigned)idx >= 64u, 0)) {
-                        cache_store();
-                        ebase += idx - 32;
-                        cache_load();
-                        erel = erel - idx + 32;
-                        idx = 32;
-                    }
-                    bool acc;
-                    if (PREC == 0) {
-                        const double gN = readlane_d(c64, idx);
-                        const double d = gEv - gN;
-                        const double t = d - luj;
-                        acc = __ballot(t > 0.0) != 0ull;
-                        if (__builtin_expect(__ballot(!(fabs(t) > kMargin64)) != 0ull, 0))
-                            acc = __ballot(ebase + idx >= lo && ebase + idx <= hi &&
-                                           accept64(d, __builtin_amdgcn_readlane(p.u, j))) != 0ull;
-                        gEs = acc ? gN : gEs;
-                        gEv = gEs + lnf_v;
-                        gEs = rfl(gEv);
-                        erel = acc ? idx : erel;
-                        c64 = (lane == erel) ? gEv : c64;
-                    } else {
-                        const float gNh = readlane_f(ch, idx);
-                        const float gNl = readlane_f(cl, idx);
-                        const float d = (gEh - gNh) + (gEl - gNl);
-                        const double t = (double)d - luj;
-                        acc = __ballot(t > 0.0) != 0ull;
-                        if (__builtin_expect(__ballot(!(fabs(t) > kMargin32)) != 0ull, 0))
-                            acc = __ballot(ebase + idx >= lo && ebase + idx <= hi &&
-                                           accept32(d, __builtin_amdgcn_readlane(p.u, j))) != 0ull;
-                        gEh = acc ? gNh : gEh;
-                        gEl = acc ? gNl : gEl;
-                        two_sum_add(gEh, gEl, lnf32);
-                        gEh = rfl(gEh);
-                        gEl = rfl(gEl);
-                        erel = acc ? idx : erel;
-                        ch = (lane == erel) ? gEh : ch;
-                        cl = (lane == erel) ? gEl : cl;
-                    }
-                    accepted |= acc ? (1ull << j) : 0ull;
-                    hist = writelane_i32(ebase + erel, j, hist);
+            // ---- event phase (large ln f): all lanes from attempt i on decide at
+            // once as if the attempts before them were refused; the first that
+            // is not (the event) is taken and the next round starts after it.
+            // A refused attempt only adds ln f to the walker's current bin, so
+            // lane l compares ga = ln g(E) + (l - i) ln f with ln g of its new
+            // energy; the exact ln g(E) is added up at the events.  A proposal
+            // with dE = 0 is accepted without an event (it changes a spin, not
+            // the bin).  An event is an accepted change of energy, a decision
+            // within the margin (evaluated exactly), or a proposal whose site or
+            // neighbour was flipped earlier in the block: the flips then go to
+            // the lattice and the later proposals they touch are made again.
+            const unsigned long long livem = todo == 64 ? ~0ull : ((1ull << todo) - 1ull);
+            const double slope = PREC == 0 ? lnf : (double)lnf32;
+            // ga is off by at most 64 roundings of values up to |ln g| + 64 ln f
+            const double Mc = (PREC == 0 ? kMargin64 : kMargin32) + (64.0 * slope + 1024.0) * (PREC == 0 ? 0x1p-46 : 0x1p-18);
+            unsigned long long seen = 0ull;   // accepted flips the lanes' proposals include
+            int i = 0, owed = 0;              // next attempt; visits not yet added to ln g(E)
+            double ga = 0.0, M = 0.0;
+            bool fin = true;
+            auto arrive = [&](int first) {    // at a bin whose ln g (in registers) attempt `first` meets
+                const double base = PREC == 0 ? gEv : (double)gEh + (double)gEl;
+                ga = base + (double)(lane - first) * slope;
+                M = PREC == 0 ? __builtin_fma(fabs(base), 0x1p-46, Mc)
+                              : __builtin_fma(fabs(base) * 0x1p-24 + (double)fabsf(gEl), 0x1p-18, Mc);
+                fin = __ballot(__builtin_isfinite(base)) != 0ull;
+            };
+            auto pay = [&]() {                // the visits owed, one addition each
+                for (; owed >= 4; owed -= 4) {
+                    if (PREC == 0) { gEv = gEv + lnf_v; gEv = gEv + lnf_v; gEv = gEv + lnf_v; gEv = gEv + lnf_v; }
+                    else for (int r = 0; r < 4; ++r) two_sum_add(gEh, gEl, lnf32);
                 }
+                for (; owed > 0; --owed) {
+                    if (PREC == 0) gEv = gEv + lnf_v;
+                    else two_sum_add(gEh, gEl, lnf32);
+                }
+                if (PREC == 0) c64 = lane == erel ? gEv : c64;
+                else { ch = lane == erel ? gEh : ch; cl = lane == erel ? gEl : cl; }
+            };
+            hist = ebase + erel;
+            arrive(0);
+            while (i < todo) {
+                const unsigned long long from = livem & (~0ull << i);
+                const unsigned long long zero = fin ? __ballot(dE == 0) & from : 0ull;
+                const int idx = erel + dE;
+                double gN = 0.0, t = 0.0, Mt = M;
+                float gNh = 0.0f, gNl = 0.0f;
+                if (PREC == 0) {
+                    gN = lane_read_d(c64, idx);
+                    t = (ga - gN) - lnu;
+                } else {
+                    gNh = lane_read_f(ch, idx);
+                    gNl = lane_read_f(cl, idx);
+                    const double d = ga - ((double)gNh + (double)gNl);
+                    t = d - lnu;
+                    Mt = M + (fabs(d) + (double)fabsf(gNl)) * 0x1p-18;
+                }
+                unsigned long long S = __ballot(!(t < -Mt)) & ~zero, C = 0ull;
+                if (anyconf) {
+                    C = __ballot((conf & (accepted | zero) & ~seen) != 0ull);
+                    S |= C;
+                }
+                S &= from;
+                const int j = S ? (int)__builtin_ctzll(S) : todo;
+                accepted |= zero & (j >= 64 ? ~0ull : ((1ull << j) - 1ull));
+                owed += j - i;
+                i = j;
                 if (j >= todo) break;
-                slow_attempt(j);
-                ++j;
+                if ((C >> j) & 1ull) {
+                    if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
+                    flushed = accepted;
+                    wave_lds_sync();
+                    if (lane >= j && (conf & accepted & ~seen) != 0ull) {
+                        x0 = sp[p.site];
+                        x1 = sp[p.nb0];
+                        x2 = sp[p.nb1];
+                        x3 = sp[p.nb2];
+                        x4 = sp[p.nb3];
+                        nv = x0 + 1 + p.off;
+                        if (nv >= q) nv -= q;
+                        dE = (int)(x0 == x1) + (int)(x0 == x2) + (int)(x0 == x3) + (int)(x0 == x4) -
+                             (int)(nv == x1) - (int)(nv == x2) - (int)(nv == x3) - (int)(nv == x4);
+                    }
+                    seen = accepted;
+                    continue;
+                }
+                const int dj = __builtin_amdgcn_readlane(dE, j);
+                bool acc = (__ballot(t > Mt) >> j) & 1ull;
+                pay();
+                if (!acc) {   // within the margin (or ln g not finite)
+                    const int En = ebase + erel + dj;
+                    const uint32_t u = __builtin_amdgcn_readlane(p.u, j);
+                    if (PREC == 0) {
+                        const double gj = dj ? readlane_d(gN, j) : gEv;
+                        acc = En >= lo && En <= hi && __ballot(accept64(gEv - gj, u)) != 0ull;
+                    } else {
+                        const float hj = dj ? readlane_f(gNh, j) : gEh, lj = dj ? readlane_f(gNl, j) : gEl;
+                        acc = En >= lo && En <= hi && __ballot(accept32((gEh - hj) + (gEl - lj), u)) != 0ull;
+                    }
+                }
+                if (acc) {
+                    accepted |= 1ull << j;
+                    erel += dj;
+                    if (dj) {
+                        if (PREC == 0) gEv = readlane_d(gN, j);
+                        else { gEh = readlane_f(gNh, j); gEl = readlane_f(gNl, j); }
+                    }
+                    hist = lane >= j ? ebase + erel : hist;
+                    // proposals reach four energies either side of the walker
+                    if (__builtin_expect((unsigned)(erel - 4) >= 56u, 0)) {
+                        cache_store();
+                        ebase += erel - 32;
+                        erel = 32;
+                        cache_load();
+                    }
+                }
+                arrive(j);
+                owed = 1;
+                i = j + 1;
             }
+            pay();
         }
 
         const long long pct = pc.now();
-        if (!spec) {
+        if constexpr (!kSpec) {
             p_nx = propose(st, kDomMove, (uint64_t)(s0 + base + 64 + lane), (uint32_t)w);
             lnu_nx = lnu_of(p_nx.u);
         }
         if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
         // (the speculative phase counted its visits per segment)
-        if (!spec && live) atomicAdd(&H[hist - lo], 1u);
+        if (!kSpec && live) atomicAdd(&H[hist - lo], 1u);
         const long long pcd = pc.now();
         pc.add(kPcTailCycles, pcd - pct);
         pc.add(kPcDecideCycles, pcd - pc1);
         pc.add(kPcBlocks, 1);
         pc.add(kPcAttempts, todo);
     }
+    };
+    if (spec) blocks(std::true_type{});
+    else blocks(std::false_type{});
     pc.flush(w, lane);
     cache_store();
     E = ebase + erel;
