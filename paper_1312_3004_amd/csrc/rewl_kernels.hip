@@ -288,15 +288,100 @@ __device__ __forceinline__ void walker_sync() {
     else __syncthreads();
 }
 
+// ln u of a uniform word (the acceptance compares it with a difference of ln g).
+template <int PREC>
+__device__ __forceinline__ double ln_uniform(uint32_t u) {
+    if (PREC == 0) return u == 0u ? -64.0 : log((double)u * 0x1p-32);
+    return (u >> 8) == 0u ? -64.0 : log((double)(u >> 8) * 0x1p-24);
+}
+
+// Lanes of `among` whose value (6 bits) equals v, by ballots of the bits.
+__device__ __forceinline__ int match_count(int value, int v, unsigned long long among) {
+    uint32_t lo = (uint32_t)among, hi = (uint32_t)(among >> 32);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const unsigned long long bits = __ballot((value >> k) & 1);
+        const uint32_t s = (uint32_t)((v << (31 - k)) >> 31);   // all ones if bit k of v is set
+        lo &= ~((uint32_t)bits ^ s);
+        hi &= ~((uint32_t)(bits >> 32) ^ s);
+    }
+    return __builtin_popcount(lo) + __builtin_popcount(hi);
+}
+
+// Earlier proposals of a block on the same (hashed) site as this lane's site
+// (W0) and its neighbours (W1 .. W4): every lane ORs its bit into the tag of
+// its site.  The table is zero before and after.
+__device__ __forceinline__ void conflict_masks(const Proposal &p, bool live, unsigned long long *tag,
+                                               uint32_t tag_mask, int lane, unsigned long long &W0,
+                                               unsigned long long &W1, unsigned long long &W2,
+                                               unsigned long long &W3, unsigned long long &W4) {
+    const uint32_t ti = (uint32_t)p.site & tag_mask;
+    if (live) atomicOr(&tag[ti], 1ull << lane);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    W0 = tag[ti] & below;
+    W1 = tag[(uint32_t)p.nb0 & tag_mask] & below;
+    W2 = tag[(uint32_t)p.nb1 & tag_mask] & below;
+    W3 = tag[(uint32_t)p.nb2 & tag_mask] & below;
+    W4 = tag[(uint32_t)p.nb3 & tag_mask] & below;
+    if (live) tag[ti] = 0ull;
+}
+
+// Keeps of hashed masks the proposals on exactly the same site.
+__device__ __forceinline__ void same_sites(const Proposal &p, int lane, unsigned long long &W0,
+                                           unsigned long long &W1, unsigned long long &W2,
+                                           unsigned long long &W3, unsigned long long &W4) {
+    unsigned long long cand = W0 | W1 | W2 | W3 | W4;
+    while (__ballot(cand != 0ull)) {
+        const int i = cand ? 63 - __builtin_clzll(cand) : lane;
+        const int si = __builtin_amdgcn_ds_bpermute(i << 2, p.site);
+        const unsigned long long bit = cand ? (1ull << i) : 0ull;
+        W0 = si == p.site ? W0 : W0 & ~bit;
+        W1 = si == p.nb0 ? W1 : W1 & ~bit;
+        W2 = si == p.nb1 ? W2 : W2 & ~bit;
+        W3 = si == p.nb2 ? W3 : W3 & ~bit;
+        W4 = si == p.nb3 ? W4 : W4 & ~bit;
+        cand &= ~bit;
+    }
+}
+
+// What the helper wavefront leaves of a block of 64 attempts, 64 bytes a lane
+// in four 16-byte words: site, neighbours and value offset in 16 bits each
+// (lattices up to 65,536 sites), the uniform word, ln u, the exact masks W0 .. W4.
+constexpr int kRecWords = 4 * 64;
+constexpr size_t kHelpLds = 2 * kRecWords * sizeof(uint4) + 16;
+constexpr int kHelpMaxSites = 65536;
+
+template <int PREC>
+__device__ __forceinline__ void draw_block(const DevState &st, int w, uint64_t t, int todo, unsigned long long *tag,
+                                           uint4 *out, int lane) {
+    const Proposal p = propose(st, kDomMove, t + (uint64_t)lane, (uint32_t)w);
+    unsigned long long W0, W1, W2, W3, W4;
+    conflict_masks(p, lane < todo, tag, (uint32_t)st.Ntag - 1u, lane, W0, W1, W2, W3, W4);
+    if (st.Ntag < st.N) same_sites(p, lane, W0, W1, W2, W3, W4);
+    const uint64_t lnu = (uint64_t)__double_as_longlong(ln_uniform<PREC>(p.u));
+    out[lane] = make_uint4((uint32_t)p.site | ((uint32_t)p.nb0 << 16), (uint32_t)p.nb1 | ((uint32_t)p.nb2 << 16),
+                           (uint32_t)p.nb3 | ((uint32_t)p.off << 16), p.u);
+    out[64 + lane] = make_uint4((uint32_t)lnu, (uint32_t)(lnu >> 32), (uint32_t)W0, (uint32_t)(W0 >> 32));
+    out[128 + lane] = make_uint4((uint32_t)W1, (uint32_t)(W1 >> 32), (uint32_t)W2, (uint32_t)(W2 >> 32));
+    out[192 + lane] = make_uint4((uint32_t)W3, (uint32_t)(W3 >> 32), (uint32_t)W4, (uint32_t)(W4 >> 32));
+}
+
 // GLOB: the walker's ln g and H rows stay in device memory (read and written
 // only when the register cache moves, H by atomic increments), so a walker
 // needs LDS for its lattice and tag table alone and more walkers fit a CU.
-template <int PREC, bool WAVE = false, bool GLOB = false>
+// HELP: a second wavefront (threads 64-127) draws the next block's proposals,
+// ln u and conflict masks, which depend on no spin, while the first one
+// decides the current block (see draw_block).  That is 250 of the 620 vector
+// instructions of a block of the small-ln f phase: 32 x 32 sites, 64 walkers,
+// ln f = 2^-21: 2274 -> 1945 us per 50,000 attempts; 80 x 80, 1,024 walkers:
+// 1085 -> 1001 us per 20,000.
+template <int PREC, bool WAVE = false, bool GLOB = false, bool HELP = false>
 __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t s0, int64_t n,
                                              unsigned char *smem) {
 #pragma clang fp contract(off)
     if (*st.converged) return;
     const int lane = threadIdx.x & 63;
+    const int tid = HELP ? (int)threadIdx.x : lane, nthr = HELP ? 128 : 64;
     const int k = w / st.m;
     const int W = st.W, Wpad = st.Wpad;
     const size_t row = (size_t)w * Wpad;
@@ -318,16 +403,15 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         H = (uint32_t *)(smem + st.Npad + (size_t)Wpad * 8);
         tag = (unsigned long long *)(smem + st.Npad + (size_t)Wpad * 12);
     }
-    const uint32_t tag_mask = (uint32_t)st.Ntag - 1u;
-    // visit counts of the register cache's 64 energies during the serial
-    // phase, in the first 256 bytes of the tag table (all zero outside the
-    // lane-parallel phase, at least 64 entries of 8 bytes)
-    uint32_t *cnt = (uint32_t *)tag;
+    // the helper's blocks (two, in turn), and a word of flips a segment overwrites
+    // (without a helper a word of the tag table, zero between blocks)
+    uint4 *rec = (uint4 *)(tag + st.Ntag);
+    unsigned long long *sup_w = HELP ? (unsigned long long *)(rec + 2 * kRecWords) : &tag[32];
 
     const uint32_t *gsp = (const uint32_t *)(st.spins + (size_t)w * st.Npad);
-    for (int i = lane; i < st.Npad / 4; i += 64) ((uint32_t *)sp)[i] = gsp[i];
+    for (int i = tid; i < st.Npad / 4; i += nthr) ((uint32_t *)sp)[i] = gsp[i];
     if (!GLOB) {
-        for (int b = lane; b < W; b += 64) {
+        for (int b = tid; b < W; b += nthr) {
             if (PREC == 0) {
                 g[b] = st.lng[row + b];
             } else {
@@ -337,7 +421,8 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             H[b] = st.H[row + b];
         }
     }
-    for (int i = lane; i < st.Ntag; i += 64) tag[i] = 0ull;
+    for (int i = tid; i < st.Ntag; i += nthr) tag[i] = 0ull;
+    if (HELP && tid == 0) *sup_w = 0ull;
     walker_sync<WAVE>();
 
     const int lo = st.start[k], hi = lo + W - 1;
@@ -347,7 +432,13 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     const bool spec = lnf <= kSpecLnf;
     int E = st.E[w];
     if (E < lo || E > hi) return;  // not walked in: leave the walker untouched
-
+    if (HELP && threadIdx.x >= 64) {
+        for (int64_t base = 0; base < n; base += 64) {
+            const int todo = (int)((n - base) < 64 ? (n - base) : 64);
+            draw_block<PREC>(st, w, (uint64_t)(s0 + base), todo, tag, rec + ((base >> 6) & 1) * kRecWords, lane);
+            __syncthreads();   // block `base` is drawn; the one before it has been read
+        }
+    } else {
     // ln g cache: lane b holds energy ebase + b (+inf outside the window)
     int ebase = E - 32;
     double c64 = 0.0;
@@ -375,14 +466,15 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     asm volatile("" : "+v"(lnf_v));
     double gEv = 0.0, gEs = 0.0;
     float gEh = 0.0f, gEl = 0.0f;
-    // proposal and ln u of lane j's attempt of the next block (they do not
-    // depend on the lattice, so they are drawn while the block before runs)
-    auto lnu_of = [&](uint32_t u) -> double {
-        if (PREC == 0) return u == 0u ? -64.0 : log((double)u * 0x1p-32);
-        return (u >> 8) == 0u ? -64.0 : log((double)(u >> 8) * 0x1p-24);
-    };
-    Proposal p_nx = propose(st, kDomMove, (uint64_t)(s0 + lane), (uint32_t)w);
-    double lnu_nx = lnu_of(p_nx.u);
+    // without a helper: proposal and ln u of lane j's attempt of the next block
+    // (they do not depend on the lattice, so they are drawn while the block
+    // before runs)
+    Proposal p_nx{};
+    double lnu_nx = 0.0;
+    if constexpr (!HELP) {
+        p_nx = propose(st, kDomMove, (uint64_t)(s0 + lane), (uint32_t)w);
+        lnu_nx = ln_uniform<PREC>(p_nx.u);
+    }
     // decision margin of lane j in a speculative segment from `start`: the
     // exact-mode slack plus, for each of the segment's earlier visits and the
     // two subtractions, ln f and the rounding of values up to |a| + |b| (the
@@ -411,28 +503,41 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             erel = 32;
             cache_load();
         }
-        // the current ln g rides in registers through the block
-        if (PREC == 0) { gEs = readlane_d(c64, erel); gEv = gEs; }
-        else { gEh = readlane_f(ch, erel); gEl = readlane_f(cl, erel); }
-        // ---- lane-parallel phase: proposal, energy change, conflicts, ln u
-        const Proposal p = p_nx;
-        const double lnu = lnu_nx;
+        // ---- lane-parallel phase: proposal, energy change, conflicts, ln u.
+        // W0 .. W4: earlier proposals of the block whose site is (or, without a
+        // helper, hashes like) this proposal's site, resp. one of its neighbours
+        Proposal p;
+        double lnu;
+        unsigned long long W0, W1, W2, W3, W4;
+        if constexpr (HELP) {
+            __syncthreads();
+            const uint4 *rb = rec + ((base >> 6) & 1) * kRecWords + lane;
+            const uint4 r0 = rb[0], r1 = rb[64], r2 = rb[128], r3 = rb[192];
+            p.site = (int)(r0.x & 0xffffu);
+            p.nb0 = (int)(r0.x >> 16);
+            p.nb1 = (int)(r0.y & 0xffffu);
+            p.nb2 = (int)(r0.y >> 16);
+            p.nb3 = (int)(r0.z & 0xffffu);
+            p.off = (int)(r0.z >> 16);
+            p.u = r0.w;
+            lnu = __longlong_as_double((long long)(((uint64_t)r1.y << 32) | r1.x));
+            W0 = ((uint64_t)r1.w << 32) | r1.z;
+            W1 = ((uint64_t)r2.y << 32) | r2.x;
+            W2 = ((uint64_t)r2.w << 32) | r2.z;
+            W3 = ((uint64_t)r3.y << 32) | r3.x;
+            W4 = ((uint64_t)r3.w << 32) | r3.z;
+        } else {
+            p = p_nx;
+            lnu = lnu_nx;
+            conflict_masks(p, live, tag, (uint32_t)st.Ntag - 1u, lane, W0, W1, W2, W3, W4);
+        }
         // spins of the site and its neighbours at block start
         int x0 = sp[p.site], x1 = sp[p.nb0], x2 = sp[p.nb1], x3 = sp[p.nb2], x4 = sp[p.nb3];
         int nv = x0 + 1 + p.off;
         if (nv >= q) nv -= q;
         int dE = (int)(x0 == x1) + (int)(x0 == x2) + (int)(x0 == x3) + (int)(x0 == x4) - (int)(nv == x1) -
                  (int)(nv == x2) - (int)(nv == x3) - (int)(nv == x4);
-        const uint32_t ti = (uint32_t)p.site & tag_mask;
-        if (live) atomicOr(&tag[ti], 1ull << lane);
-        const unsigned long long below = (1ull << lane) - 1ull;
-        // earlier proposals of the block whose site is (or hashes like) this
-        // proposal's site, resp. one of its neighbours
-        unsigned long long W0 = tag[ti] & below, W1 = tag[(uint32_t)p.nb0 & tag_mask] & below,
-                           W2 = tag[(uint32_t)p.nb1 & tag_mask] & below, W3 = tag[(uint32_t)p.nb2 & tag_mask] & below,
-                           W4 = tag[(uint32_t)p.nb3 & tag_mask] & below;
         unsigned long long conf = W0 | W1 | W2 | W3 | W4;
-        if (live) tag[ti] = 0ull;
         unsigned long long anyconf = __ballot(conf != 0ull);
 
         unsigned long long accepted = 0ull, flushed = 0ull;
@@ -541,21 +646,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             // energy outside the cache) ends the segment and runs through
             // slow_attempt; the next segment starts after it.
             const unsigned long long livem = todo == 64 ? ~0ull : ((1ull << todo) - 1ull);
-            if (st.Ntag < st.N) {
-                // hashed tag table: keep only proposals on exactly the same site
-                unsigned long long cand = conf;
-                while (__ballot(cand != 0ull)) {
-                    const int i = cand ? 63 - __builtin_clzll(cand) : lane;
-                    const int si = __builtin_amdgcn_ds_bpermute(i << 2, p.site);
-                    const unsigned long long bit = cand ? (1ull << i) : 0ull;
-                    W0 = si == p.site ? W0 : W0 & ~bit;
-                    W1 = si == p.nb0 ? W1 : W1 & ~bit;
-                    W2 = si == p.nb1 ? W2 : W2 & ~bit;
-                    W3 = si == p.nb2 ? W3 : W3 & ~bit;
-                    W4 = si == p.nb3 ? W4 : W4 & ~bit;
-                    cand &= ~bit;
-                }
-            }
+            if (!HELP && st.Ntag < st.N) same_sites(p, lane, W0, W1, W2, W3, W4);
             int start = 0;
             while (start < todo) {
                 pc.add(kPcSegments, 1);
@@ -578,9 +669,9 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 // proposals (independent work that fills the round's waits)
                 auto round = [&](auto first) {
                     pc.add(kPcRounds, 1);
-                    if constexpr (decltype(first)::value) {
+                    if constexpr (decltype(first)::value && !HELP) {
                         p_nx = propose(st, kDomMove, (uint64_t)(s0 + base + 64 + lane), (uint32_t)w);
-                        lnu_nx = lnu_of(p_nx.u);
+                        lnu_nx = ln_uniform<PREC>(p_nx.u);
                     }
                     constexpr bool kFirst = decltype(first)::value;
                     const unsigned long long Aa = A & act;
@@ -693,27 +784,21 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                     // hits the same site
                     unsigned long long sup = 0ull;
                     if (__ballot(mine_acc && (W0 & aseg) != 0ull)) {
-                        if (mine_acc && (W0 & aseg) != 0ull) atomicOr(&tag[32], W0 & aseg);
+                        if (mine_acc && (W0 & aseg) != 0ull) atomicOr(sup_w, W0 & aseg);
                         wave_lds_sync();
-                        sup = tag[32];
+                        sup = *sup_w;
                         wave_lds_sync();
-                        if (lane == 0) tag[32] = 0ull;
+                        if (lane == 0) *sup_w = 0ull;
                     }
                     if (mine_acc && !((sup >> lane) & 1ull)) sp[p.site] = (int8_t)nvi;
                     nv = inseg ? nvi : nv;
                     dE = inseg ? dEi : dE;
                     hist = inseg ? ej : hist;
-                    if (inseg) atomicAdd(&cnt[ej - ebase], 1u);
-                    wave_lds_sync();
-                    uint32_t nb = cnt[lane];
-                    cnt[lane] = 0u;
-                    // the segment's visits go to H here, one add per energy (device-
-                    // memory rows: atomic, since a later block may read the bin from
-                    // another lane)
-                    if (nb != 0u) {
-                        if (GLOB) atomicAdd(&H[ebase + lane - lo], nb);
-                        else H[ebase + lane - lo] += nb;
-                    }
+                    // visits of lane's energy: the segment's lanes that ended there
+                    uint32_t nb = (uint32_t)match_count(ej - ebase, lane, seg);
+                    // the segment's visits go to H here, one add per energy (atomic:
+                    // a later block may add to the bin from another lane)
+                    if (nb != 0u) atomicAdd(&H[ebase + lane - lo], nb);
                     if (PREC == 0 && nb != 0u) {
                         // n sequential adds of ln f in closed form: after the first
                         // add, every add moves x by the same exact step d2 while x
@@ -772,10 +857,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 if (PREC == 0) { gEs = readlane_d(c64, erel); gEv = gEs; }
                 else { gEh = readlane_f(ch, erel); gEl = readlane_f(cl, erel); }
                 slow_attempt(c);
-                if (lane == 0) {
-                    if (GLOB) atomicAdd(&H[ebase + erel - lo], 1u);
-                    else H[ebase + erel - lo] += 1u;
-                }
+                if (lane == 0) atomicAdd(&H[ebase + erel - lo], 1u);
                 start = c + 1;
                 // every accepted flip so far goes to the lattice; proposals after
                 // c that one of them touched read their spins from it again
@@ -842,6 +924,8 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 if (PREC == 0) c64 = lane == erel ? gEv : c64;
                 else { ch = lane == erel ? gEh : ch; cl = lane == erel ? gEl : cl; }
             };
+            if (PREC == 0) gEv = readlane_d(c64, erel);
+            else { gEh = readlane_f(ch, erel); gEl = readlane_f(cl, erel); }
             hist = ebase + erel;
             arrive(0);
             while (i < todo) {
@@ -927,9 +1011,9 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         }
 
         const long long pct = pc.now();
-        if constexpr (!kSpec) {
+        if constexpr (!kSpec && !HELP) {
             p_nx = propose(st, kDomMove, (uint64_t)(s0 + base + 64 + lane), (uint32_t)w);
-            lnu_nx = lnu_of(p_nx.u);
+            lnu_nx = ln_uniform<PREC>(p_nx.u);
         }
         if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
         // (the speculative phase counted its visits per segment)
@@ -946,11 +1030,12 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     pc.flush(w, lane);
     cache_store();
     E = ebase + erel;
+    }
     walker_sync<WAVE>();
     uint32_t *osp = (uint32_t *)(st.spins + (size_t)w * st.Npad);
-    for (int i = lane; i < st.Npad / 4; i += 64) osp[i] = ((uint32_t *)sp)[i];
+    for (int i = tid; i < st.Npad / 4; i += nthr) osp[i] = ((uint32_t *)sp)[i];
     if (!GLOB) {
-        for (int b = lane; b < W; b += 64) {
+        for (int b = tid; b < W; b += nthr) {
             if (PREC == 0) {
                 st.lng[row + b] = g[b];
             } else {
@@ -960,21 +1045,15 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             st.H[row + b] = H[b];
         }
     }
-    if (lane == 0) st.E[w] = E;
+    if (tid == 0) st.E[w] = E;
 }
 
-template <int PREC>
-__global__ __launch_bounds__(64) void k_sweep(DevState st, int64_t s0, int64_t n) {
+// GLOB: for a run whose ln g and H rows do not fit in LDS beside the lattice;
+// the rows stay in device memory.
+template <int PREC, bool GLOB, bool HELP>
+__global__ __launch_bounds__(HELP ? 128 : 64) void k_sweep(DevState st, int64_t s0, int64_t n) {
     extern __shared__ __align__(16) unsigned char smem[];
-    sweep_walker<PREC>(st, blockIdx.x, s0, n, smem);
-}
-
-// The same walk for a run whose ln g and H rows do not fit in LDS beside the
-// lattice: the rows stay in device memory (see sweep_walker's GLOB form).
-template <int PREC>
-__global__ __launch_bounds__(64) void k_sweep_glob(DevState st, int64_t s0, int64_t n) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    sweep_walker<PREC, false, true>(st, blockIdx.x, s0, n, smem);
+    sweep_walker<PREC, false, GLOB, HELP>(st, blockIdx.x, s0, n, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -2071,18 +2150,37 @@ hipError_t launch_walkin(const DevState &st, int64_t chunk, int64_t budget, hipS
     return hipGetLastError();
 }
 
+// A helper wavefront per walker where the chip has SIMDs to spare: at most
+// four walkers a CU, all resident (the tag table gives way, down to 64
+// entries, so that the helper's blocks fit).
+static bool sweep_helped(const DevState &st, DevState *out) {
+    constexpr int kCUs = 256, kPerCu = 4;
+    const int per_cu = (st.nw + kCUs - 1) / kCUs;
+    if (per_cu > kPerCu || st.N > kHelpMaxSites) return false;
+    *out = st;
+    while (out->Ntag > 64 && (size_t)per_cu * (sweep_lds_bytes(*out) + kHelpLds) > kLdsBytes) out->Ntag /= 2;
+    return (size_t)per_cu * (sweep_lds_bytes(*out) + kHelpLds) <= kLdsBytes;
+}
+
 hipError_t launch_sweep(const DevState &st, int64_t s0, int64_t n, hipStream_t s) {
     if (st.model == kModelTrimer3D) return launch_trimer_sweep(st, s0, n, s);
     if (st.model == kModelLipid3D) return launch_lipid_sweep(st, s0, n, s);
-    const size_t lds = sweep_lds_bytes(st);
+    DevState hs;
+    const bool help = sweep_helped(st, &hs);
+    const DevState &d = help ? hs : st;
+    const size_t lds = sweep_lds_bytes(d) + (help ? kHelpLds : 0);
     auto go = [&](auto kernel) -> hipError_t {
         hipError_t e = allow_lds((const void *)kernel, lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(st.nw), dim3(64), lds, s, st, s0, n);
+        hipLaunchKernelGGL(kernel, dim3(st.nw), dim3(help ? 128 : 64), lds, s, d, s0, n);
         return hipGetLastError();
     };
-    if (st.rows_glob) return st.precision == 0 ? go(k_sweep_glob<0>) : go(k_sweep_glob<1>);
-    return st.precision == 0 ? go(k_sweep<0>) : go(k_sweep<1>);
+    if (help) {
+        if (st.rows_glob) return st.precision == 0 ? go(k_sweep<0, true, true>) : go(k_sweep<1, true, true>);
+        return st.precision == 0 ? go(k_sweep<0, false, true>) : go(k_sweep<1, false, true>);
+    }
+    if (st.rows_glob) return st.precision == 0 ? go(k_sweep<0, true, false>) : go(k_sweep<1, true, false>);
+    return st.precision == 0 ? go(k_sweep<0, false, false>) : go(k_sweep<1, false, false>);
 }
 
 hipError_t launch_sync(const DevState &st, int64_t attempts, hipStream_t s) {
