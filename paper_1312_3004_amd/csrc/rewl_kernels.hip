@@ -132,85 +132,6 @@ __global__ __launch_bounds__(256) void k_init_energy(DevState st) {
 }
 
 // ---------------------------------------------------------------------------
-// Walk-in: a Wang-Landau walk over all 2N+1 energies with ln f = 1, run until
-// the walker's energy first lies in its own window (every walker must start
-// inside its window, Sec. 3.2).  With ln f = 1 every ln g entry is an integer
-// visit count, kept exactly as uint32 in LDS.  A walker above its window
-// walks under a lid (moves more than walkin_slack above the lowest energy
-// reached are rejected), a walker below it above a floor; the flooded band
-// then stays walkin_slack wide instead of spanning the whole way down.  Runs at most `chunk`
-// attempts per launch; the host relaunches until every walker is placed.
-__device__ __forceinline__ void walkin_walker(const DevState &st, int w, int64_t chunk, int64_t budget,
-                                              unsigned char *smem) {
-    const int lane = threadIdx.x;
-    if (st.walkin_done[w]) return;
-    int8_t *sp = (int8_t *)smem;
-    uint32_t *cnt = (uint32_t *)(smem + st.Npad);
-    const uint32_t *gsp = (const uint32_t *)(st.spins + (size_t)w * st.Npad);
-    for (int i = lane; i < st.Npad / 4; i += 64) ((uint32_t *)sp)[i] = gsp[i];
-    const uint32_t *gcnt = st.walkin_cnt + (size_t)w * st.Bpad;
-    for (int b = lane; b < st.B; b += 64) cnt[b] = gcnt[b];
-    __syncthreads();
-
-    const int k = w / st.m;
-    const int lo = st.start[k], hi = lo + st.W - 1;
-    const int e_lo = st.e_lo, q = st.q;
-    int E = st.E[w];
-    int64_t t = st.walkin_att[w];
-    const int slack = st.walkin_slack;
-    const bool down = E > hi;
-    int bound = t == 0 ? (down ? E + slack : E - slack) : st.walkin_bound[w];
-    const int64_t end = (t + chunk < budget) ? t + chunk : budget;
-    bool done = (E >= lo && E <= hi);
-    while (!done && t < end) {
-        const Proposal p = propose(st, kDomWalkin, (uint64_t)(t + lane), (uint32_t)w);
-        const int todo = (int)((end - t) < 64 ? (end - t) : 64);
-        for (int j = 0; j < todo; ++j) {
-            const int site = __builtin_amdgcn_readlane(p.site, j);
-            const int off = __builtin_amdgcn_readlane(p.off, j);
-            const uint32_t u = __builtin_amdgcn_readlane(p.u, j);
-            const int n0 = __builtin_amdgcn_readlane(p.nb0, j);
-            const int n1 = __builtin_amdgcn_readlane(p.nb1, j);
-            const int n2 = __builtin_amdgcn_readlane(p.nb2, j);
-            const int n3 = __builtin_amdgcn_readlane(p.nb3, j);
-            const int sc = rfl((int)sp[site]);
-            int nv = sc + 1 + off;
-            if (nv >= q) nv -= q;
-            const int En = E + rfl(delta_e(sp, sc, nv, n0, n1, n2, n3));
-            const int64_t ci = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(cnt[E - e_lo]);
-            const int64_t cn = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane(cnt[En - e_lo]);
-            const double d = (double)(ci - cn);
-            const bool inside = slack == 0 || (down ? En <= bound : En >= bound);
-            if (inside && accept64(d, u)) {
-                if (lane == 0) sp[site] = (int8_t)nv;
-                E = En;
-                if (slack && down && E + slack < bound) bound = E + slack;
-                if (slack && !down && E - slack > bound) bound = E - slack;
-            }
-            if (lane == 0) cnt[E - e_lo] += 1u;
-            ++t;
-            if (E >= lo && E <= hi) { done = true; break; }
-        }
-    }
-    __syncthreads();
-    uint32_t *osp = (uint32_t *)(st.spins + (size_t)w * st.Npad);
-    for (int i = lane; i < st.Npad / 4; i += 64) osp[i] = ((uint32_t *)sp)[i];
-    uint32_t *ocnt = st.walkin_cnt + (size_t)w * st.Bpad;
-    for (int b = lane; b < st.B; b += 64) ocnt[b] = cnt[b];
-    if (lane == 0) {
-        st.E[w] = E;
-        st.walkin_att[w] = t;
-        st.walkin_done[w] = done ? 1 : 0;
-        st.walkin_bound[w] = bound;
-    }
-}
-
-__global__ __launch_bounds__(64) void k_walkin(DevState st, int64_t chunk, int64_t budget) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    walkin_walker(st, blockIdx.x, chunk, budget, smem);
-}
-
-// ---------------------------------------------------------------------------
 // Main-phase Wang-Landau attempts (Sec. 2): n attempts of every walker,
 // attempt indices s0 .. s0+n-1.  Per attempt: propose a single spin flip,
 // reject it if the new energy leaves the window, else accept with
@@ -364,6 +285,184 @@ __device__ __forceinline__ void draw_block(const DevState &st, int w, uint64_t t
     out[64 + lane] = make_uint4((uint32_t)lnu, (uint32_t)(lnu >> 32), (uint32_t)W0, (uint32_t)(W0 >> 32));
     out[128 + lane] = make_uint4((uint32_t)W1, (uint32_t)(W1 >> 32), (uint32_t)W2, (uint32_t)(W2 >> 32));
     out[192 + lane] = make_uint4((uint32_t)W3, (uint32_t)(W3 >> 32), (uint32_t)W4, (uint32_t)(W4 >> 32));
+}
+
+// ---------------------------------------------------------------------------
+// Walk-in: a Wang-Landau walk over all 2N+1 energies with ln f = 1, run until
+// the walker's energy first lies in its own window (every walker must start
+// inside its window, Sec. 3.2).  With ln f = 1 every ln g entry is an integer
+// visit count, kept exactly as uint32 in LDS (and as binary64 in the register
+// cache).  A walker above its window walks under a lid (moves more than
+// walkin_slack above the lowest energy reached are rejected), a walker below
+// it above a floor; the flooded band then stays walkin_slack wide instead of
+// spanning the whole way down.  Runs at most `chunk` attempts per launch; the
+// host relaunches until every walker is placed.
+//
+// Blocks of 64 attempts are decided from event to event as in the main phase
+// (sweep_walker): 32 x 32 sites, 64 walkers from random lattices, 130 -> 18.5 ms
+// from creation to the last walker placed, against one attempt after the other.
+// Entries of its conflict-tag table: one per site up to 1,024 (hashed beyond:
+// a collision only has a proposal made again), as far as `lds` bytes hold them
+// beside the lattice and the counts (64 always fit).
+__host__ __device__ inline int walkin_tags(const DevState &st, size_t lds) {
+    const size_t state = (size_t)st.Npad + (size_t)st.Bpad * 4;
+    int t = 64;
+    while (t < st.N && t < 1024 && state + (size_t)t * 16 <= lds) t *= 2;
+    return t;
+}
+__device__ __forceinline__ void walkin_walker(const DevState &st, int w, int64_t chunk, int64_t budget, int ntag,
+                                              unsigned char *smem) {
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x;
+    if (st.walkin_done[w]) return;
+    int8_t *sp = (int8_t *)smem;
+    uint32_t *cnt = (uint32_t *)(smem + st.Npad);
+    unsigned long long *tag = (unsigned long long *)(smem + st.Npad + (size_t)st.Bpad * 4);
+    const uint32_t *gsp = (const uint32_t *)(st.spins + (size_t)w * st.Npad);
+    for (int i = lane; i < st.Npad / 4; i += 64) ((uint32_t *)sp)[i] = gsp[i];
+    const uint32_t *gcnt = st.walkin_cnt + (size_t)w * st.Bpad;
+    for (int b = lane; b < st.B; b += 64) cnt[b] = gcnt[b];
+    for (int i = lane; i < ntag; i += 64) tag[i] = 0ull;
+    __syncthreads();
+
+    const int k = w / st.m;
+    const int lo = st.start[k], hi = lo + st.W - 1;
+    const int e_lo = st.e_lo, B = st.B, q = st.q;
+    int E = rfl(st.E[w]);
+    int64_t t = st.walkin_att[w];
+    const int slack = st.walkin_slack;
+    const bool down = E > hi;
+    int bound = rfl(t == 0 ? (down ? E + slack : E - slack) : st.walkin_bound[w]);
+    const int64_t end = (t + chunk < budget) ? t + chunk : budget;
+    bool done = (E >= lo && E <= hi);
+    // visit counts of 64 energies around the walker: lane b holds energy ebase + b
+    int ebase = E - 32, erel = 32;
+    double c64 = 0.0;
+    auto cache_load = [&]() {
+        const int b = ebase + lane - e_lo;
+        c64 = b >= 0 && b < B ? (double)cnt[b] : __builtin_inf();
+    };
+    auto cache_store = [&]() {
+        const int b = ebase + lane - e_lo;
+        if (b >= 0 && b < B) cnt[b] = (uint32_t)c64;
+    };
+    cache_load();
+    while (!done && t < end) {
+        const Proposal p = propose(st, kDomWalkin, (uint64_t)(t + lane), (uint32_t)w);
+        const double lnu = ln_uniform<0>(p.u);
+        const int todo = (int)((end - t) < 64 ? (end - t) : 64);
+        const unsigned long long livem = todo == 64 ? ~0ull : ((1ull << todo) - 1ull);
+        unsigned long long W0, W1, W2, W3, W4;
+        conflict_masks(p, lane < todo, tag, (uint32_t)ntag - 1u, lane, W0, W1, W2, W3, W4);
+        const unsigned long long conf = W0 | W1 | W2 | W3 | W4;
+        const unsigned long long anyconf = __ballot(conf != 0ull);
+        int x0 = sp[p.site], x1 = sp[p.nb0], x2 = sp[p.nb1], x3 = sp[p.nb2], x4 = sp[p.nb3];
+        int nv = 0, dE = 0;
+        auto make = [&]() {
+            nv = x0 + 1 + p.off;
+            if (nv >= q) nv -= q;
+            dE = (int)(x0 == x1) + (int)(x0 == x2) + (int)(x0 == x3) + (int)(x0 == x4) - (int)(nv == x1) -
+                 (int)(nv == x2) - (int)(nv == x3) - (int)(nv == x4);
+        };
+        make();
+        unsigned long long accepted = 0ull, flushed = 0ull, seen = 0ull;
+        int i = 0;
+        while (i < todo) {
+            // counts are integers below 2^32: every sum and difference is exact,
+            // the margin covers ln u and exp alone
+            const unsigned long long from = livem & (~0ull << i);
+            const unsigned long long zero = __ballot(dE == 0) & from;
+            const int idx = erel + dE, En = ebase + idx;
+            const double cN = lane_read_d(c64, idx);
+            const double cE = readlane_d(c64, erel);
+            const double tt = ((cE + (double)(lane - i)) - cN) - lnu;
+            const bool inside = slack == 0 || (down ? En <= bound : En >= bound);
+            const bool maybe = inside && !(tt < -kMargin64);
+            unsigned long long S = __ballot(maybe) & ~zero, C = 0ull;
+            if (anyconf) {
+                C = __ballot((conf & (accepted | zero) & ~seen) != 0ull);
+                S |= C;
+            }
+            S &= from;
+            const int j = S ? (int)__builtin_ctzll(S) : todo;
+            accepted |= zero & (j >= 64 ? ~0ull : ((1ull << j) - 1ull));
+            double cNow = cE + (double)(j - i);     // refused attempts count at the walker's energy
+            i = j;
+            if (j < todo && ((C >> j) & 1ull)) {
+                c64 = lane == erel ? cNow : c64;
+                if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
+                flushed = accepted;
+                wave_lds_sync();
+                if (lane >= j && (conf & accepted & ~seen) != 0ull) {
+                    x0 = sp[p.site];
+                    x1 = sp[p.nb0];
+                    x2 = sp[p.nb1];
+                    x3 = sp[p.nb2];
+                    x4 = sp[p.nb3];
+                    make();
+                }
+                seen = accepted;
+                continue;
+            }
+            if (j >= todo) {
+                c64 = lane == erel ? cNow : c64;
+                break;
+            }
+            const int dj = __builtin_amdgcn_readlane(dE, j);
+            bool acc = (__ballot(tt > kMargin64) >> j) & 1ull;
+            if (!acc)
+                acc = __ballot(accept64(cNow - readlane_d(cN, j), __builtin_amdgcn_readlane(p.u, j))) != 0ull;
+            if (acc) {
+                c64 = lane == erel ? cNow : c64;
+                accepted |= 1ull << j;
+                erel += dj;
+                cNow = readlane_d(c64, erel);
+            }
+            c64 = lane == erel ? cNow + 1.0 : c64;
+            i = j + 1;
+            if (acc) {
+                E = ebase + erel;
+                if (slack && down && E + slack < bound) bound = E + slack;
+                if (slack && !down && E - slack > bound) bound = E - slack;
+                if (E >= lo && E <= hi) {
+                    done = true;
+                    break;
+                }
+                // proposals reach four energies either side of the walker
+                if ((unsigned)(erel - 4) >= 56u) {
+                    cache_store();
+                    ebase += erel - 32;
+                    erel = 32;
+                    cache_load();
+                }
+            }
+        }
+        t += i;
+        if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
+        if ((unsigned)(erel - 16) >= 32u) {
+            cache_store();
+            ebase += erel - 32;
+            erel = 32;
+            cache_load();
+        }
+    }
+    cache_store();
+    __syncthreads();
+    uint32_t *osp = (uint32_t *)(st.spins + (size_t)w * st.Npad);
+    for (int i = lane; i < st.Npad / 4; i += 64) osp[i] = ((uint32_t *)sp)[i];
+    uint32_t *ocnt = st.walkin_cnt + (size_t)w * st.Bpad;
+    for (int b = lane; b < st.B; b += 64) ocnt[b] = cnt[b];
+    if (lane == 0) {
+        st.E[w] = ebase + erel;
+        st.walkin_att[w] = t;
+        st.walkin_done[w] = done ? 1 : 0;
+        st.walkin_bound[w] = bound;
+    }
+}
+
+__global__ __launch_bounds__(64) void k_walkin(DevState st, int64_t chunk, int64_t budget, int ntag) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    walkin_walker(st, blockIdx.x, chunk, budget, ntag, smem);
 }
 
 // GLOB: the walker's ln g and H rows stay in device memory (read and written
@@ -1781,11 +1880,11 @@ __device__ __forceinline__ int wave_broadcast(int v) { return __builtin_amdgcn_r
 
 __global__ __launch_bounds__(64) void k_walkin_batch(const DevState *__restrict__ descs,
                                                      const BatchTask *__restrict__ tasks, int64_t chunk,
-                                                     int64_t budget) {
+                                                     int64_t budget, size_t lds_bytes) {
     extern __shared__ __align__(16) unsigned char smem[];
     const BatchTask t = tasks[blockIdx.x];
     const DevState st = descs[t.inst];
-    walkin_walker(st, t.idx, chunk, budget, smem);
+    walkin_walker(st, t.idx, chunk, budget, walkin_tags(st, lds_bytes), smem);
 }
 
 // One thread per instance: 0 every walker placed, 1 some still walking,
@@ -2126,7 +2225,10 @@ size_t sweep_lds_bytes(const DevState &st) {
     return (size_t)st.Npad + (st.rows_glob ? (size_t)0 : (size_t)st.Wpad * 12) + (size_t)st.Ntag * 8;
 }
 
-size_t walkin_lds_bytes(const DevState &st) { return (size_t)st.Npad + (size_t)st.Bpad * 4; }
+size_t walkin_lds_bytes(const DevState &st) {
+    const size_t state = (size_t)st.Npad + (size_t)st.Bpad * 4;
+    return state + (size_t)walkin_tags(st, kLdsBytes) * 8;
+}
 
 static hipError_t allow_lds(const void *fn, size_t bytes) {
     if (bytes <= 65536) return hipSuccess;
@@ -2146,7 +2248,7 @@ hipError_t launch_walkin(const DevState &st, int64_t chunk, int64_t budget, hipS
     const size_t lds = walkin_lds_bytes(st);
     hipError_t e = allow_lds((const void *)k_walkin, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_walkin, dim3(st.nw), dim3(64), lds, s, st, chunk, budget);
+    hipLaunchKernelGGL(k_walkin, dim3(st.nw), dim3(64), lds, s, st, chunk, budget, walkin_tags(st, lds));
     return hipGetLastError();
 }
 
@@ -2275,7 +2377,8 @@ hipError_t launch_walkin_batch(const DevState *descs, const BatchTask *tasks, in
     if (ntasks <= 0) return hipSuccess;
     hipError_t e = allow_lds((const void *)k_walkin_batch, lds_bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_walkin_batch, dim3(ntasks), dim3(64), lds_bytes, s, descs, tasks, chunk, budget);
+    hipLaunchKernelGGL(k_walkin_batch, dim3(ntasks), dim3(64), lds_bytes, s, descs, tasks, chunk, budget,
+                       lds_bytes);
     return hipGetLastError();
 }
 

@@ -263,6 +263,7 @@ int check_params(int model, int L, int q, int h, double o, int m, const rewl_opt
     const int per_cu = (p->nw + kCUs - 1) / kCUs;
     auto fits = [&](int t) { return (int)((size_t)kMaxLds / (lds_state + (size_t)t * 8)); };
     while (p->Ntag > 256 && fits(p->Ntag) < per_cu && fits(p->Ntag / 2) > fits(p->Ntag)) p->Ntag /= 2;
+    // (the walk-in's 64-entry tag table fits beside every lattice that passes: L <= 134)
     if ((size_t)p->Npad + (size_t)p->Bpad * 4 > (size_t)kMaxLds)
         return fail(REWL_EINVAL, "walk-in ln g over all energies exceeds the 160 KiB LDS (L too large)");
     return REWL_OK;
