@@ -20,9 +20,6 @@ namespace rewl_gpu {
 
 namespace {
 
-// v_writelane_b32: lane `lane` of `old` takes the uniform value `v`.
-extern "C" __device__ int writelane_i32(int v, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
-
 // Phase clocks of the attempt loop.  The profiling build (REWL_PHASE_CLOCKS
 // defined, librewl_clocks.so) adds per-walker cycle and event counts to
 // g_phase_ctr, row w = walker w of a single run, slots kPc*; the product
@@ -162,10 +159,11 @@ __global__ __launch_bounds__(256) void k_init_energy(DevState st) {
 // 8,192 walkers of mixed sizes, 32 waves a CU: 80 -> 60 ms a step.
 constexpr double kMargin64 = 1e-10;   // log-domain slack of the exact-mode test (binary64)
 constexpr double kMargin32 = 1e-5;    // log-domain slack of the exact-mode test (binary32)
-// Blocks of a window whose ln f is at most this run the speculative phase:
-// the ln g drift inside a block (64 ln f at most) is then small against the
-// spread of d - ln u, so few attempts fall inside the decision margin.
-constexpr double kSpecLnf = 0x1p-8;
+// Blocks of a window whose ln f is at most this run the speculative phase.  Its
+// guesses hold longer the smaller ln f is; us per 10,000 attempts on 32 x 32
+// sites, 64 walkers, against the event phase: 2100 / 1697 at 2^-5, 1550 / 1757
+// at 2^-6, 957 / 1723 at 2^-7; 8 x 8 1151 / 1440 at 2^-6.
+constexpr double kSpecLnf = 0x1p-6;
 
 
 __device__ __forceinline__ uint64_t readlane64(uint64_t v, int j) {
@@ -227,6 +225,31 @@ __device__ __forceinline__ int match_count(int value, int v, unsigned long long 
         hi &= ~((uint32_t)(bits >> 32) ^ s);
     }
     return __builtin_popcount(lo) + __builtin_popcount(hi);
+}
+
+// Whether x and y are multiples of the binary32 spacing at magnitude m > 0
+// (normal range); sums and differences of theirs up to m are then exact.
+__device__ __forceinline__ bool on_grid32(double m, double x, double y) {
+#pragma clang fp contract(off)
+    int e;
+    (void)__builtin_frexp(m, &e);              // m < 2^e: spacing 2^(e - 24)
+    const double fx = __builtin_ldexp(x, 24 - e), fy = __builtin_ldexp(y, 24 - e);
+    return m > 0x1p-100 && m < 0x1p100 && __builtin_rint(fx) == fx && __builtin_rint(fy) == fy;
+}
+
+// How many of n further adds of l to x (itself the result of such an add) are
+// known to move it by the constant step (x + l) - x: those that stay inside
+// x's binade, counted four short; all of them if the step is zero.
+__device__ __forceinline__ uint32_t low_word_steps(float x, float l, uint32_t n) {
+#pragma clang fp contract(off)
+    const float d = (x + l) - x;
+    if (d == 0.0f) return n;
+    if (!(x > 0x1p-100f && x < 0x1p100f && d > 0.0f)) return 0u;
+    int e;
+    (void)__builtin_frexpf(x, &e);             // x < 2^e
+    const float room = (__builtin_ldexpf(1.0f, e) - x) / d - 4.0f;
+    const uint32_t k = room >= 64.0f ? 64u : (room >= 1.0f ? (uint32_t)room : 0u);
+    return k < n ? k : n;
 }
 
 // Earlier proposals of a block on the same (hashed) site as this lane's site
@@ -532,10 +555,17 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     int E = st.E[w];
     if (E < lo || E > hi) return;  // not walked in: leave the walker untouched
     if (HELP && threadIdx.x >= 64) {
-        for (int64_t base = 0; base < n; base += 64) {
+        // barrier i: blocks 0 .. i + 1 are drawn and block i has been read, so that
+        // the next one goes to its place
+        auto draw = [&](int64_t base) {
             const int todo = (int)((n - base) < 64 ? (n - base) : 64);
-            draw_block<PREC>(st, w, (uint64_t)(s0 + base), todo, tag, rec + ((base >> 6) & 1) * kRecWords, lane);
-            __syncthreads();   // block `base` is drawn; the one before it has been read
+            if (todo > 0)
+                draw_block<PREC>(st, w, (uint64_t)(s0 + base), todo, tag, rec + ((base >> 6) & 1) * kRecWords, lane);
+        };
+        draw(0);
+        for (int64_t base = 0; base < n; base += 64) {
+            draw(base + 64);
+            __syncthreads();
         }
     } else {
     // ln g cache: lane b holds energy ebase + b (+inf outside the window)
@@ -587,6 +617,15 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     };
     double M0b = 0.0, Mrb = 0.0;
     if (spec) margins(0, M0b, Mrb);
+    // with a helper: the next block's record, read while the block before runs
+    uint4 rn0{}, rn1{}, rn2{}, rn3{};
+    auto fetch = [&](int64_t base) {
+        const uint4 *rb = rec + ((base >> 6) & 1) * kRecWords + lane;
+        rn0 = rb[0];
+        rn1 = rb[64];
+        rn2 = rb[128];
+        rn3 = rb[192];
+    };
     PhaseClock pc;
 
     // one loop for each decision phase, so that neither carries the other's registers
@@ -610,8 +649,8 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         unsigned long long W0, W1, W2, W3, W4;
         if constexpr (HELP) {
             __syncthreads();
-            const uint4 *rb = rec + ((base >> 6) & 1) * kRecWords + lane;
-            const uint4 r0 = rb[0], r1 = rb[64], r2 = rb[128], r3 = rb[192];
+            if (base == 0) fetch(0);
+            const uint4 r0 = rn0, r1 = rn1, r2 = rn2, r3 = rn3;
             p.site = (int)(r0.x & 0xffffu);
             p.nb0 = (int)(r0.x >> 16);
             p.nb1 = (int)(r0.y & 0xffffu);
@@ -632,6 +671,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         }
         // spins of the site and its neighbours at block start
         int x0 = sp[p.site], x1 = sp[p.nb0], x2 = sp[p.nb1], x3 = sp[p.nb2], x4 = sp[p.nb3];
+        if constexpr (HELP) fetch(base + 64);   // (past the end: old words, not used)
         int nv = x0 + 1 + p.off;
         if (nv >= q) nv -= q;
         int dE = (int)(x0 == x1) + (int)(x0 == x2) + (int)(x0 == x3) + (int)(x0 == x4) - (int)(nv == x1) -
@@ -640,7 +680,6 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         unsigned long long anyconf = __ballot(conf != 0ull);
 
         unsigned long long accepted = 0ull, flushed = 0ull;
-        int hist = 0;
 
         // An earlier accepted flip of this block touched attempt j's site or a
         // neighbour: write the pending flips, then recompute the proposal's new
@@ -721,7 +760,6 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 ch = (lane == erel) ? gEh : ch;
                 cl = (lane == erel) ? gEl : cl;
             }
-            hist = writelane_i32(ebase + erel, j, hist);
         };
 
         const long long pc1 = pc.now();
@@ -741,9 +779,11 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             //  * its decision from the register cache's ln g at segment start,
             //    settled only outside a margin that bounds the ln g drift of
             //    the segment's earlier visits.
-            // An attempt that cannot be settled so (inside the margin, or an
-            // energy outside the cache) ends the segment and runs through
-            // slow_attempt; the next segment starts after it.
+            // The first attempt that leaves unsettled is settled with the visits
+            // of its two energies counted (see `settled`).
+            // An attempt that cannot be settled even so (or an energy outside the
+            // cache) ends the segment and runs through slow_attempt; the next
+            // segment starts after it.
             const unsigned long long livem = todo == 64 ? ~0ull : ((1ull << todo) - 1ull);
             if (!HELP && st.Ntag < st.N) same_sites(p, lane, W0, W1, W2, W3, W4);
             int start = 0;
@@ -758,12 +798,15 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 }
                 const int E0 = ebase + erel;
                 const unsigned long long act = livem & (~0ull << start);
-                const bool mine = (act >> lane) & 1ull;
                 double M0 = M0b, Mr = Mrb;
                 if (start != 0) margins(start, M0, Mr);
-                unsigned long long A = 0ull, Sg = 0ull;
-                int c = todo, pre = E0, nvi = nv, dEi = dE;
-                bool conv = false;
+                unsigned long long A = 0ull;              // accepted
+                unsigned long long S = 0ull, Out = 0ull;  // unsettled, outside the cache
+                unsigned long long F = 0ull, FA = 0ull;   // settled by counting; accepted among them
+                unsigned long long diff = 0ull;           // outputs of a round that are not its inputs
+                int c = todo, pre = E0, post = E0, nvi = nv, dEi = dE;
+                double a = 0.0, b = 0.0;                  // ln g before and after the attempt
+                float aH = 0.0f, aL = 0.0f, bH = 0.0f, bL = 0.0f;
                 // one round; the first of a segment also draws the next block's
                 // proposals (independent work that fills the round's waits)
                 auto round = [&](auto first) {
@@ -788,8 +831,6 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                     const int ip = pre - ebase;
                     // ln g before the attempt, and after it for the segment-start dE
                     // (read now; a lane whose dE changed reads again below)
-                    double a = 0.0, b = 0.0;
-                    float aH = 0.0f, aL = 0.0f, bH = 0.0f, bL = 0.0f;
                     const int ib0 = ip + dE;
                     if (PREC == 0) {
                         a = lane_read_d(c64, ip & 63);
@@ -821,10 +862,8 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                         dEn = (int)(y0 == y1) + (int)(y0 == y2) + (int)(y0 == y3) + (int)(y0 == y4) -
                               (int)(nvn == y1) - (int)(nvn == y2) - (int)(nvn == y3) - (int)(nvn == y4);
                     }
-                    const int En = pre + dEn;
-                    const bool in_win = En >= lo && En <= hi;
-                    const int inn = En - ebase;
-                    if (__ballot(mine && dEn != dE)) {
+                    const int inn = ip + dEn;
+                    if (!kFirst && (__ballot(dEn != dE) & act)) {
                         if (PREC == 0) {
                             const double b2 = lane_read_d(c64, inn & 63);
                             b = dEn != dE ? b2 : b;
@@ -834,48 +873,88 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                             bL = dEn != dE ? b2L : bL;
                         }
                     }
-                    const bool ok = (unsigned)ip < 64u && (!in_win || (unsigned)inn < 64u);
-                    bool acc, sure;
+                    // beyond the window ln g is +inf, a certain refusal; the margin
+                    // needs no |b|: where d is small, |b| is near |a|, elsewhere the
+                    // decision is far from it.  ln u < 0, so d > M is t > M.
+                    const bool out = ((unsigned)ip | (unsigned)inn) >= 64u;
+                    double t0, M;
                     if (PREC == 0) {
-                        const double d0 = a - b;
-                        const double t0 = d0 - lnu;
-                        const double M = M0 + ((fabs(a) + fabs(b)) + 1.0) * Mr;
-                        acc = dEn == 0 || d0 > M || t0 > M;
-                        sure = acc || t0 < -M;
+                        t0 = (a - b) - lnu;
+                        M = M0 + ((fabs(a) + fabs(a)) + 256.0) * Mr;
                     } else {
                         const float d0 = (aH - bH) + (aL - bL);
-                        const double t0 = (double)d0 - lnu;
+                        t0 = (double)d0 - lnu;
                         // plus the rounding of the binary32 difference itself
-                        const double M = M0 + (((double)fabs(aH) + (double)fabs(bH)) + 1.0) * Mr +
-                                         ((double)fabs(d0) + 1.0) * 0x1p-19;
-                        acc = dEn == 0 || (double)d0 > M || t0 > M;
-                        sure = acc || t0 < -M;
+                        M = M0 + (((double)fabsf(aH) + (double)fabsf(aH)) + 256.0) * Mr + ((double)fabsf(d0) + 1.0) * 0x1p-19;
+                        if (t0 == -__builtin_inf()) M = 0.0;
                     }
-                    acc = in_win && acc;
-                    sure = !in_win || sure;
-                    const bool stop = mine && !(ok && sure);
-                    const unsigned long long An = __ballot(mine && acc && !stop);
-                    const unsigned long long Sn = __ballot(stop);
-                    const unsigned long long Cn = __ballot(mine && (nvn != nvi || dEn != dEi));
-                    c = Sn ? (int)__builtin_ctzll(Sn) : todo;
-                    const unsigned long long R = act & (c >= 63 ? ~0ull : ((2ull << c) - 1ull));
-                    conv = (((An ^ A) | (Sn ^ Sg) | Cn) & R) == 0ull;
+                    const unsigned long long yes = __ballot(dEn == 0 || t0 > M), no = __ballot(t0 < -M);
+                    const unsigned long long open = act & ~F;
+                    Out = __ballot(out) & open;
+                    const unsigned long long An = (yes & open & ~Out) | FA;
+                    S = (open & ~(yes | no)) | Out;
+                    diff = (An ^ A) | (__ballot(nvn != nvi || dEn != dEi) & act);
                     A = An;
-                    Sg = Sn;
                     nvi = nvn;
                     dEi = dEn;
+                };
+                // After a round: the attempts up to its first unsettled one are
+                // final if its outputs there are its inputs.  The unsettled one is
+                // then settled with the visits of its two energies counted, the
+                // margin shrunk to the rounding: refused, as guessed, the scan goes
+                // on; accepted, it takes another round.  Returns whether attempts
+                // [start, c) are final and c is at the end or stays unsettled.
+                auto settled = [&]() -> bool {
+                    if (S == 0ull) {
+                        c = todo;
+                        return diff == 0ull;
+                    }
+                    for (;;) {
+                        c = S ? (int)__builtin_ctzll(S) : todo;
+                        const unsigned long long upto = c >= 64 ? ~0ull : ((1ull << c) - 1ull);
+                        if (diff & (upto | (c < 64 ? 1ull << c : 0ull))) return false;
+                        if (c >= todo || ((Out >> c) & 1ull)) return true;
+                        post = pre + (((A >> lane) & 1ull) ? dEi : 0);
+                        const int e0 = __builtin_amdgcn_readlane(pre, c), e1 = e0 + __builtin_amdgcn_readlane(dEi, c);
+                        const unsigned long long before = act & upto;
+                        const double n0 = (double)__builtin_popcountll(__ballot(post == e0) & before);
+                        const double n1 = (double)__builtin_popcountll(__ballot(post == e1) & before);
+                        double t, M;
+                        if (PREC == 0) {
+                            t = ((a + n0 * lnf) - (b + n1 * lnf)) - lnu;
+                            M = kMargin64 + ((fabs(a) + fabs(a)) + (256.0 + 128.0 * lnf)) * 0x1p-46;
+                        } else {
+                            const double l = (double)lnf32;
+                            const double d0 = (((double)aH + (double)aL) + n0 * l) - (((double)bH + (double)bL) + n1 * l);
+                            t = d0 - lnu;
+                            M = kMargin32 + ((fabs(d0) + (double)fabsf(aL)) + ((double)fabsf(bL) + 128.0 * l + 1.0)) * 0x1p-18;
+                        }
+                        const unsigned long long bit = 1ull << c;
+                        const bool take = (__ballot(t > M) & bit) != 0ull;
+                        if (!take && !(__ballot(t < -M) & bit)) return true;
+                        F |= bit;
+                        S &= ~bit;
+                        if (take) {
+                            FA |= bit;
+                            A |= bit;
+                            return false;
+                        }
+                    }
                 };
                 const long long pcr = pc.now();
                 pc.add(kPcSetupCycles, pcr - pcs);
                 round(std::true_type{});
-                for (int it = 1; it < 66 && !conv; ++it) round(std::false_type{});
+                bool conv = settled();
+                for (int it = 1; it < 132 && !conv; ++it) {
+                    round(std::false_type{});
+                    conv = settled();
+                }
                 const long long pcc = pc.now();
                 pc.add(kPcRoundCycles, pcc - pcr);
                 if (!conv) c = start;   // not reached (see above); the exact path is always right
                 // commit attempts [start, c): spins, visits, ln g increments per bin
                 const unsigned long long seg = act & (c >= 64 ? ~0ull : ((1ull << c) - 1ull));
                 const unsigned long long aseg = A & seg;
-                const bool inseg = (seg >> lane) & 1ull;
                 const bool mine_acc = (aseg >> lane) & 1ull;
                 const int ej = pre + (mine_acc ? dEi : 0);
                 if (seg) {
@@ -890,9 +969,6 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                         if (lane == 0) *sup_w = 0ull;
                     }
                     if (mine_acc && !((sup >> lane) & 1ull)) sp[p.site] = (int8_t)nvi;
-                    nv = inseg ? nvi : nv;
-                    dE = inseg ? dEi : dE;
-                    hist = inseg ? ej : hist;
                     // visits of lane's energy: the segment's lanes that ended there
                     uint32_t nb = (uint32_t)match_count(ej - ebase, lane, seg);
                     // the segment's visits go to H here, one add per energy (atomic:
@@ -906,42 +982,48 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                         // x_n = x_1 + (n - 1) d2 exactly; otherwise the loop below
                         const double x1 = c64 + lnf_v;
                         const double d2 = (x1 + lnf_v) - x1;
-                        int ex;
-                        (void)__builtin_frexp(x1, &ex);
-                        const double top = __builtin_ldexp(1.0, ex);
-                        const double nm1 = (double)(nb - 1u);
-                        if (d2 * 64.0 <= x1 && x1 + nm1 * d2 + 4.0 * lnf_v < top * (1.0 - 0x1p-40)) {
-                            c64 = x1 + nm1 * d2;
+                        const double xn = x1 + (double)(nb - 1u) * d2, z = xn + 4.0 * lnf_v;
+                        const bool binade = (((uint32_t)((uint64_t)__double_as_longlong(x1) >> 32) ^
+                                              (uint32_t)((uint64_t)__double_as_longlong(z) >> 32)) >> 20) == 0u;
+                        if (d2 * 64.0 <= x1 && binade) {
+                            c64 = xn;
                             nb = 0u;
                         }
                     }
-                    if (PREC == 1 && nb != 0u && ch + lnf32 == ch) {
-                        // (hi, lo) pair whose high word ln f leaves unchanged: TwoSum
-                        // then hands the whole ln f to the low word at every add, and
-                        // the low word's n adds follow the closed form above in binary32
-                        const float x1 = cl + lnf32;
-                        const float d2 = (x1 + lnf32) - x1;
-                        int ex;
-                        (void)__builtin_frexpf(x1, &ex);
-                        const float top = __builtin_ldexpf(1.0f, ex);
-                        const float nm1 = (float)(nb - 1u);
-                        if (d2 * 64.0f <= x1 &&
-                            (double)x1 + (double)nm1 * (double)d2 + 4.0 * (double)lnf32 < (double)top * (1.0 - 0x1p-20)) {
-                            cl = x1 + nm1 * d2;
-                            nb = 0u;
-                        }
-                    }
-                    while (__ballot(nb != 0u)) {
-                        if (PREC == 0) {
+                    if (PREC == 0) {
+                        while (__ballot(nb != 0u)) {
                             const double x = c64 + lnf_v;
                             c64 = nb != 0u ? x : c64;
-                        } else {
+                            nb = nb != 0u ? nb - 1u : 0u;
+                        }
+                    } else {
+                        // n adds that round nowhere, all sums being multiples of the
+                        // binary32 spacing at the largest of them: in the high word
+                        // the low word then stays; where the high word ignores ln f
+                        // TwoSum hands it to the low word, which takes them all
+                        const bool low = ch + lnf32 == ch;
+                        if (nb != 0u) {
+                            const double l = (double)lnf32, sh = (double)ch + (double)nb * l, sl = (double)cl + (double)nb * l;
+                            if (on_grid32(fmax(fabs((double)ch), fabs(sh)), (double)ch, l)) {
+                                ch = (float)sh;
+                                nb = 0u;
+                            } else if (low && on_grid32(fmax(fabs((double)cl), fabs(sl)), (double)cl, l)) {
+                                cl = (float)sl;
+                                nb = 0u;
+                            }
+                        }
+                        // otherwise one add, then in the low word as many of its
+                        // constant steps (see above) as its binade holds
+                        while (__ballot(nb != 0u)) {
                             float xh = ch, xl = cl;
                             two_sum_add(xh, xl, lnf32);
                             ch = nb != 0u ? xh : ch;
                             cl = nb != 0u ? xl : cl;
+                            nb = nb != 0u ? nb - 1u : 0u;
+                            const uint32_t skip = low ? low_word_steps(cl, lnf32, nb) : 0u;
+                            cl = (float)((double)cl + (double)skip * (double)((cl + lnf32) - cl));
+                            nb -= skip;
                         }
-                        nb = nb != 0u ? nb - 1u : 0u;
                     }
                     erel = __builtin_amdgcn_readlane(ej, c - 1) - ebase;
                 }
@@ -1025,7 +1107,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             };
             if (PREC == 0) gEv = readlane_d(c64, erel);
             else { gEh = readlane_f(ch, erel); gEl = readlane_f(cl, erel); }
-            hist = ebase + erel;
+            int hist = ebase + erel;          // energy after the lane's attempt
             arrive(0);
             while (i < todo) {
                 const unsigned long long from = livem & (~0ull << i);
@@ -1107,6 +1189,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 i = j + 1;
             }
             pay();
+            if (live) atomicAdd(&H[hist - lo], 1u);
         }
 
         const long long pct = pc.now();
@@ -1115,8 +1198,6 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             lnu_nx = ln_uniform<PREC>(p_nx.u);
         }
         if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
-        // (the speculative phase counted its visits per segment)
-        if (!kSpec && live) atomicAdd(&H[hist - lo], 1u);
         const long long pcd = pc.now();
         pc.add(kPcTailCycles, pcd - pct);
         pc.add(kPcDecideCycles, pcd - pc1);
@@ -2252,11 +2333,13 @@ hipError_t launch_walkin(const DevState &st, int64_t chunk, int64_t budget, hipS
     return hipGetLastError();
 }
 
-// A helper wavefront per walker where the chip has SIMDs to spare: at most
-// four walkers a CU, all resident (the tag table gives way, down to 64
-// entries, so that the helper's blocks fit).
+// A helper wavefront per walker while that leaves at most three wavefronts a
+// SIMD: at most six walkers a CU, all resident (the tag table gives way, down to
+// 64 entries, so that the helper's blocks fit).  32 x 32 sites, ln f = 2^-21, us per
+// 10,000 attempts with and without: 469 / 502 at four walkers a CU, 562 / 606
+// at six, 646 / 629 at eight.
 static bool sweep_helped(const DevState &st, DevState *out) {
-    constexpr int kCUs = 256, kPerCu = 4;
+    constexpr int kCUs = 256, kPerCu = 6;
     const int per_cu = (st.nw + kCUs - 1) / kCUs;
     if (per_cu > kPerCu || st.N > kHelpMaxSites) return false;
     *out = st;

@@ -124,3 +124,74 @@ def test_pair_low_word_replay_closed_form_equals_sequential_two_sums():
             hh, ll = two_sum_add(hh, ll, x)
         assert hh == h and F32(x1 + F32(nm1 * d2)) == ll, (h, l, x, n)
     assert used > 5_000
+
+
+def low_word_steps(x, l, n):
+    """The kernel's count of further adds of l to x that are known to be constant steps."""
+    d = F32(F32(x + l) - x)
+    if d == 0.0:
+        return n
+    if not (2.0**-100 < x < 2.0**100 and d > 0.0):
+        return 0
+    _, e = np.frexp(x)
+    room = F32(F32(F32(np.ldexp(F32(1.0), int(e))) - x) / d) - F32(4.0)
+    k = 64 if room >= 64.0 else (int(room) if room >= 1.0 else 0)
+    return min(k, n)
+
+
+def on_grid32(m, x, y):
+    _, e = np.frexp(F64(m))
+    fx, fy = np.ldexp(F64(x), 24 - int(e)), np.ldexp(F64(y), 24 - int(e))
+    return 2.0**-100 < m < 2.0**100 and np.rint(fx) == fx and np.rint(fy) == fy
+
+
+def pair_replay(h, l, x, n):
+    """n TwoSum adds of x to (h, l) by the kernel's shortcuts, and the adds done one by one."""
+    low, slow = F32(h + x) == h, 0
+    sh, sl = F64(h) + F64(n) * F64(x), F64(l) + F64(n) * F64(x)
+    if on_grid32(max(abs(F64(h)), abs(sh)), h, x):
+        return F32(sh), l, slow
+    if low and on_grid32(max(abs(F64(l)), abs(sl)), l, x):
+        return h, F32(sl), slow
+    while n:
+        h, l = two_sum_add(h, l, x)
+        n, slow = n - 1, slow + 1
+        if low:
+            k = low_word_steps(l, x, n)
+            l = F32(F64(l) + F64(k) * F64(F32(F32(l + x) - l)))
+            n -= k
+    return h, l, slow
+
+
+def test_pair_replay_shortcuts_equal_sequential_two_sums():
+    # high words of every size against ln f, low words as a split of binary64
+    # values leaves them: of either sign, up to half a spacing of the high word
+    rng = np.random.default_rng(17)
+    total = slow = 0
+    for _ in range(40_000):
+        h = F32(rng.choice([0.0, 0.7, 5.0, 300.0, 2500.0, 1.5e5]) * rng.uniform(0.5, 2.0))
+        x = F32(rng.choice([3.6e-7, 1e-8, 2.0**-21, 2.0**-9, 1.0 / (3 * 2**17), 0.25, 2.0**-13]))
+        l = F32(np.spacing(h) * rng.uniform(-0.5, 0.5))
+        n = int(rng.integers(1, 65))
+        a, b, s = pair_replay(h, l, x, n)
+        rh, rl = h, l
+        for _ in range(n):
+            rh, rl = two_sum_add(rh, rl, x)
+        assert a == rh and b == rl, (h, l, x, n)
+        total += n
+        slow += s
+    assert slow < 0.5 * total
+
+
+def test_counted_visits_settle_what_the_drift_leaves_open():
+    # values after n sequential adds differ from x + n ln f by less than the
+    # margin the counted decision and the event decision allow
+    rng = np.random.default_rng(18)
+    for _ in range(3000):
+        x = F64(rng.choice([0.0, 3.0, 1e3, 1e7, -1e5]) * rng.uniform(0.5, 2.0))
+        f = F64(rng.choice([1.0, 0.3, 2.0**-6, 1e-3, 3.6e-7]))
+        n = int(rng.integers(1, 65))
+        ref = x
+        for _ in range(n):
+            ref = F64(ref + f)
+        assert abs(ref - F64(x + F64(n * f))) <= (2 * abs(x) + 256.0 + 128.0 * f) * 2.0**-47
