@@ -746,7 +746,7 @@ namespace {
 
 // Device scratch of a bootstrap: offsets of its buffers (256-byte aligned).
 struct BootLayout {
-    size_t draws, pieces, vis, beta, shift, cuts, status, joined, T, th, out, total;
+    size_t draws, pieces, vis, beta, runs, shift, cuts, status, joined, T, th, out, total;
 };
 
 BootLayout boot_layout(const DevState &d, int R, int nboot, int nT) {
@@ -762,6 +762,8 @@ BootLayout boot_layout(const DevState &d, int R, int nboot, int nT) {
     l.pieces = take(sizeof(double) * (size_t)nboot * hw);
     l.vis = take(hw);
     l.beta = take(sizeof(double) * (size_t)nboot * hw);
+    // the runs' pieces are read before beta is written: they share its place
+    l.runs = R <= nboot ? l.beta : take(sizeof(double) * (size_t)R * hw);
     l.shift = take(sizeof(double) * (size_t)nboot * d.h);
     l.cuts = take(sizeof(int32_t) * (size_t)nboot * d.h);
     l.status = take(sizeof(int32_t) * (size_t)nboot);
@@ -819,6 +821,7 @@ int rewl_batch_bootstrap(rewl_batch_t *b, int nboot, uint64_t seed, const double
     a.e0 = (double)d.e_lo; a.de = 1.0;
     a.start = d.start;
     a.draws = (int32_t *)(w + l.draws);
+    a.runs = (double *)(w + l.runs);
     a.pieces = (double *)(w + l.pieces);
     a.vis = (uint8_t *)(w + l.vis);
     a.beta = (double *)(w + l.beta);
@@ -827,6 +830,9 @@ int rewl_batch_bootstrap(rewl_batch_t *b, int nboot, uint64_t seed, const double
     a.status = (int32_t *)(w + l.status);
     a.joined = (double *)(w + l.joined);
     a.T = (const double *)(w + l.T);
+    a.plain_T = 1;
+    for (int i = 0; i < nT; ++i)
+        if (!(T[i] > 1e-100 && T[i] < 1e100)) a.plain_T = 0;
     a.th = (double *)(w + l.th);
     a.out = (double *)(w + l.out);
     if (nT > 0) HIP_TRY(hipMemcpyAsync((void *)a.T, T, sizeof(double) * nT, hipMemcpyHostToDevice, b->stream));

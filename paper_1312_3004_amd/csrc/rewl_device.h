@@ -414,6 +414,8 @@ struct BootArgs {
     double log_total, e0, de;
     const int32_t *start;
     int32_t *draws;     // [nboot][R]
+    int plain_T;        // every temperature within 1e-100 .. 1e100
+    double *runs;       // [R][h][Wpad] (may share beta's place: read before it is written)
     double *pieces;     // [nboot][h][Wpad]
     uint8_t *vis;       // [h][Wpad]
     double *beta;       // [nboot][h][Wpad]

@@ -2113,6 +2113,7 @@ struct BootView {
     int R, h, W, Wpad, B, Bpad, e_lo, m, nboot;
     const int32_t *start;   // [h]
     int32_t *draws;         // [nboot][R]
+    double *runs;           // [R][h][Wpad] the runs' own pieces
     double *pieces;         // [nboot][h][Wpad]
     uint8_t *vis;           // [h][Wpad] union of the runs' flags
     double *beta;           // [nboot][h][Wpad]
@@ -2135,6 +2136,7 @@ struct BootView {
 __global__ __launch_bounds__(256) void k_boot_draws(BootView bv, uint32_t key0, uint32_t key1) {
     const int nblk = (bv.R + 3) / 4;
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    for (long long b = t; b < (long long)bv.h * bv.Wpad; b += (long long)gridDim.x * blockDim.x) bv.vis[b] = 0;
     if (t >= (long long)bv.nboot * nblk) return;
     const int j = (int)(t / nblk), c = (int)(t % nblk);
     const U4 w = philox10((uint32_t)j, (uint32_t)c, 0u, kDomBoot << 24, key0, key1);
@@ -2145,26 +2147,37 @@ __global__ __launch_bounds__(256) void k_boot_draws(BootView bv, uint32_t key0, 
     }
 }
 
-__global__ __launch_bounds__(256) void k_boot_visited(BootView bv, const DevState *__restrict__ descs) {
-    const int k = blockIdx.y;
+// The runs' pieces side by side, run r at runs[r][h][Wpad], and the union of
+// their visited flags: the resamples then index one array instead of following
+// R descriptors.  64 runs of 8 x 8, 1,000 resamples, with k_boot_pieces: 61 -> 22 us.
+__global__ __launch_bounds__(256) void k_boot_gather(BootView bv, const DevState *__restrict__ descs) {
+    const int r = blockIdx.z, k = blockIdx.y;
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= bv.W) return;
-    uint8_t v = 0;
-    for (int r = 0; r < bv.R; ++r) v |= descs[r].visited[(size_t)k * bv.Wpad + b] ? 1 : 0;
-    bv.vis[(size_t)k * bv.Wpad + b] = v;
+    const DevState &st = descs[r];
+    const size_t kb = (size_t)k * bv.Wpad + b;
+    bv.runs[(size_t)r * bv.h * bv.Wpad + kb] = lng_at(st, k * bv.m, b, st.precision);
+    if (st.visited[kb]) bv.vis[kb] = 1;   // (cleared by k_boot_draws; every writer writes the same)
 }
 
-__global__ __launch_bounds__(256) void k_boot_pieces(BootView bv, const DevState *__restrict__ descs) {
+__global__ __launch_bounds__(256) void k_boot_pieces(BootView bv) {
 #pragma clang fp contract(off)
     const int k = blockIdx.y, j = blockIdx.z;
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= bv.W) return;
     const int32_t *dr = bv.draws + (size_t)j * bv.R;
+    const size_t hw = (size_t)bv.h * bv.Wpad;
+    const double *__restrict__ at = bv.runs + (size_t)k * bv.Wpad + b;
     double sum = 0.0;
-    for (int i = 0; i < bv.R; ++i) {
-        const DevState &st = descs[dr[i]];
-        sum = sum + lng_at(st, k * bv.m, b, st.precision);
+    int i = 0;
+    for (; i + 8 <= bv.R; i += 8) {        // eight loads in flight, added in draw order
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = at[(size_t)dr[i + u] * hw];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum = sum + v[u];
     }
+    for (; i < bv.R; ++i) sum = sum + at[(size_t)dr[i] * hw];
     bv.pieces[((size_t)j * bv.h + k) * bv.Wpad + b] = sum / (double)bv.R;
 }
 
@@ -2193,8 +2206,67 @@ __global__ __launch_bounds__(256) void k_boot_normalise(BootView bv, double log_
     join_normalise(bv.joined + (size_t)blockIdx.x * bv.Bpad, bv.B, log_total);
 }
 
-// Canonical averages of replicate j at temperature T[t], one wavefront: the
-// same four passes as thermo_one, reduced across lanes with shuffles.
+// Canonical averages of replicate j, a temperature per lane: four wavefronts
+// of a workgroup take every fourth bin for the same 64 temperatures, so that a
+// bin's ln g is one scalar for all lanes and nothing is reduced across them.
+// Two passes: the largest exponent and its energy e*, then one exponential a
+// bin for sum p, sum p (e - e*) and sum p (e - e*)^2.  e / T is the division's
+// own rounding from the reciprocal and one residual (Markstein).  1,000
+// replicates x 201 temperatures x 129 bins: 288 -> 68 us against a wavefront per
+// temperature with lane sums and three exponentials a bin.
+__global__ __launch_bounds__(256) void k_boot_thermo_lanes(BootView bv, const double *T, int nT, double e0, double de,
+                                                           double *out) {
+    __shared__ double s_m[4][64], s_e[4][64], s_z[4][64], s_1[4][64], s_2[4][64];
+    const int lane = threadIdx.x & 63;
+    const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int t = blockIdx.x * 64 + lane, j = blockIdx.y;
+    const double *__restrict__ joined = bv.joined + (size_t)j * bv.Bpad;
+    const double temp = T[t < nT ? t : nT - 1], inv = 1.0 / temp;
+    auto exponent = [&](int b, double e) {
+        const double q = e * inv;
+        return joined[b] - __builtin_fma(__builtin_fma(-q, temp, e), inv, q);
+    };
+    double m = -__builtin_inf(), em = e0;
+    for (int b = part; b < bv.B; b += 4) {
+        if (joined[b] == -__builtin_inf()) continue;
+        const double e = e0 + (double)b * de, a = exponent(b, e);
+        em = a > m ? e : em;
+        m = a > m ? a : m;
+    }
+    s_m[part][lane] = m;
+    s_e[part][lane] = em;
+    __syncthreads();
+    for (int k = 0; k < 4; ++k) {
+        em = s_m[k][lane] > m ? s_e[k][lane] : em;
+        m = s_m[k][lane] > m ? s_m[k][lane] : m;
+    }
+    // equal maxima in different parts: every part takes the first one's energy
+    for (int k = 3; k >= 0; --k) em = s_m[k][lane] == m ? s_e[k][lane] : em;
+    double z = 0.0, s1 = 0.0, s2 = 0.0;
+    for (int b = part; b < bv.B; b += 4) {
+        if (joined[b] == -__builtin_inf()) continue;
+        const double e = e0 + (double)b * de, p = exp(exponent(b, e) - m), d = e - em;
+        z += p;
+        s1 = __builtin_fma(p, d, s1);
+        s2 = __builtin_fma(p * d, d, s2);
+    }
+    s_z[part][lane] = z;
+    s_1[part][lane] = s1;
+    s_2[part][lane] = s2;
+    __syncthreads();
+    if (part != 0 || t >= nT) return;
+    z = (s_z[0][lane] + s_z[1][lane]) + (s_z[2][lane] + s_z[3][lane]);
+    s1 = (s_1[0][lane] + s_1[1][lane]) + (s_1[2][lane] + s_1[3][lane]);
+    s2 = (s_2[0][lane] + s_2[1][lane]) + (s_2[2][lane] + s_2[3][lane]);
+    const double c = z == 0.0 ? 0.0 : s1 / z, var = z == 0.0 ? 0.0 : __builtin_fma(-c, c, s2 / z);
+    double *o = out + ((size_t)j * nT + t) * 3;
+    o[0] = m + log(z);
+    o[1] = z == 0.0 ? 0.0 : em + c;
+    o[2] = var / (temp * temp);
+}
+
+// The same for few temperatures: replicate j at temperature T[t], one
+// wavefront: the four passes of thermo_one, reduced across lanes with shuffles.
 __device__ __forceinline__ double wave_sum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
@@ -2432,18 +2504,23 @@ hipError_t launch_bootstrap(const BootArgs &a, const DevState *descs, hipStream_
     BootView bv;
     bv.R = a.R; bv.h = a.h; bv.W = a.W; bv.Wpad = a.Wpad; bv.B = a.B; bv.Bpad = a.Bpad; bv.e_lo = a.e_lo;
     bv.m = a.m; bv.nboot = a.nboot;
-    bv.start = a.start; bv.draws = a.draws; bv.pieces = a.pieces; bv.vis = a.vis; bv.beta = a.beta;
+    bv.start = a.start; bv.draws = a.draws; bv.runs = a.runs; bv.pieces = a.pieces; bv.vis = a.vis; bv.beta = a.beta;
     bv.shift = a.shift; bv.cuts = a.cuts; bv.status = a.status; bv.joined = a.joined;
     const long long ndraw = (long long)a.nboot * ((a.R + 3) / 4);
     const unsigned wb = (unsigned)((a.W + 255) / 256);
     hipLaunchKernelGGL(k_boot_draws, dim3((unsigned)((ndraw + 255) / 256)), dim3(256), 0, s, bv, a.key0, a.key1);
-    hipLaunchKernelGGL(k_boot_visited, dim3(wb, a.h), dim3(256), 0, s, bv, descs);
-    hipLaunchKernelGGL(k_boot_pieces, dim3(wb, a.h, a.nboot), dim3(256), 0, s, bv, descs);
+    hipLaunchKernelGGL(k_boot_gather, dim3(wb, a.h, a.R), dim3(256), 0, s, bv, descs);
+    hipLaunchKernelGGL(k_boot_pieces, dim3(wb, a.h, a.nboot), dim3(256), 0, s, bv);
     hipLaunchKernelGGL(k_boot_beta, dim3(wb, a.h, a.nboot), dim3(256), 0, s, bv);
     hipLaunchKernelGGL(k_boot_cuts, dim3(a.nboot), dim3(256), 0, s, bv);
     hipLaunchKernelGGL(k_boot_assemble, dim3((unsigned)((a.B + 255) / 256), a.nboot), dim3(256), 0, s, bv);
     hipLaunchKernelGGL(k_boot_normalise, dim3(a.nboot), dim3(256), 0, s, bv, a.log_total);
-    if (a.nT > 0)
+    // a temperature per lane needs half a wavefront of them and enough
+    // workgroups for the chip; the residual division wants T within 10^+-100
+    const unsigned tb = (unsigned)((a.nT + 63) / 64);
+    if (a.nT >= 32 && (long long)tb * a.nboot >= 256 && a.plain_T)
+        hipLaunchKernelGGL(k_boot_thermo_lanes, dim3(tb, a.nboot), dim3(256), 0, s, bv, a.T, a.nT, a.e0, a.de, a.th);
+    else if (a.nT > 0)
         hipLaunchKernelGGL(k_boot_thermo, dim3(a.nT, a.nboot), dim3(64), 0, s, bv, a.T, a.nT, a.e0, a.de, a.th);
     hipLaunchKernelGGL(k_boot_stats, dim3((unsigned)(a.B + 2 * a.nT)), dim3(256), 0, s, bv, (const double *)a.th,
                        a.nT, a.out);

@@ -85,3 +85,26 @@ def test_bootstrap_argument_errors():
         c.bootstrap(10, 1, [1.0])                 # instances of different systems
     out = b.bootstrap(50, 2)
     assert np.isfinite(out["lng_mean"]).any()
+
+
+@pytest.mark.parametrize("R,nboot,nT", [(9, 300, 32), (6, 130, 65), (9, 5, 40), (5, 300, 31)])
+def test_bootstrap_temperature_grids_match_oracle(R, nboot, nT):
+    # a temperature per lane (32 temperatures and 256 workgroups up, a ragged
+    # second wavefront of them) and a wavefront per temperature, more and fewer
+    # runs than resamples
+    L, q, h, m = 5, 3, 2, 1
+    insts, spins = runs_of(L, q, h, m, R, 1e-2, 1000)
+    b = _pk().Batch(insts, spins)
+    assert b.run(10**6) == _pk().CONVERGED
+    os_ = oracle_runs(insts, spins)
+    T = np.geomspace(0.05, 40.0, nT)
+    g = b.bootstrap(nboot, 5, T)
+    pv = [oracle.run_pieces(o) for o in os_]
+    o = os_[0]
+    st, ref = oracle.bootstrap(np.stack([p for p, _ in pv]), np.stack([v for _, v in pv]), o.starts, o.e_lo, o.B,
+                               L * L * math.log(q), nboot, 5, T)
+    assert st == 0
+    # the bounds of the test above; the absolute ones cover temperatures where
+    # C_v is below the rounding of U^2 / T^2 (|U| <= 50, T >= 0.05)
+    for k in ("U_mean", "U_std", "C_mean", "C_std"):
+        np.testing.assert_allclose(g[k], ref[k], rtol=1e-9, atol=1e-9)
