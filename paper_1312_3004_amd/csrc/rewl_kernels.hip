@@ -1256,9 +1256,10 @@ __device__ __forceinline__ void sync_window(const DevState &st, int k, int64_t a
     const size_t base = (size_t)k * m * Wpad;
     uint8_t *vis = st.visited + (size_t)k * Wpad;
     for (int b = tid; b < W; b += 256) {
-        uint8_t v = vis[b];
-        for (int j = 0; j < m; ++j) v |= (st.H[base + (size_t)j * Wpad + b] != 0u) ? 1 : 0;
-        vis[b] = v;
+        uint32_t any = 0u;
+#pragma unroll 8
+        for (int j = 0; j < m; ++j) any |= st.H[base + (size_t)j * Wpad + b];
+        if (any) vis[b] = 1;
     }
     if (PREC == 1) {
         for (int idx = tid; idx < m * W; idx += 256) {
@@ -1289,50 +1290,45 @@ __device__ __forceinline__ void sync_window(const DevState &st, int k, int64_t a
     if (st.fixed_lnf) return;
     __syncthreads();
 
-    __shared__ unsigned long long s_sum[256];
-    __shared__ unsigned int s_n[256], s_min[256];
     __shared__ int s_avg;
     const int regime = st.regime[k];
+    if (tid == 0) s_avg = 1;
+    __syncthreads();
     if (regime == 0) {
-        int all_flat = 1;
-        for (int j = 0; j < m; ++j) {
+        // a wavefront per walker: sum, minimum and number of its visited bins
+        const int lane = tid & 63;
+        for (int j = tid >> 6; j < m; j += 4) {
             unsigned long long sum = 0;
             unsigned int cnt = 0, mn = 0xFFFFFFFFu;
-            for (int b = tid; b < W; b += 256) {
+            for (int b = lane; b < W; b += 64) {
                 if (!vis[b]) continue;
                 const unsigned int hv = st.H[base + (size_t)j * Wpad + b];
                 cnt += 1;
                 sum += hv;
                 mn = hv < mn ? hv : mn;
             }
-            s_sum[tid] = sum; s_n[tid] = cnt; s_min[tid] = mn;
-            __syncthreads();
-            for (int o = 128; o > 0; o >>= 1) {
-                if (tid < o) {
-                    s_sum[tid] += s_sum[tid + o];
-                    s_n[tid] += s_n[tid + o];
-                    s_min[tid] = s_min[tid + o] < s_min[tid] ? s_min[tid + o] : s_min[tid];
-                }
-                __syncthreads();
+            for (int o = 32; o > 0; o >>= 1) {
+                sum += __shfl_xor(sum, o, 64);
+                cnt += __shfl_xor(cnt, o, 64);
+                const unsigned int other = __shfl_xor(mn, o, 64);
+                mn = other < mn ? other : mn;
             }
-            const unsigned long long n_act = s_n[0], tot = s_sum[0], hmin = s_min[0];
+            const unsigned long long n_act = cnt, tot = sum, hmin = mn;
             const bool flat = n_act > 0 &&
                               (unsigned long long)st.flat_den * hmin * n_act >=
                                   (unsigned long long)st.flat_num * tot;
-            all_flat = all_flat && flat;
-            __syncthreads();
+            if (!flat && lane == 0) s_avg = 0;
         }
-        if (tid == 0) s_avg = all_flat;
-    } else {
-        if (tid == 0) s_avg = 1;
     }
     __syncthreads();
     if (!s_avg) return;
     for (int b = tid; b < W; b += 256) {
         double sum;
         if (PREC == 0) {
-            sum = st.lng[base + b];
-            for (int j = 1; j < m; ++j) sum = sum + st.lng[base + (size_t)j * Wpad + b];
+            const double *gw = st.lng + base + b;
+            sum = gw[0];
+#pragma unroll 8
+            for (int j = 1; j < m; ++j) sum = sum + gw[(size_t)j * Wpad];
         } else {
             sum = (double)st.lng_hi[base + b] + (double)st.lng_lo[base + b];
             for (int j = 1; j < m; ++j) {
@@ -1409,67 +1405,91 @@ __device__ __forceinline__ double lng_at(const DevState &st, int w, int b, int p
     return (double)st.lng_hi[i] + (double)st.lng_lo[i];
 }
 
+//
+// The words are drawn four a thread, the decisions taken one pair a thread
+// (every walker is in one pair), and the accepted swaps shared by the
+// wavefronts: 64 windows x 16 walkers of 80 x 80, 46 -> 13 us against one lane
+// doing all but the swaps.
 __device__ __forceinline__ void exchange_pair(const DevState &st, uint32_t r, int pair) {
 #pragma clang fp contract(off)
     if (*st.converged) return;
     const int k = (int)(r & 1u) + 2 * pair;
     if (k + 1 >= st.h) return;
     const int m = st.m;
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
+    __shared__ uint32_t s_word[2048];   // 2m - 1 words, m <= 1024
     __shared__ int s_perm[1024];
     __shared__ int s_acc[1024];
-    if (threadIdx.x == 0) {
-        uint32_t buf[4];
-        int pos = 4;
-        uint32_t n = 0;
-        auto next = [&]() -> uint32_t {
-            if (pos == 4) {
-                const U4 v = philox10(r, (uint32_t)k, n, st.ctr3 | (kDomExch << 24), st.key0, st.key1);
-                buf[0] = v.x; buf[1] = v.y; buf[2] = v.z; buf[3] = v.w;
-                ++n;
-                pos = 0;
+    __shared__ int s_nacc;
+    for (int n = tid; 4 * n < 2 * m - 1; n += nthr) {
+        const U4 v = philox10(r, (uint32_t)k, (uint32_t)n, st.ctr3 | (kDomExch << 24), st.key0, st.key1);
+        s_word[4 * n] = v.x; s_word[4 * n + 1] = v.y; s_word[4 * n + 2] = v.z; s_word[4 * n + 3] = v.w;
+    }
+    if (m > 64)
+        for (int j = tid; j < m; j += nthr) s_perm[j] = j;
+    if (tid == 0) s_nacc = 0;
+    __syncthreads();
+    if (m <= 64) {
+        if (tid < 64) {   // the permutation in one register, lane j holding entry j
+            const uint32_t word = s_word[lane < m ? lane : 0];
+            int perm = lane;
+            for (int i = m - 1; i >= 1; --i) {
+                const int j = (int)mul_shift(__builtin_amdgcn_readlane(word, m - 1 - i), (uint32_t)(i + 1));
+                const int pi = __builtin_amdgcn_readlane(perm, i), pj = __builtin_amdgcn_readlane(perm, j);
+                perm = lane == i ? pj : (lane == j ? pi : perm);
             }
-            return buf[pos++];
-        };
-        for (int j = 0; j < m; ++j) s_perm[j] = j;
+            if (lane < m) s_perm[lane] = perm;
+        }
+    } else if (tid == 0) {
         for (int i = m - 1; i >= 1; --i) {
-            const int j = (int)mul_shift(next(), (uint32_t)(i + 1));
+            const int j = (int)mul_shift(s_word[m - 1 - i], (uint32_t)(i + 1));
             const int t = s_perm[i]; s_perm[i] = s_perm[j]; s_perm[j] = t;
         }
-        const int lo_a = st.start[k], hi_a = lo_a + st.W - 1;
-        const int lo_b = st.start[k + 1], hi_b = lo_b + st.W - 1;
-        unsigned long long nacc = 0;
-        for (int j = 0; j < m; ++j) {
-            const int a = k * m + j, b = (k + 1) * m + s_perm[j];
-            const uint32_t u = next();
-            const int ex = st.E[a], ey = st.E[b];
-            int acc = 0;
-            if (ey >= lo_a && ey <= hi_a && ex >= lo_b && ex <= hi_b) {
-                const double d = ((lng_at(st, a, ex - lo_a, st.precision) -
-                                   lng_at(st, a, ey - lo_a, st.precision)) +
-                                  lng_at(st, b, ey - lo_b, st.precision)) -
-                                 lng_at(st, b, ex - lo_b, st.precision);
-                acc = accept64(d, u) ? 1 : 0;
-            }
-            s_acc[j] = acc;
-            nacc += (unsigned long long)acc;
-        }
-        st.x_att[k] += (unsigned long long)m;
-        st.x_acc[k] += nacc;
     }
     __syncthreads();
-    // Rows are 256-byte aligned and padded: swap them in 16-byte words, four
-    // per lane in flight before any is stored.
+    const int lo_a = st.start[k], hi_a = lo_a + st.W - 1;
+    const int lo_b = st.start[k + 1], hi_b = lo_b + st.W - 1;
+    int mine = 0;
+    for (int j = tid; j < m; j += nthr) {
+        const int a = k * m + j, b = (k + 1) * m + s_perm[j];
+        const uint32_t u = s_word[m - 1 + j];
+        const int ex = st.E[a], ey = st.E[b];
+        int acc = 0;
+        if (ey >= lo_a && ey <= hi_a && ex >= lo_b && ex <= hi_b) {
+            const double d = ((lng_at(st, a, ex - lo_a, st.precision) -
+                               lng_at(st, a, ey - lo_a, st.precision)) +
+                              lng_at(st, b, ey - lo_b, st.precision)) -
+                             lng_at(st, b, ex - lo_b, st.precision);
+            acc = accept64(d, u) ? 1 : 0;
+        }
+        s_acc[j] = acc;
+        mine += acc;
+        if (acc) {
+            st.E[a] = ey;
+            st.E[b] = ex;
+            if (st.Efx) { const int64_t te = st.Efx[a]; st.Efx[a] = st.Efx[b]; st.Efx[b] = te; }
+            const uint32_t rr = st.replica[a]; st.replica[a] = st.replica[b]; st.replica[b] = rr;
+        }
+    }
+    if (mine) atomicAdd(&s_nacc, mine);
+    __syncthreads();
+    if (tid == 0) {
+        st.x_att[k] += (unsigned long long)m;
+        st.x_acc[k] += (unsigned long long)s_nacc;
+    }
+    // Rows are 256-byte aligned and padded: a wavefront swaps a pair of them in
+    // 16-byte words, four per lane in flight before any is stored.
     const int n16 = st.Npad / 16;
-    for (int j = 0; j < m; ++j) {
+    for (int j = tid >> 6; j < m; j += nthr >> 6) {
         if (!s_acc[j]) continue;
         const int a = k * m + j, b = (k + 1) * m + s_perm[j];
         uint4 *__restrict__ pa = (uint4 *)(st.spins + (size_t)a * st.Npad);
         uint4 *__restrict__ pb = (uint4 *)(st.spins + (size_t)b * st.Npad);
-        for (int i0 = 0; i0 < n16; i0 += 4 * (int)blockDim.x) {
+        for (int i0 = 0; i0 < n16; i0 += 4 * 64) {
             uint4 ta[4], tb[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int i = i0 + u * (int)blockDim.x + (int)threadIdx.x;
+                const int i = i0 + u * 64 + lane;
                 if (i < n16) {
                     ta[u] = pa[i];
                     tb[u] = pb[i];
@@ -1477,22 +1497,17 @@ __device__ __forceinline__ void exchange_pair(const DevState &st, uint32_t r, in
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int i = i0 + u * (int)blockDim.x + (int)threadIdx.x;
+                const int i = i0 + u * 64 + lane;
                 if (i < n16) {
                     pa[i] = tb[u];
                     pb[i] = ta[u];
                 }
             }
         }
-        if (threadIdx.x == 0) {
-            const int t = st.E[a]; st.E[a] = st.E[b]; st.E[b] = t;
-            if (st.Efx) { const int64_t te = st.Efx[a]; st.Efx[a] = st.Efx[b]; st.Efx[b] = te; }
-            const uint32_t rr = st.replica[a]; st.replica[a] = st.replica[b]; st.replica[b] = rr;
-        }
     }
 }
 
-__global__ __launch_bounds__(64) void k_exchange(DevState st, uint32_t r) {
+__global__ __launch_bounds__(1024) void k_exchange(DevState st, uint32_t r) {
     exchange_pair(st, r, blockIdx.x);
 }
 
@@ -1656,22 +1671,23 @@ __global__ __launch_bounds__(256) void k_obs_thermo(DevState st, const double *T
 }
 
 // Termination (Sec. 2): the run ends once every window reached ln f_final
-// (never in the production phase).
-__device__ __forceinline__ void check_instance(const DevState &st, int64_t step, int64_t round_after) {
-    if (*st.converged || *st.production) return;
-    for (int k = 0; k < st.h; ++k)
-        if (!st.finished[k]) return;
+// (never in the production phase).  `all`: whether every window is finished.
+__device__ __forceinline__ void check_instance(const DevState &st, bool all, int64_t step, int64_t round_after) {
+    if (*st.converged || *st.production || !all) return;
     *st.converged = 1;
     st.stop[0] = step;
     st.stop[1] = round_after;
 }
 
-__global__ void k_check(DevState st, int64_t step, int64_t round_after) {
+__global__ __launch_bounds__(256) void k_check(DevState st, int64_t step, int64_t round_after) {
     if (!*st.converged) track_replicas(st, (int)threadIdx.x, (int)blockDim.x);
-    if (threadIdx.x == 0) check_instance(st, step, round_after);
+    bool all = true;
+    for (int k = threadIdx.x; k < st.h; k += blockDim.x) all = all && st.finished[k] != 0;
+    const int fin = __syncthreads_and(all ? 1 : 0);
+    if (threadIdx.x == 0) check_instance(st, fin != 0, step, round_after);
 }
 
-__global__ void k_track(DevState st) {
+__global__ __launch_bounds__(256) void k_track(DevState st) {
     if (!*st.converged) track_replicas(st, (int)threadIdx.x, (int)blockDim.x);
 }
 
@@ -2068,7 +2084,7 @@ __global__ __launch_bounds__(256) void k_measure_batch(const DevState *__restric
 }
 
 // Exchange round of instance t.inst (at its own round counter), pair slot t.idx.
-__global__ __launch_bounds__(64) void k_exchange_batch(const DevState *__restrict__ descs,
+__global__ __launch_bounds__(256) void k_exchange_batch(const DevState *__restrict__ descs,
                                                        const BatchTask *__restrict__ xtasks, int lo) {
     const BatchTask t = xtasks[lo + (int)blockIdx.x];
     const DevState st = descs[t.inst];
@@ -2087,7 +2103,9 @@ __global__ void k_advance_batch(const DevState *__restrict__ descs, int lo, int 
     const int64_t round = st.ctl[1] + (st.exchange ? 1 : 0);
     st.ctl[0] = step;
     st.ctl[1] = round;
-    check_instance(st, step, round);
+    bool all = true;
+    for (int k = 0; k < st.h && all; ++k) all = st.finished[k] != 0;
+    check_instance(st, all, step, round);
 }
 
 __global__ void k_status_batch(const DevState *__restrict__ descs, int n, BatchStatus *out) {
@@ -2451,17 +2469,18 @@ hipError_t launch_sync(const DevState &st, int64_t attempts, hipStream_t s) {
 hipError_t launch_exchange(const DevState &st, uint32_t round, hipStream_t s) {
     const int pairs = (st.h - (int)(round & 1u)) / 2;
     if (pairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_exchange, dim3(pairs), dim3(64), 0, s, st, round);
+    // a wavefront per walker pair, at most 16
+    hipLaunchKernelGGL(k_exchange, dim3(pairs), dim3(64 * std::min(st.m, 16)), 0, s, st, round);
     return hipGetLastError();
 }
 
 hipError_t launch_check(const DevState &st, int64_t step, int64_t round_after, hipStream_t s) {
-    hipLaunchKernelGGL(k_check, dim3(1), dim3(64), 0, s, st, step, round_after);
+    hipLaunchKernelGGL(k_check, dim3(1), dim3(256), 0, s, st, step, round_after);
     return hipGetLastError();
 }
 
 hipError_t launch_track(const DevState &st, hipStream_t s) {
-    hipLaunchKernelGGL(k_track, dim3(1), dim3(64), 0, s, st);
+    hipLaunchKernelGGL(k_track, dim3(1), dim3(256), 0, s, st);
     return hipGetLastError();
 }
 
@@ -2626,7 +2645,7 @@ hipError_t launch_measure_batch(const DevState *descs, const BatchTask *tasks, i
 hipError_t launch_exchange_batch(const DevState *descs, const BatchTask *xtasks, int lo, int n,
                                  hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_exchange_batch, dim3(n), dim3(64), 0, s, descs, xtasks, lo);
+    hipLaunchKernelGGL(k_exchange_batch, dim3(n), dim3(256), 0, s, descs, xtasks, lo);
     return hipGetLastError();
 }
 
