@@ -65,4 +65,5 @@ struct rewl {
     int64_t step = 0, round = 0;
     bool walked_in = false, converged = false, joined = false;
     bool in_batch = false;   // owned by a rewl_batch (rewl_destroy refuses it)
+    unsigned char *pin = nullptr;   // pinned copy of [converged .. stop], from the first run on
 };

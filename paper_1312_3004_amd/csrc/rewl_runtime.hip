@@ -674,6 +674,7 @@ int rewl_get_energy_fx(rewl_t *r, int w, int64_t *E) {
 void rewl_destroy(rewl_t *r) {
     if (!r || r->in_batch) return;
     timer_destroy(r->timer);
+    if (r->pin) (void)hipHostFree(r->pin);
     delete r;
 }
 
@@ -725,12 +726,18 @@ int rewl_walkin(rewl_t *r, int64_t max_attempts) {
     return REWL_OK;
 }
 
+// Waits for the run's work and reads the convergence flag and the stop point,
+// which lie one behind the other in the workspace: one copy into pinned memory
+// instead of two into pageable memory.
 static int read_converged(rewl_t *r) {
+    const size_t off = r->lay.stop - r->lay.converged, bytes = off + 2 * sizeof(int64_t);
+    if (!r->pin) HIP_TRY(hipHostMalloc((void **)&r->pin, bytes, hipHostMallocDefault));
+    HIP_TRY(hipMemcpyAsync(r->pin, r->st.converged, bytes, hipMemcpyDeviceToHost, r->stream));
+    HIP_TRY(hipStreamSynchronize(r->stream));
     int32_t conv = 0;
     int64_t stop[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(&conv, r->st.converged, sizeof(int32_t), hipMemcpyDeviceToHost, r->stream));
-    HIP_TRY(hipMemcpyAsync(stop, r->st.stop, sizeof(stop), hipMemcpyDeviceToHost, r->stream));
-    HIP_TRY(hipStreamSynchronize(r->stream));
+    std::memcpy(&conv, r->pin, sizeof(conv));
+    std::memcpy(stop, r->pin + off, sizeof(stop));
     if (conv) {
         r->converged = true;
         r->step = stop[0];
