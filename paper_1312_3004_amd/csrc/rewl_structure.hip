@@ -7,20 +7,25 @@
 // LDS; the contact graph is held as one bit row per lipid, built 64 partners
 // at a time with a ballot, each pair tested once (the rows are shared among
 // the four wavefronts, the blocks left of the diagonal filled by transposing
-// bits).  Then wavefront 0 alone takes S_mol, grows the clusters level by
-// level (visited set, frontier and each level's finds as register bit
-// masks), unfolds the largest one level by level in binary64 and reduces it.
-// Sums across lanes use butterfly shuffles, so the floating-point outputs
+// bits).  Then wavefront 1 takes S_mol, and wavefront 0 finds the clusters
+// (free set, frontier and finds as bit masks, the contact rows in registers up
+// to 256 lipids), takes the largest one again with its tree, unfolds it level
+// by level and reduces it.
+// 125 lipids, 4,096 configurations: 299 -> 121 us; 64 configurations, one a CU,
+// 108 -> 43 us, bound by the chain of levels on wavefront 0.
+// Sums across lanes are taken in butterfly order, so the floating-point outputs
 // agree with a plain evaluation to rounding, while every integer output
 // (cluster count and sizes, the tree that unfolds a cluster) is decided as in
 // the definition (binary32 minimum images, binary64 squared distances, a
-// binary32 screen settling only the pairs it provably can) and is exact.
+// screen on 16-bit places, or in binary32 for places outside [0, box),
+// settling only the pairs it provably can) and is exact.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <mutex>
 
 #include "rewl_host.h"
+#include "rewl_moves.h"
 
 namespace rewl_gpu {
 
@@ -53,8 +58,33 @@ __device__ __forceinline__ void st_diff(const float *a, const float *b, float bo
 
 __device__ __forceinline__ double st_r2(const double d[3]) { return (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]; }
 
+// Sum over the 64 lanes (all active), in the order of a butterfly over lane
+// distances 32, 16, 8, 4, 2, 1; every lane returns it.  Without LDS: the
+// halves and the rows of 16 swapped (v_permlane32_swap, v_permlane16_swap),
+// rows rotated by 8, then by 4 (equal to distance 4 where lanes 8 apart agree),
+// quads permuted.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+    return __longlong_as_double(dpp64<CTRL, 0xF>(__double_as_longlong(v)));
+}
+template <int ROWS>
+__device__ __forceinline__ double swap_sum(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+    const auto l = ROWS == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                              : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = ROWS == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                              : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0])) +
+           __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
+}
 __device__ __forceinline__ double wave_sum(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    v = swap_sum<32>(v);
+    v = swap_sum<16>(v);
+    v += dpp_d<0x128>(v);   // row_ror:8
+    v += dpp_d<0x124>(v);   // row_ror:4
+    v += dpp_d<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+    v += dpp_d<0xB1>(v);    // quad_perm [1, 0, 3, 2]
     return v;
 }
 
@@ -100,44 +130,37 @@ __device__ __forceinline__ bool tails_touch_fast(const float *xi, const float *x
     return hit != 0;
 }
 
-// Place the beads of a lipid other than `b` through its bonds, starting from
-// bead b (0 head, 1 centre, 2 end) already at u[3 b].
-__device__ __forceinline__ void st_chain(const float *x, double *u, int b, float box, float half) {
-    double d[3];
-    if (b == 1) {
-        st_diff(x + 3, x, box, half, d);
-        for (int a = 0; a < 3; ++a) u[a] = u[3 + a] + d[a];
-        st_diff(x + 3, x + 6, box, half, d);
-        for (int a = 0; a < 3; ++a) u[6 + a] = u[3 + a] + d[a];
-    } else if (b == 2) {
-        st_diff(x + 6, x + 3, box, half, d);
-        for (int a = 0; a < 3; ++a) u[3 + a] = u[6 + a] + d[a];
-        st_diff(x + 3, x, box, half, d);
-        for (int a = 0; a < 3; ++a) u[a] = u[3 + a] + d[a];
-    } else {
-        st_diff(x, x + 3, box, half, d);
-        for (int a = 0; a < 3; ++a) u[3 + a] = u[a] + d[a];
-        st_diff(x + 3, x + 6, box, half, d);
-        for (int a = 0; a < 3; ++a) u[6 + a] = u[3 + a] + d[a];
-    }
+// The same decision from places rounded down to box / 65536 (16 bits an axis,
+// rewl_moves.h): differences wrap by themselves and the squared distance takes
+// 4 operations where the binary32 minimum image takes 26.  The rounding moves
+// a distance by less than 1.8 units, so below 1.4 by 2 units is a contact and
+// above it by 2 is none; the squares of the two limits are lim.x and lim.y.
+// t: (xy, z) of the centre and end bead.
+__device__ __forceinline__ bool tails_touch_grid(uint4 ti, uint4 tj, uint2 lim, bool *unsure) {
+    const MoveGrid a0{ti.x, ti.y}, a1{ti.z, ti.w}, b0{tj.x, tj.y}, b1{tj.z, tj.w};
+    const uint32_t d0 = move_grid2(a0, b0), d1 = move_grid2(a0, b1), d2 = move_grid2(a1, b0), d3 = move_grid2(a1, b1);
+    const uint32_t e0 = d0 < d1 ? d0 : d1, e1 = d2 < d3 ? d2 : d3, d = e0 < e1 ? e0 : e1;
+    *unsure = d >= lim.x && d <= lim.y;
+    return d < lim.x;
 }
 
 // LDS layout for M lipids (W = ceil(M / 64) mask words):
+//   gt  uint4 [M]         tail beads on the 16-bit grid
 //   xs  float [M][9]      bead coordinates (head, centre, end)
 //   adj u64   [M][W]      contact rows
 //   u   double[M][9]      unfolded beads of the largest cluster
-//   root, level, parent int32[M]
+// NW >= W mask words are unrolled; up to four, a lane keeps the contact rows of
+// its lipids (64 w + lane) in registers, else it reads them from LDS.
+template <int NW>
 __global__ __launch_bounds__(256) void k_lipid_structure(const unsigned char *xbase, size_t xstride,
                                                        const unsigned char *lbase, size_t lstride, int np, int M,
                                                        float box, double *out) {
     extern __shared__ __align__(16) unsigned char st_lds[];
     const int W = (M + 63) >> 6;
-    uint64_t *adj = (uint64_t *)st_lds;
+    uint4 *gt = (uint4 *)st_lds;
+    uint64_t *adj = (uint64_t *)(gt + M);
     double *u = (double *)(adj + (size_t)M * W);
     float *xs = (float *)(u + (size_t)M * 9);
-    int *root = (int *)(xs + (size_t)M * 9);
-    int *level = root + M;
-    int *parent = level + M;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -149,7 +172,8 @@ __global__ __launch_bounds__(256) void k_lipid_structure(const unsigned char *xb
     double *rec = out + (size_t)c * 8;
 
     // Beads to LDS; an index outside [0, np) turns the record into NaN.
-    bool bad = false;
+    bool bad = false, outside = false;
+    const float scale = 65536.0f / box;
     for (int l = tid; l < M; l += 64 * kStructWaves) {
         for (int b = 0; b < 3; ++b) {
             const int p = lp[3 * l + b];
@@ -158,8 +182,13 @@ __global__ __launch_bounds__(256) void k_lipid_structure(const unsigned char *xb
             const int q = ok ? p : 0;
             for (int a = 0; a < 3; ++a) xs[9 * l + 3 * b + a] = x[3 * (size_t)q + a];
         }
-        root[l] = -1;
+        const float *tail = xs + 9 * l + 3;
+        for (int a = 0; a < 6; ++a) outside = outside || !(tail[a] >= 0.0f && tail[a] < box);
+        const MoveGrid g0 = move_grid(tail, scale), g1 = move_grid(tail + 3, scale);
+        gt[l] = make_uint4(g0.xy, g0.z, g1.xy, g1.z);
     }
+    // the grid knows places in [0, box) only
+    const bool on_grid = __syncthreads_or(outside) == 0;
     if (__syncthreads_or(bad)) {
         if (tid < 8) rec[tid] = __builtin_nan("");
         return;
@@ -170,15 +199,27 @@ __global__ __launch_bounds__(256) void k_lipid_structure(const unsigned char *xb
     // is symmetric in i and j).  Each lane keeps its own lipid's beads in
     // registers (NaN past the end, which never touches) and reads lipid i's,
     // the same address for all lanes.
+    const float r = 1.4f * scale;
+    const float in = fminf(fmaxf(r - 2.0f, 0.0f), 65535.0f), out_ = fminf(r + 2.0f, 65535.0f);
+    const uint2 lim = make_uint2((uint32_t)(in * in), (uint32_t)(out_ * out_) + 1u);
     for (int w = 0; w < W; ++w) {
         const int j = 64 * w + lane;
         float tj[9];
         for (int a = 0; a < 9; ++a) tj[a] = j < M ? xs[9 * j + a] : __builtin_nanf("");
+        const uint4 gj = gt[j < M ? j : 0];
+        const uint64_t real = M - 64 * w >= 64 ? ~0ull : (1ull << (M - 64 * w)) - 1ull;
         for (int i = wave; i < M && (i >> 6) <= w; i += kStructWaves) {
             bool unsure;
-            bool hit = tails_touch_fast(xs + 9 * i, tj, box, half, &unsure);
-            if (__any(unsure)) hit = tails_touch(xs + 9 * i, tj, box, half);
-            const uint64_t m = __ballot(hit & (j != i));
+            uint64_t m;
+            if (on_grid) {
+                const bool hit = tails_touch_grid(gt[i], gj, lim, &unsure);
+                m = __ballot(hit) & real;
+                if (__ballot(unsure) & real) m = __ballot(tails_touch(xs + 9 * i, tj, box, half));
+            } else {
+                const bool hit = tails_touch_fast(xs + 9 * i, tj, box, half, &unsure);
+                m = __any(unsure) ? __ballot(tails_touch(xs + 9 * i, tj, box, half)) : __ballot(hit);
+            }
+            if ((i >> 6) == w) m &= ~(1ull << (i & 63));
             if (lane == 0) adj[(size_t)i * W + w] = m;
         }
     }
@@ -194,148 +235,243 @@ __global__ __launch_bounds__(256) void k_lipid_structure(const unsigned char *xb
         }
     }
     __syncthreads();
-    // The rest runs on wavefront 0 alone: the others leave after the last
-    // workgroup barrier, and wavefront 0 orders its LDS traffic with
-    // wave-level fences from here on.
-    if (wave != 0) return;
-
-    // Eq. 6: <cos^2> of the head-to-centre bonds along each axis.
-    double cx = 0.0, cy = 0.0, cz = 0.0;
-    for (int l = lane; l < M; l += 64) {
-        double d[3];
-        st_diff(xs + 9 * l, xs + 9 * l + 3, box, half, d);
-        const double r2 = st_r2(d);
-        cx += d[0] * d[0] / r2;
-        cy += d[1] * d[1] / r2;
-        cz += d[2] * d[2] / r2;
+    // Wavefront 1 takes Eq. 6 while wavefront 0 takes the clusters; all meet
+    // once more at the end.
+    __shared__ double s_cos[3];
+    if (wave > 1) {
+        __syncthreads();
+        return;
     }
-    cx = wave_sum(cx);
-    cy = wave_sum(cy);
-    cz = wave_sum(cz);
+    if (wave == 1) {
+        // Eq. 6: <cos^2> of the head-to-centre bonds along each axis.
+        double cx = 0.0, cy = 0.0, cz = 0.0;
+        for (int l = lane; l < M; l += 64) {
+            double d[3];
+            st_diff(xs + 9 * l, xs + 9 * l + 3, box, half, d);
+            const double r2 = st_r2(d);
+            cx += d[0] * d[0] / r2;
+            cy += d[1] * d[1] / r2;
+            cz += d[2] * d[2] / r2;
+        }
+        cx = wave_sum(cx);
+        cy = wave_sum(cy);
+        cz = wave_sum(cz);
+        if (lane == 0) {
+            s_cos[0] = cx;
+            s_cos[1] = cy;
+            s_cos[2] = cz;
+        }
+        __syncthreads();
+        return;
+    }
 
-    // Clusters, grown breadth first from their lowest free lipid.  The
-    // visited set and the frontier are bit masks held by every lane alike;
-    // the search reads only the contact rows and writes root, level and
-    // parent for the unfolding, so it needs no LDS ordering.
-    uint64_t vis[kStructWords], front[kStructWords];
+    // Clusters.  Visited set, frontier and finds are bit masks held by the whole
+    // wavefront.  Lipids without contacts are clusters of one, all at once; the
+    // others are grown breadth first from their lowest free lipid, only to know
+    // their size.
+    constexpr bool kRegs = NW <= 4;
+    uint64_t rows[kRegs ? NW : 1][kRegs ? NW : 1];
+    auto row = [&](int w, int v) -> uint64_t {
+        if constexpr (kRegs) return rows[w][v];
+        else return v < W && 64 * w + lane < M ? adj[(size_t)(64 * w + lane) * W + v] : 0ull;
+    };
+    if constexpr (kRegs) {
 #pragma unroll
-    for (int w = 0; w < kStructWords; ++w) {
-        const int left = M - 64 * w;   // lipids in word w
-        vis[w] = left >= 64 ? 0ull : (left <= 0 ? ~0ull : ~((1ull << left) - 1ull));
-        front[w] = 0ull;
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int v = 0; v < NW; ++v)
+                rows[w][v] = v < W && 64 * w + lane < M ? adj[(size_t)(64 * w + lane) * W + v] : 0ull;
     }
-    int ncl = 0, best_root = -1, best_size = 0, best_depth = 0;
+    uint64_t free_[NW], front[NW];
+    int ncl = 0, best_root = 0, best_size = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int left = M - 64 * w;   // lipids in word w
+        free_[w] = left >= 64 ? ~0ull : (left <= 0 ? 0ull : (1ull << left) - 1ull);
+        uint64_t any = 0ull;
+#pragma unroll
+        for (int v = 0; v < NW; ++v) any |= row(w, v);
+        const uint64_t alone = __ballot(any == 0ull) & free_[w];
+        if (alone && best_size == 0) {
+            best_size = 1;
+            best_root = 64 * w + (int)__builtin_ctzll(alone);
+        }
+        ncl += __builtin_popcountll(alone);
+        free_[w] &= ~alone;
+    }
+    // one level: the free lipids that touch the frontier
+    auto grow = [&](uint64_t *found) -> int {
+        int n = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            uint64_t t = 0ull;
+#pragma unroll
+            for (int v = 0; v < NW; ++v) t |= row(w, v) & front[v];
+            found[w] = __ballot(t != 0ull) & free_[w];
+            n += __builtin_popcountll(found[w]);
+        }
+        return n;
+    };
+    auto start_at = [&](int r) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            front[w] = w == (r >> 6) ? 1ull << (r & 63) : 0ull;
+            free_[w] &= ~front[w];
+        }
+    };
     for (;;) {
         int r = -1;
 #pragma unroll
-        for (int w = kStructWords - 1; w >= 0; --w)
-            if (~vis[w]) r = 64 * w + __builtin_ctzll(~vis[w]);
+        for (int w = NW - 1; w >= 0; --w)
+            if (free_[w]) r = 64 * w + (int)__builtin_ctzll(free_[w]);
         if (r < 0) break;
         ++ncl;
-        if (lane == 0) {
-            root[r] = r;
-            level[r] = 0;
-            parent[r] = -1;
-        }
-#pragma unroll
-        for (int w = 0; w < kStructWords; ++w) {
-            front[w] = w == (r >> 6) ? 1ull << (r & 63) : 0ull;
-            vis[w] |= front[w];
-        }
-        int size = 1, k = 0;
+        start_at(r);
+        int size = 1;
         for (;;) {
-            uint64_t found[kStructWords];
-            int nfound = 0;
+            uint64_t found[NW];
+            const int n = grow(found);
+            if (n == 0) break;
+            size += n;
 #pragma unroll
-            for (int w = 0; w < kStructWords; ++w) {
-                found[w] = 0ull;
-                if (w < W) {
-                    const int j = 64 * w + lane;
-                    int p = -1;
-                    if (!((vis[w] >> lane) & 1ull)) {   // free, and j < M
-#pragma unroll
-                        for (int v = 0; v < kStructWords; ++v) {
-                            if (v < W) {
-                                const uint64_t t = adj[(size_t)j * W + v] & front[v];
-                                if (p < 0 && t) p = 64 * v + __builtin_ctzll(t);
-                            }
-                        }
-                    }
-                    found[w] = __ballot(p >= 0);
-                    if (p >= 0) {
-                        root[j] = r;
-                        level[j] = k + 1;
-                        parent[j] = p;
-                    }
-                    nfound += __builtin_popcountll(found[w]);
-                }
-            }
-            if (nfound == 0) break;
-            size += nfound;
-            ++k;
-#pragma unroll
-            for (int w = 0; w < kStructWords; ++w) {
+            for (int w = 0; w < NW; ++w) {
                 front[w] = found[w];
-                vis[w] |= found[w];
+                free_[w] &= ~found[w];
             }
         }
         if (size > best_size) {
             best_size = size;
             best_root = r;
-            best_depth = k;
+        }
+    }
+
+    // The largest cluster again, with the tree that unfolds it: level and the
+    // lowest touching lipid of the level before.
+    int level[NW], parent[NW], depth = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int left = M - 64 * w;
+        free_[w] = left >= 64 ? ~0ull : (left <= 0 ? 0ull : (1ull << left) - 1ull);
+        level[w] = 64 * w + lane == best_root ? 0 : -1;
+        parent[w] = -1;
+    }
+    start_at(best_root);
+    for (;;) {
+        uint64_t found[NW];
+        if (grow(found) == 0) break;
+        ++depth;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            if ((found[w] >> lane) & 1ull) {
+                level[w] = depth;
+#pragma unroll
+                for (int v = NW - 1; v >= 0; --v) {
+                    const uint64_t t = row(w, v) & front[v];
+                    if (t) parent[w] = 64 * v + (int)__builtin_ctzll(t);
+                }
+            }
+        }
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            front[w] = found[w];
+            free_[w] &= ~found[w];
+        }
+    }
+
+    // Unfolding.  First, for all lipids at once, the bead a lipid is placed by
+    // (through its first touching tail pair; the root by its stored head), its
+    // difference from the parent's bead, and its bonds: to u, from which a lipid
+    // is then placed, level after level, by additions alone.
+    int hang[NW];   // 4 parent bead + own bead
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        hang[w] = 0;
+        const int j = 64 * w + lane;
+        if (level[w] < 0) continue;
+        const float *xj = xs + 9 * j;
+        double *uj = u + 9 * j;
+        double d[3], to_head[3], to_end[3];   // from the centre bead
+        st_diff(xj + 3, xj, box, half, to_head);
+        st_diff(xj + 3, xj + 6, box, half, to_end);
+        int bb = 0;
+        if (level[w] == 0) {
+            for (int a = 0; a < 3; ++a) d[a] = (double)xj[a];
+        } else {
+            const float *xi = xs + 9 * parent[w];
+            for (int pr = 3; pr >= 0; --pr) {   // the first that touches is written last
+                double e[3];
+                const int ba = 1 + (pr >> 1), b2 = 1 + (pr & 1);
+                st_diff(xi + 3 * ba, xj + 3 * b2, box, half, e);
+                if (st_r2(e) < kTailContact2) {
+                    bb = b2;
+                    hang[w] = 4 * ba + b2;
+                    for (int a = 0; a < 3; ++a) d[a] = e[a];
+                }
+            }
+        }
+        for (int a = 0; a < 3; ++a) {
+            // bead bb: its difference; the beads along the chain from it: the bond
+            uj[a] = bb == 0 ? d[a] : to_head[a];
+            uj[3 + a] = bb == 1 ? d[a] : (bb == 0 ? -to_head[a] : -to_end[a]);
+            uj[6 + a] = bb == 2 ? d[a] : to_end[a];
         }
     }
     wave_sync();
-
-    // Unfold the largest cluster level by level.
-    for (int k = 0; k <= best_depth; ++k) {
-        for (int j = lane; j < M; j += 64) {
-            if (root[j] != best_root || level[j] != k) continue;
-            const float *xj = xs + 9 * j;
-            double *uj = u + 9 * j;
-            if (k == 0) {
-                for (int a = 0; a < 3; ++a) uj[a] = (double)xj[a];
-                st_chain(xj, uj, 0, box, half);
-                continue;
-            }
-            const int i = parent[j];
-            const float *xi = xs + 9 * i;
-            const double *ui = u + 9 * i;
-            int b = 0;
-            for (int pr = 0; pr < 4 && b == 0; ++pr) {
-                const int ba = 1 + (pr >> 1), bb = 1 + (pr & 1);
-                double d[3];
-                st_diff(xi + 3 * ba, xj + 3 * bb, box, half, d);
-                if (st_r2(d) < kTailContact2) {
-                    for (int a = 0; a < 3; ++a) uj[3 * bb + a] = ui[3 * ba + a] + d[a];
-                    b = bb;
+    for (int k = 0; k <= depth; ++k) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            if (level[w] != k) continue;
+            double *uj = u + 9 * (64 * w + lane);
+            const int bb = hang[w] & 3;
+            const double *ui = u + 9 * (k == 0 ? 0 : parent[w]) + 3 * (hang[w] >> 2);
+            for (int a = 0; a < 3; ++a) {
+                double h = uj[a], c0 = uj[3 + a], t = uj[6 + a];
+                const double at = k == 0 ? 0.0 : ui[a];
+                if (bb == 0) {
+                    h = k == 0 ? h : at + h;
+                    c0 = h + c0;
+                    t = c0 + t;
+                } else if (bb == 1) {
+                    c0 = at + c0;
+                    h = c0 + h;
+                    t = c0 + t;
+                } else {
+                    t = at + t;
+                    c0 = t + c0;
+                    h = c0 + h;
                 }
+                uj[a] = h;
+                uj[3 + a] = c0;
+                uj[6 + a] = t;
             }
-            st_chain(xj, uj, b, box, half);
         }
         wave_sync();
     }
 
     // Eq. 7 over the 3 x best_size beads, then Eq. 8.
     double s[3] = {0.0, 0.0, 0.0};
-    for (int j = lane; j < M; j += 64) {
-        if (root[j] != best_root) continue;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (level[w] < 0) continue;
         for (int b = 0; b < 3; ++b)
-            for (int a = 0; a < 3; ++a) s[a] += u[9 * j + 3 * b + a];
+            for (int a = 0; a < 3; ++a) s[a] += u[9 * (64 * w + lane) + 3 * b + a];
     }
     const double n = 3.0 * (double)best_size;
     double com[3], q[3];
     for (int a = 0; a < 3; ++a) com[a] = wave_sum(s[a]) / n;
     for (int a = 0; a < 3; ++a) s[a] = 0.0;
-    for (int j = lane; j < M; j += 64) {
-        if (root[j] != best_root) continue;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (level[w] < 0) continue;
         for (int b = 0; b < 3; ++b)
             for (int a = 0; a < 3; ++a) {
-                const double e = u[9 * j + 3 * b + a] - com[a];
+                const double e = u[9 * (64 * w + lane) + 3 * b + a] - com[a];
                 s[a] += e * e;
             }
     }
     for (int a = 0; a < 3; ++a) q[a] = wave_sum(s[a]) / n;
+    __syncthreads();
+    const double cx = s_cos[0], cy = s_cos[1], cz = s_cos[2];
 
     if (lane == 0) {
         const double sx = 1.5 * (cx / (double)M) - 0.5;
@@ -393,20 +529,26 @@ __global__ __launch_bounds__(64) void k_measure_lipid(DevState st) {
 
 size_t lipid_structure_lds_bytes(int M) {
     const size_t W = (size_t)(M + 63) / 64;
-    return (size_t)M * W * 8 + (size_t)M * 72 + (size_t)M * 36 + (size_t)M * 12;
+    return (size_t)M * 16 + (size_t)M * W * 8 + (size_t)M * 72 + (size_t)M * 36;
 }
 
 hipError_t launch_lipid_structure(const void *coords, size_t xstride, const void *lipids, size_t lstride, int nconf,
                                   int np, int M, float box, double *out, hipStream_t s) {
     const size_t lds = lipid_structure_lds_bytes(M);
-    if (lds > 48 * 1024) {   // with margin for the kernel's own static LDS
-        const hipError_t e = hipFuncSetAttribute((const void *)k_lipid_structure,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_lipid_structure, dim3(nconf), dim3(64 * kStructWaves), lds, s,
-                       (const unsigned char *)coords, xstride, (const unsigned char *)lipids, lstride, np, M, box, out);
-    return hipGetLastError();
+    auto go = [&](auto kernel) -> hipError_t {
+        if (lds > 48 * 1024) {   // with margin for the kernel's own static LDS
+            const hipError_t e = hipFuncSetAttribute((const void *)kernel,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3(nconf), dim3(64 * kStructWaves), lds, s, (const unsigned char *)coords,
+                           xstride, (const unsigned char *)lipids, lstride, np, M, box, out);
+        return hipGetLastError();
+    };
+    if (M <= 64) return go(k_lipid_structure<1>);
+    if (M <= 128) return go(k_lipid_structure<2>);
+    if (M <= 256) return go(k_lipid_structure<4>);
+    return go(k_lipid_structure<8>);
 }
 
 hipError_t launch_lipid_measure(const DevState &st, hipStream_t s) {

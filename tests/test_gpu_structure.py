@@ -81,6 +81,24 @@ def test_random_configurations(nconf, M, nsol, box, seed):
         assert_same_record(got[c], S.structure(xs[c], lips[c], box), f"conf {c}")
 
 
+@pytest.mark.parametrize("M,box,shift,seed", [
+    (70, 7.0, 1.0, 10),       # places outside [0, box): the binary32 screen
+    (256, 9.0, 0.4, 11),      # the last size with its rows in registers
+    (257, 9.0, 0.0, 12),      # the first that reads them from LDS
+    (40, 2.5, 0.0, 13),       # contact radius beyond half the box: all touch
+    (40, 0.5, 0.0, 14),       # beyond the box: the limits' upper end
+    (40, 3.0e5, 0.0, 15),     # contact radius below the grid's step: every pair exact
+])
+def test_screen_and_row_forms(M, box, shift, seed):
+    print(f"[case] structure screen M={M} box={box} shift={shift} seed={seed}", flush=True)
+    xs, lips = random_configs(3, M, 9, min(box, 9.0), seed)
+    xs = (xs % np.float32(box)).astype(np.float32)
+    xs[1:] += np.float32(shift * box) * np.random.default_rng(seed).integers(-1, 2, xs[1:].shape).astype(np.float32)
+    got = gpu_records(xs, lips, box)
+    for c in range(3):
+        assert_same_record(got[c], S.structure(xs[c], lips[c], box), f"conf {c}")
+
+
 def test_rods_and_hand_built_clusters():
     # a ring of 10 lipids closing through the boundary, and a straight rod
     K, s = 10, 0.6
