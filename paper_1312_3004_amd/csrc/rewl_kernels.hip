@@ -154,17 +154,17 @@ __global__ __launch_bounds__(256) void k_init_energy(DevState st) {
 // energy, a proposal to be made again), all lanes in between being refused at
 // once; at small ln f the lanes guess and refine (see the two phases below).
 // 32 x 32 sites, 16 windows x 4 walkers, ln f = 1, ns per attempt of the
-// slowest walker: 174 with one attempt after the other, 149 from event to
-// event (31 events a block in the disordered windows, 6 in the ordered ones);
-// 8,192 walkers of mixed sizes, 32 waves a CU: 80 -> 60 ms a step.
+// slowest walker: 174 with one attempt after the other, 86 from event to
+// event (31 events a block in the disordered windows, 6 in the ordered ones;
+// 380 cycles an event); 8,192 walkers of mixed sizes, 32 a CU, 100 sweeps: 80
+// -> 40 ms.
 constexpr double kMargin64 = 1e-10;   // log-domain slack of the exact-mode test (binary64)
 constexpr double kMargin32 = 1e-5;    // log-domain slack of the exact-mode test (binary32)
 // Blocks of a window whose ln f is at most this run the speculative phase.  Its
 // guesses hold longer the smaller ln f is; us per 10,000 attempts on 32 x 32
-// sites, 64 walkers, against the event phase: 2100 / 1697 at 2^-5, 1550 / 1757
-// at 2^-6, 957 / 1723 at 2^-7; 8 x 8 1151 / 1440 at 2^-6.
-constexpr double kSpecLnf = 0x1p-6;
-
+// sites, 64 walkers, against the event phase: 1557 / 1028 at 2^-6, 963 / 1016
+// at 2^-7, 672 / 1009 at 2^-8; 8 x 8 1162 / 1096 at 2^-6.
+constexpr double kSpecLnf = 0x1p-7;
 
 __device__ __forceinline__ uint64_t readlane64(uint64_t v, int j) {
     const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, j);
@@ -190,6 +190,16 @@ __device__ __forceinline__ double lane_read_d(double v, int src) {
 }
 __device__ __forceinline__ float lane_read_f(float v, int src) {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));
+}
+// Sum of v over the lanes up to this one (all active).
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 to rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 to rows 2, 3
+    return v;
 }
 // Orders this wavefront's LDS writes before its later LDS reads by other lanes.
 __device__ __forceinline__ void wave_lds_sync() {
@@ -547,12 +557,12 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     if (HELP && tid == 0) *sup_w = 0ull;
     walker_sync<WAVE>();
 
-    const int lo = st.start[k], hi = lo + W - 1;
+    const int lo = __builtin_amdgcn_readfirstlane(st.start[k]), hi = lo + W - 1;
     const int q = st.q;
     const double lnf = st.lnf[k];
     const float lnf32 = (float)lnf;
     const bool spec = lnf <= kSpecLnf;
-    int E = st.E[w];
+    int E = __builtin_amdgcn_readfirstlane(st.E[w]);
     if (E < lo || E > hi) return;  // not walked in: leave the walker untouched
     if (HELP && threadIdx.x >= 64) {
         // barrier i: blocks 0 .. i + 1 are drawn and block i has been read, so that
@@ -1078,69 +1088,145 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             // within the margin (evaluated exactly), or a proposal whose site or
             // neighbour was flipped earlier in the block: the flips then go to
             // the lattice and the later proposals they touch are made again.
-            const unsigned long long livem = todo == 64 ? ~0ull : ((1ull << todo) - 1ull);
+            //
+            // The loop is bound by the length of its instruction stream (one
+            // wavefront issues an instruction every 4 to 5 cycles) and by the
+            // chain from the event's lane through ln g of the lanes' new
+            // energies to the next event.  So what an event does not change is
+            // kept: A = (lane) ln f - ln u, with -inf for dE = 0 (never an event
+            // while ln g(E) is finite; else all lanes are, and are decided
+            // exactly), and the conflicts not yet included in a proposal.
             const double slope = PREC == 0 ? lnf : (double)lnf32;
-            // ga is off by at most 64 roundings of values up to |ln g| + 64 ln f
+            // t is off by at most 64 roundings of values up to |ln g| + 64 ln f + |ln u|
             const double Mc = (PREC == 0 ? kMargin64 : kMargin32) + (64.0 * slope + 1024.0) * (PREC == 0 ? 0x1p-46 : 0x1p-18);
-            unsigned long long seen = 0ull;   // accepted flips the lanes' proposals include
-            int i = 0, owed = 0;              // next attempt; visits not yet added to ln g(E)
-            double ga = 0.0, M = 0.0;
-            bool fin = true;
+            const double ls = (double)lane * slope;
+            const int lane4 = 4 * lane;
+            double A = dE == 0 || !live ? -__builtin_inf() : ls - lnu;
+            int dE4 = 4 * dE;                 // cache lanes are named by 4 lane, the unit of ds_bpermute
+            conf = live ? conf : 0ull;
+            // accepted attempts, and those with dE = 0 still ahead (taken in passing)
+            unsigned long long may = __ballot(dE == 0);
+            unsigned long long rem = ~0ull;   // attempts not decided yet
+            int i = 0;                        // next attempt; its predecessors' visits are in ln g(E)
+            int e4 = 4 * erel;
+            const int E0 = ebase + erel;
+            double gb = 0.0, M = 0.0;         // ln g(E) extended back to attempt 0; margin
             auto arrive = [&](int first) {    // at a bin whose ln g (in registers) attempt `first` meets
                 const double base = PREC == 0 ? gEv : (double)gEh + (double)gEl;
-                ga = base + (double)(lane - first) * slope;
+                gb = base - readlane_d(ls, first);
                 M = PREC == 0 ? __builtin_fma(fabs(base), 0x1p-46, Mc)
                               : __builtin_fma(fabs(base) * 0x1p-24 + (double)fabsf(gEl), 0x1p-18, Mc);
-                fin = __ballot(__builtin_isfinite(base)) != 0ull;
             };
-            auto pay = [&]() {                // the visits owed, one addition each
-                for (; owed >= 4; owed -= 4) {
-                    if (PREC == 0) { gEv = gEv + lnf_v; gEv = gEv + lnf_v; gEv = gEv + lnf_v; gEv = gEv + lnf_v; }
-                    else for (int r = 0; r < 4; ++r) two_sum_add(gEh, gEl, lnf32);
+            auto visit = [&]() {
+                if (PREC == 0) gEv = gEv + lnf_v;
+                else two_sum_add(gEh, gEl, lnf32);
+            };
+            auto stay = [&](int at4, int times) {   // visits of refused attempts, one addition each; the bin to the cache
+                for (; times >= 4; times -= 4) {
+                    visit();
+                    visit();
+                    visit();
+                    visit();
                 }
-                for (; owed > 0; --owed) {
-                    if (PREC == 0) gEv = gEv + lnf_v;
-                    else two_sum_add(gEh, gEl, lnf32);
-                }
-                if (PREC == 0) c64 = lane == erel ? gEv : c64;
-                else { ch = lane == erel ? gEh : ch; cl = lane == erel ? gEl : cl; }
+                for (; times > 0; --times) visit();
+                if (PREC == 0) c64 = lane4 == at4 ? gEv : c64;
+                else { ch = lane4 == at4 ? gEh : ch; cl = lane4 == at4 ? gEl : cl; }
             };
             if (PREC == 0) gEv = readlane_d(c64, erel);
             else { gEh = readlane_f(ch, erel); gEl = readlane_f(cl, erel); }
-            int hist = ebase + erel;          // energy after the lane's attempt
-            arrive(0);
-            while (i < todo) {
-                const unsigned long long from = livem & (~0ull << i);
-                const unsigned long long zero = fin ? __ballot(dE == 0) & from : 0ull;
-                const int idx = erel + dE;
-                double gN = 0.0, t = 0.0, Mt = M;
-                float gNh = 0.0f, gNl = 0.0f;
+            double gN = 0.0, t = 0.0, Mt = 0.0;    // ln g of the lane's new energy, ...
+            float gNh = 0.0f, gNl = 0.0f;
+            // attempts that may be the event; conflicts; plain ones (no conflict,
+            // the cache holds the energies four either side); the event, if plain
+            // and accepted for sure
+            unsigned long long S = 0ull, C = 0ull, R = 0ull, first = 0ull;
+            int idx4 = 0;                     // the lane's new energy in the cache
+            auto read = [&]() {
+                idx4 = e4 + dE4;
                 if (PREC == 0) {
-                    gN = lane_read_d(c64, idx);
-                    t = (ga - gN) - lnu;
+                    const uint64_t bits = (uint64_t)__double_as_longlong(c64);
+                    const uint32_t l0 = (uint32_t)__builtin_amdgcn_ds_bpermute(idx4, (int)(uint32_t)bits);
+                    const uint32_t l1 = (uint32_t)__builtin_amdgcn_ds_bpermute(idx4, (int)(uint32_t)(bits >> 32));
+                    gN = __longlong_as_double((long long)(((uint64_t)l1 << 32) | l0));
                 } else {
-                    gNh = lane_read_f(ch, idx);
-                    gNl = lane_read_f(cl, idx);
-                    const double d = ga - ((double)gNh + (double)gNl);
-                    t = d - lnu;
+                    gNh = __int_as_float(__builtin_amdgcn_ds_bpermute(idx4, __float_as_int(ch)));
+                    gNl = __int_as_float(__builtin_amdgcn_ds_bpermute(idx4, __float_as_int(cl)));
+                }
+            };
+            auto sort = [&]() {
+                C = __ballot((conf & may) != 0ull);
+                R = __ballot((unsigned)(idx4 - 16) < 224u) & ~C;
+            };
+            auto weigh = [&]() {
+                Mt = M;
+                if (PREC == 0) {
+                    t = (gb - gN) + A;
+                } else {
+                    const double d = gb - ((double)gNh + (double)gNl);
+                    t = d + A;
                     Mt = M + (fabs(d) + (double)fabsf(gNl)) * 0x1p-18;
                 }
-                unsigned long long S = __ballot(!(t < -Mt)) & ~zero, C = 0ull;
-                if (anyconf) {
-                    C = __ballot((conf & (accepted | zero) & ~seen) != 0ull);
-                    S |= C;
+                S = (__ballot(!(t < -Mt)) | C) & rem;
+                first = __ballot(t > Mt) & R & S & (0ull - S);
+            };
+            auto next = [&](int j) {          // attempt j is decided
+                arrive(j);
+                visit();
+                i = j + 1;
+                rem = ~1ull << j;
+            };
+            arrive(0);
+            read();
+            sort();
+            weigh();
+            for (;;) {
+                // Events accepted for sure, one after the other.  With a helper the
+                // SIMD has little else to issue: the lanes' next ln g is on its way
+                // while the walker's bin is paid, and the lanes that go back to it
+                // take the paid value.  Without, many walkers share the issue slots
+                // and the bin is paid first (256 mixed instances: 41.8 against
+                // 42.9 ms per 100 sweeps; 64 walkers of 32 x 32 sites, 10,000
+                // attempts: 2011 against 1885 us).
+                while (first != 0ull) {
+                    const int j = (int)__builtin_ctzll(first);
+                    const double to64 = PREC == 0 ? readlane_d(gN, j) : 0.0;
+                    const float toh = PREC == 0 ? 0.0f : readlane_f(gNh, j), tol = PREC == 0 ? 0.0f : readlane_f(gNl, j);
+                    const int from4 = e4;
+                    e4 += __builtin_amdgcn_readlane(dE4, j);
+                    if constexpr (!HELP) stay(from4, j - i);
+                    read();
+                    if constexpr (HELP) stay(from4, j - i);
+                    const bool back = idx4 == from4;
+                    const double paid = gEv;
+                    const float paidh = gEh, paidl = gEl;
+                    if (PREC == 0) gEv = to64;
+                    else { gEh = toh; gEl = tol; }
+                    may |= first;
+                    next(j);
+                    sort();
+                    if constexpr (HELP) {
+                        __builtin_amdgcn_sched_barrier(0);   // what does not need them comes before the wait for them
+                        if (PREC == 0) gN = back ? paid : gN;
+                        else {
+                            gNh = back ? paidh : gNh;
+                            gNl = back ? paidl : gNl;
+                        }
+                    }
+                    weigh();
                 }
-                S &= from;
-                const int j = S ? (int)__builtin_ctzll(S) : todo;
-                accepted |= zero & (j >= 64 ? ~0ull : ((1ull << j) - 1ull));
-                owed += j - i;
-                i = j;
+                if (S == 0ull) break;
+                const int j = (int)__builtin_ctzll(S);
                 if (j >= todo) break;
+                const int dj = __builtin_amdgcn_readlane(dE, j);
+                stay(e4, j - i);
+                i = j;
                 if ((C >> j) & 1ull) {
+                    const unsigned long long ahead = ~0ull << j;
+                    accepted = may & ~ahead;
                     if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
                     flushed = accepted;
-                    wave_lds_sync();
-                    if (lane >= j && (conf & accepted & ~seen) != 0ull) {
+                    asm volatile("" ::: "memory");   // a wavefront's LDS operations execute in order
+                    if (lane >= j && (conf & accepted) != 0ull) {
                         x0 = sp[p.site];
                         x1 = sp[p.nb0];
                         x2 = sp[p.nb1];
@@ -1150,45 +1236,50 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                         if (nv >= q) nv -= q;
                         dE = (int)(x0 == x1) + (int)(x0 == x2) + (int)(x0 == x3) + (int)(x0 == x4) -
                              (int)(nv == x1) - (int)(nv == x2) - (int)(nv == x3) - (int)(nv == x4);
+                        A = dE == 0 ? -__builtin_inf() : ls - lnu;
+                        dE4 = 4 * dE;
                     }
-                    seen = accepted;
-                    continue;
+                    conf &= ahead;            // what came before is in the proposals now
+                    may = accepted | (__ballot(dE == 0) & ahead);
+                } else {
+                    bool acc = (__ballot(t > Mt) >> j) & 1ull;
+                    if (!acc) {               // within the margin (or ln g not finite)
+                        const int En = ebase + (e4 >> 2) + dj;
+                        const uint32_t u = __builtin_amdgcn_readlane(p.u, j);
+                        if (PREC == 0) {
+                            const double gj = dj ? readlane_d(gN, j) : gEv;
+                            acc = En >= lo && En <= hi && __ballot(accept64(gEv - gj, u)) != 0ull;
+                        } else {
+                            const float hj = dj ? readlane_f(gNh, j) : gEh, lj = dj ? readlane_f(gNl, j) : gEl;
+                            acc = En >= lo && En <= hi && __ballot(accept32((gEh - hj) + (gEl - lj), u)) != 0ull;
+                        }
+                        may &= ~(1ull << j);
+                    }
+                    if (acc) {
+                        may |= 1ull << j;
+                        if (dj) {
+                            if (PREC == 0) gEv = readlane_d(gN, j);
+                            else { gEh = readlane_f(gNh, j); gEl = readlane_f(gNl, j); }
+                            e4 += 4 * dj;
+                            if ((unsigned)(e4 - 16) >= 224u) {
+                                cache_store();
+                                ebase += (e4 >> 2) - 32;
+                                e4 = 4 * 32;
+                                cache_load();
+                            }
+                        }
+                    }
+                    next(j);
                 }
-                const int dj = __builtin_amdgcn_readlane(dE, j);
-                bool acc = (__ballot(t > Mt) >> j) & 1ull;
-                pay();
-                if (!acc) {   // within the margin (or ln g not finite)
-                    const int En = ebase + erel + dj;
-                    const uint32_t u = __builtin_amdgcn_readlane(p.u, j);
-                    if (PREC == 0) {
-                        const double gj = dj ? readlane_d(gN, j) : gEv;
-                        acc = En >= lo && En <= hi && __ballot(accept64(gEv - gj, u)) != 0ull;
-                    } else {
-                        const float hj = dj ? readlane_f(gNh, j) : gEh, lj = dj ? readlane_f(gNl, j) : gEl;
-                        acc = En >= lo && En <= hi && __ballot(accept32((gEh - hj) + (gEl - lj), u)) != 0ull;
-                    }
-                }
-                if (acc) {
-                    accepted |= 1ull << j;
-                    erel += dj;
-                    if (dj) {
-                        if (PREC == 0) gEv = readlane_d(gN, j);
-                        else { gEh = readlane_f(gNh, j); gEl = readlane_f(gNl, j); }
-                    }
-                    hist = lane >= j ? ebase + erel : hist;
-                    // proposals reach four energies either side of the walker
-                    if (__builtin_expect((unsigned)(erel - 4) >= 56u, 0)) {
-                        cache_store();
-                        ebase += erel - 32;
-                        erel = 32;
-                        cache_load();
-                    }
-                }
-                arrive(j);
-                owed = 1;
-                i = j + 1;
+                read();
+                sort();
+                weigh();
             }
-            pay();
+            stay(e4, todo - i);
+            erel = e4 >> 2;
+            accepted = may & (todo == 64 ? ~0ull : ((1ull << todo) - 1ull));
+            // energy after the lane's attempt: its accepted changes and those before
+            const int hist = E0 + wave_scan((int)(((accepted >> lane) & 1ull) ? dE : 0));
             if (live) atomicAdd(&H[hist - lo], 1u);
         }
 

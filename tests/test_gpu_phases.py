@@ -1,0 +1,41 @@
+"""GPU parity at the edges of the attempt kernel's rules: ln f on either side
+of the line between its two decision phases, blocks of one attempt more or less
+than a wavefront, walkers with and without a drawing wavefront beside them,
+and walkers per window around the exchange kernel's workgroup."""
+import pytest
+
+from statecmp import assert_same_state
+from test_gpu_parity import make_pair
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L,q,h,m,sync,precision,lnf", [
+    (4, 2, 2, 3, 333, 0, 1.0),            # 16 sites: nearly every attempt touches an earlier one
+    (4, 2, 2, 3, 333, 1, 0.3),
+    (8, 10, 4, 1, 63, 0, 1.0),            # blocks of 63, 64 and 65 attempts
+    (8, 10, 4, 1, 64, 1, 1.0),
+    (8, 10, 4, 1, 65, 0, 2.0**-6),
+    (32, 10, 16, 4, 1000, 0, 2.0**-6),     # last halving from event to event
+    (32, 10, 16, 4, 1000, 1, 2.0**-6),
+    (32, 10, 16, 4, 1000, 0, 2.0**-7),     # first that guesses
+    (32, 10, 16, 4, 1000, 1, 2.0**-7),
+    (12, 3, 4, 384, 500, 0, 1.0),         # six walkers a compute unit: with a drawing wavefront
+    (12, 3, 4, 385, 500, 0, 1.0),         # more: without
+    (12, 3, 4, 385, 500, 1, 1.0),
+    (12, 3, 4, 385, 500, 0, 2.0**-7),
+])
+def test_decision_phases_bitexact(L, q, h, m, sync, precision, lnf):
+    g, o = make_pair(L, q, h, m, lnf_init=lnf, fixed_lnf=1, sync_attempts=sync, exchange=1, precision=precision, seed=23)
+    for n in (sync, 3 * sync + 1):
+        g.run(n)
+        o.run(n)
+    assert_same_state(g, o)
+
+
+@pytest.mark.parametrize("m", [1, 2, 17, 64, 65])
+def test_exchange_and_flatness_over_walkers_per_window(m):
+    g, o = make_pair(6, 3, 3, m, lnf_init=1.0, flat=(1, 2), sync_attempts=300, exchange=1, seed=31)
+    g.run(6000)
+    o.run(6000)
+    assert_same_state(g, o)
