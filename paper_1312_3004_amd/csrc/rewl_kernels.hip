@@ -582,11 +582,14 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     int ebase = E - 32;
     double c64 = 0.0;
     float ch = 0.0f, cl = 0.0f;
+    // all ones while the window's ln g in the cache is finite: dE = 0 is then accepted
+    unsigned long long tame = 0ull;
     auto cache_load = [&]() {
         const int b = ebase + lane - lo;
         const bool in = b >= 0 && b < W;
         if (PREC == 0) c64 = in ? g[b] : __builtin_inf();
         else { ch = in ? gh[b] : __builtin_inff(); cl = in ? gl[b] : 0.0f; }
+        tame = __ballot(in && !__builtin_isfinite(PREC == 0 ? c64 : (double)(ch + cl))) ? 0ull : ~0ull;
     };
     auto cache_store = [&]() {
         const int b = ebase + lane - lo;
@@ -898,7 +901,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                         M = M0 + (((double)fabsf(aH) + (double)fabsf(aH)) + 256.0) * Mr + ((double)fabsf(d0) + 1.0) * 0x1p-19;
                         if (t0 == -__builtin_inf()) M = 0.0;
                     }
-                    const unsigned long long yes = __ballot(dEn == 0 || t0 > M), no = __ballot(t0 < -M);
+                    const unsigned long long yes = (__ballot(dEn == 0) & tame) | __ballot(t0 > M), no = __ballot(t0 < -M);
                     const unsigned long long open = act & ~F;
                     Out = __ballot(out) & open;
                     const unsigned long long An = (yes & open & ~Out) | FA;

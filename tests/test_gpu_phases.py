@@ -1,7 +1,8 @@
 """GPU parity at the edges of the attempt kernel's rules: ln f on either side
 of the line between its two decision phases, blocks of one attempt more or less
 than a wavefront, walkers with and without a drawing wavefront beside them,
-and walkers per window around the exchange kernel's workgroup."""
+infinite ln g, and walkers per window around the exchange kernel's workgroup."""
+import numpy as np
 import pytest
 
 from statecmp import assert_same_state
@@ -30,6 +31,20 @@ def test_decision_phases_bitexact(L, q, h, m, sync, precision, lnf):
     for n in (sync, 3 * sync + 1):
         g.run(n)
         o.run(n)
+    assert_same_state(g, o)
+
+
+@pytest.mark.parametrize("precision,lnf", [(0, 0.5), (1, 0.5), (0, 2.0**-9), (1, 2.0**-9)])
+def test_infinite_weights_bitexact(precision, lnf):
+    # bins no walker may enter (+inf) and bins every proposal is accepted into (-inf)
+    g, o = make_pair(8, 3, 1, 4, lnf_init=lnf, fixed_lnf=1, sync_attempts=500, precision=precision, seed=29)
+    for w in range(4):
+        lng = 0.25 * np.arange(g.W, dtype=np.float64)
+        lng[w::9] = np.inf if w % 2 else -np.inf
+        g.set_lng(w, lng)
+        o.set_lng(w, lng)
+    g.run(3001)
+    o.run(3001)
     assert_same_state(g, o)
 
 
