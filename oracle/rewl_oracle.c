@@ -349,7 +349,7 @@ static orc_t *orc_new(int B, int e_lo, int N, int h, double overlap, int m, uint
     o->precision = precision; o->fixed_lnf = fixed_lnf; o->shadow = shadow != 0; o->threads = 1;
     o->walkin_slack = walkin_slack;
     size_t nw = (size_t)o->nw, W = (size_t)o->W;
-    o->spin = (int8_t *)malloc(nw * (size_t)N);
+    o->spin = (int8_t *)calloc(nw * (size_t)N, 1);
     o->E = (int32_t *)calloc(nw, sizeof(int32_t));
     if (precision == 0) o->lng = (double *)calloc(nw * W, sizeof(double));
     else { o->lng_hi = (float *)calloc(nw * W, sizeof(float)); o->lng_lo = (float *)calloc(nw * W, sizeof(float)); }
