@@ -30,13 +30,16 @@
 // list alone, 32 partners x 2 places per pass.  In the N = 1000 lipid system
 // 6% of the partners pass the screen.
 //
+// Decisions go from one accepted attempt to the next, all lanes at once, the
+// corrections in registers (a lane's 16, the column by a uniform index).
+//
 // Measured on 64 walkers (one workgroup each), us per attempt of a walker:
-// 64 trimers 1.45 -> 0.64 (six wavefronts sharing the partners of one attempt
-// before), N = 1000 lipids 4.06 -> 1.49 (sixteen).  A block of 14.5 trimer
-// attempts takes 1,350 cycles of proposals, 7,100 of evaluation (bound by
-// instruction issue, four wavefronts per SIMD) and 8,000 of decisions (one
-// wavefront; 6.7 accepted attempts, a chain of binary64 operations and LDS
-// reads each).
+// 64 trimers 1.45 -> 0.49 (six wavefronts sharing the partners of one attempt
+// before), N = 1000 lipids 4.06 -> 1.23 (sixteen).  A block of 14.5 trimer
+// attempts takes 1,350 cycles of proposals, 7,200 of evaluation (VALU issue,
+// four wavefronts per SIMD, 76% busy) and 5,200 of decisions (one wavefront,
+// 6.7 accepted attempts; 8,000 with a read of the correction table and the
+// bin paid in the chain of each).
 #pragma once
 
 #include "rewl_device.h"
@@ -50,7 +53,7 @@ constexpr int kMoveList = 96;    // list entries of a wavefront: at most 31 left
 struct MoveRow {
     int64_t de;        // energy change against the block-start configuration
     uint32_t bad;      // bits 0-15: (n_l, n_i) is a hard overlap; bits 16-31: (n_l, o_i) is one
-    uint32_t info;     // bits 0-15: earlier attempts on the same particle; bits 16-31: those with a correction
+    uint32_t same;     // earlier attempts on the same particle
     int32_t nbad;      // hard overlaps against the block-start configuration
     int32_t pad;
 };
@@ -261,9 +264,9 @@ __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &m
         }
         c += __shfl_xor(c, 16, 64);
         c += __shfl_xor(c, 32, 64);
-        if (lane < l) tab[l * waves + lane] = c;
     }
-    const unsigned long long badm = __ballot(bad), nzm = __ballot(c != 0) & 0xffffull;
+    if (lane < l) tab[l * waves + lane] = c;
+    const unsigned long long badm = __ballot(bad);
     const int64_t de = wave_sum64(acc);
     // the lanes' overlap counts (new places only can have one)
     int over = 0;
@@ -272,7 +275,7 @@ __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &m
         MoveRow r;
         r.de = de;
         r.bad = (uint32_t)(badm & 0xffffull) | ((uint32_t)(badm >> 32) << 16);
-        r.info = (uint32_t)(samem & 0xffffull) | ((uint32_t)nzm << 16);
+        r.same = (uint32_t)(samem & 0xffffull);
         r.nbad = over;
         r.pad = 0;
         rows[l] = r;
@@ -398,20 +401,20 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
         // refused; the first one that is not is taken, the energies of the
         // later ones corrected for it, and so on.
         int64_t tot = 0;
-        uint32_t bad = 0, info = 0;
+        uint32_t bad = 0, prior = 0;         // prior: earlier attempts on the same particle
         int over = 0;
         const bool mine = lane < nblk;
         if (mine) {
             const MoveRow r = rows[lane];
             tot = r.de;
             bad = r.bad;
-            info = r.info;
+            prior = r.same;
             over = r.nbad;
         }
-        const unsigned long long blkm = (1ull << nblk) - 1ull;
+        const uint32_t blkm = (1u << nblk) - 1u;
         uint32_t accm = 0;
         int i = 0, bE = E - lo;              // next attempt; the walker's bin in its window
-        uint32_t visits = 0;                 // at the walker's bin, not yet in H
+        int hist = bE;                       // bin after the lane's attempt
         double gE = 0.0;
         float gEh = 0.0f, gEl = 0.0f;
         if (PREC == 0) gE = g[bE];
@@ -421,16 +424,109 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
                 if (PREC == 0) gE = gE + lnf;
                 else two_sum_add(gEh, gEl, lnf32);
             }
-            visits += (uint32_t)times;
         };
         auto flush = [&]() {
             if (lane == 0) {
                 if (PREC == 0) g[bE] = gE;
                 else { gh[bE] = gEh; gl[bE] = gEl; }
-                atomicAdd(&H[bE], visits);
             }
-            visits = 0;
         };
+        // The common case in a loop of its own: no overlaps, energies of the
+        // window inside the fixed-point range (B < 2^16 bins: the walk-in's
+        // counts are in LDS).  It is bound by the chain from one accepted
+        // attempt to the next, so the corrections are in registers, what an
+        // event does not change is kept (A = (lane) ln f - ln u), and the lanes'
+        // next ln g is read while the walker's bin is paid; lanes that go back
+        // to it take the paid value.
+        const bool plain = st.binw_fx <= ((int64_t)1 << 44) && !__ballot(over != 0 || bad != 0u);
+        if (plain) {
+            // the lane's corrections for attempts 0 .. 15 (those for itself and
+            // later ones, and of lanes past the block, are never looked at)
+            typedef long long move_l16 __attribute__((ext_vector_type(16)));
+            move_l16 corr;
+            const int64_t *row = tab + (lane < waves ? lane : waves - 1) * waves;
+#pragma unroll
+            for (int r = 0; r < kMoveMaxWaves; ++r) corr[r] = row[r];
+            const double slope = PREC == 0 ? lnf : (double)lnf32;
+            const double ls = (double)lane * slope, A = ls - lnu;
+            // t is off by at most 64 roundings of values up to |ln g| + 64 ln f + |ln u|
+            const double Mc = PREC == 0 ? 1e-10 + (64.0 * slope + 1024.0) * 0x1p-46 : 1e-5 + (64.0 * slope + 1024.0) * 0x1p-18;
+            int64_t e_new = 0;
+            int bn = 0, from = -1;            // the lanes' new bins; the bin left last
+            double gN = 0.0, paid = 0.0;      // ln g of the new bin
+            float gNh = 0.0f, gNl = 0.0f, paidh = 0.0f, paidl = 0.0f;
+            bool in = false;
+            auto look = [&]() {
+                e_new = Ef + tot;
+                const double qd = (double)(e_new - st.emin_fx) * st.binw_inv;
+                const double fl = __builtin_floor(qd), fr = qd - fl;
+                bn = (int)fl - lo;
+                if (__ballot(!(fabs(fr - 0.5) < 0.5 - 0x1p-20))) bn = fx_bin(st.emin_fx, st.binw_fx, st.binw_inv, e_new) - lo;
+                in = (unsigned)bn < (unsigned)W;
+                const int bi = in ? bn : 0;
+                if (PREC == 0) gN = g[bi];
+                else { gNh = gh[bi]; gNl = gl[bi]; }
+            };
+            uint32_t S = 0u, first = 0u;      // may be the event; the event, if accepted for sure
+            auto weigh = [&]() {
+                const double base = PREC == 0 ? gE : (double)gEh + (double)gEl;
+                const double gb = base - move_readlane_d(ls, i);
+                const double M = PREC == 0 ? __builtin_fma(fabs(base), 0x1p-46, Mc)
+                                           : __builtin_fma(fabs(base) * 0x1p-24 + (double)fabsf(gEl), 0x1p-18, Mc);
+                const uint32_t C = (uint32_t)__ballot((prior & accm) != 0u), rem = blkm & (~0u << i);
+                double v;
+                if (PREC == 0) {
+                    gN = bn == from ? paid : gN;
+                    v = gN;
+                } else {
+                    gNh = bn == from ? paidh : gNh;
+                    gNl = bn == from ? paidl : gNl;
+                    v = (double)gNh + (double)gNl;
+                }
+                // the walker's own bin: accepted; outside the window: refused (both
+                // while ln g(E) is finite; else all lanes are left to the exact round)
+                const uint64_t vb = (uint64_t)__double_as_longlong(v);
+                uint32_t hi = (uint32_t)(vb >> 32);
+                hi = bn == bE ? 0xffe00000u : hi;
+                hi = in ? hi : 0x7fe00000u;
+                v = __longlong_as_double((long long)(((uint64_t)hi << 32) | (uint32_t)vb));
+                const double d = gb - v, t = d + A;
+                const double Mt = PREC == 0 ? M : M + (fabs(d) + (double)fabsf(gNl)) * 0x1p-18;
+                S = ((uint32_t)__ballot(!(t < -Mt)) | C) & rem;
+                first = (uint32_t)__ballot(t > Mt) & ~C & S & (0u - S);
+            };
+            look();
+            weigh();
+            while (first != 0u) {
+                const int j = (int)__builtin_ctz(first);
+                const int bj = __builtin_amdgcn_readlane(bn, j);
+                Ef = move_readlane64(e_new, j);
+                const double gj = PREC == 0 ? move_readlane_d(gN, j) : 0.0;
+                const float hj = PREC == 0 ? 0.0f : move_readlane_f(gNh, j), lj = PREC == 0 ? 0.0f : move_readlane_f(gNl, j);
+                tot += corr[j];
+                accm |= first;
+                look();
+                add_lnf(j - i);
+                i = j + 1;
+                from = bE;
+                paid = gE;
+                paidh = gEh;
+                paidl = gEl;
+                if (bj != bE) {
+                    flush();
+                    bE = bj;
+                    if (PREC == 0) gE = gj;
+                    else { gEh = hj; gEl = lj; }
+                    hist = lane >= j ? bj : hist;
+                }
+                add_lnf(1);
+                weigh();
+            }
+            if (S == 0u) {
+                add_lnf(nblk - i);
+                i = nblk;
+            }
+        }
         while (i < nblk) {
             int64_t e_new = 0;
             const bool none = over - __builtin_popcount((bad >> 16) & accm) + __builtin_popcount(bad & accm) == 0;
@@ -460,13 +556,13 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
                 yes = d > M || tt > M;
                 no = tt < -M;
             }
-            const unsigned long long Y = __ballot(in && (yes || stay)), C = __ballot((info & 0xffffu & accm) != 0u);
-            const unsigned long long S = (__ballot(in && (!no || stay)) | C) & blkm & (~0ull << i);
-            const int j = S ? (int)__builtin_ctzll(S) : nblk;
+            const uint32_t Y = (uint32_t)__ballot(in && (yes || stay)), C = (uint32_t)__ballot((prior & accm) != 0u);
+            const uint32_t S = ((uint32_t)__ballot(in && (!no || stay)) | C) & blkm & (~0u << i);
+            const int j = S ? (int)__builtin_ctz(S) : nblk;
             add_lnf(j - i);
             i = j;
-            if (j >= nblk || ((C >> j) & 1ull)) break;
-            bool acc = (Y >> j) & 1ull;
+            if (j >= nblk || ((C >> j) & 1u)) break;
+            bool acc = (Y >> j) & 1u;
             const int bj = __builtin_amdgcn_readlane(bi, j);
             if (PREC == 0) {
                 const double gj = move_readlane_d(gN, j);
@@ -484,16 +580,15 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
             if (acc) {
                 Ef = move_readlane64(e_new, j);
                 bE = bj;
+                hist = lane >= j ? bj : hist;
                 accm |= 1u << j;
-                const bool fix = mine && ((info >> (16 + j)) & 1u);   // a correction for attempt j
-                if (__ballot(fix)) {
-                    if (fix) tot += tab[lane * waves + j];
-                }
+                if (mine && lane > j) tot += tab[lane * waves + j];   // the correction for attempt j
             }
             add_lnf(1);
             i = j + 1;
         }
         flush();
+        if (lane < i) atomicAdd(&H[hist], 1u);
         E = bE + lo;
         if ((accm >> (lane & 31)) & 1u & (uint32_t)(lane < nblk)) {
             float *xo = md.x + 3 * bead;

@@ -78,3 +78,14 @@ def test_moves_beyond_a_million_bins():
     o.run(3000)
     assert_same_state(g, o)
     assert_same_energies(g, o)
+
+
+@pytest.mark.parametrize("bin_w,precision", [(4096.0, 0), (4096.0, 1), (4097.0, 0), (4097.0, 1)])
+def test_widest_bins_of_the_quick_decisions(bin_w, precision):
+    # 2^44 units of energy a bin, and a unit of energy more: exact rounds only
+    g, o = trimer_pair(8, 5.0, -5.0 * bin_w, bin_w, 10, 1, 2, lnf_init=0.05, fixed_lnf=1, sync_attempts=300,
+                       precision=precision, seed=7)
+    g.run(900)
+    o.run(900)
+    assert_same_state(g, o)
+    assert_same_energies(g, o)
