@@ -405,7 +405,9 @@ __global__ __launch_bounds__(64) void k_lipid_walkin(DevState st, int64_t chunk,
 // v, v + waves, ...; the waves' exact sums are added by wavefront 0, which
 // decides.  All branches that contain a barrier depend only on the attempt's
 // random words or on values every wave reads from LDS, so the waves agree.
+template <bool GRID>
 struct LipidMoves {
+    static constexpr bool kGrid = GRID;    // 16-bit places in LDS
     static constexpr bool kReptation = true;
     static constexpr bool kHeads = false;
     float *x;
@@ -539,7 +541,7 @@ struct LipidMoves {
                     const int j = c * 64 + lane;
                     const int jj = j < st.nb ? j : 0;
                     bool near = j < st.nb && j != ci &&
-                                move_grid2(grid ? grid[jj] : move_grid(v.x + 3 * jj, scale), gc) <= lim;
+                                move_grid2(GRID ? grid[jj] : move_grid(v.x + 3 * jj, scale), gc) <= lim;
                     for (int a = 0; a < 4; ++a) near = near && !(p.c[a] == j && ci > j);
                     const unsigned long long m = __ballot(near);
                     if (near) list[cnt + move_mbcnt(m)] = (uint16_t)j;
@@ -589,7 +591,8 @@ struct LipidMoves {
 static __host__ __device__ inline size_t lip_rep_bytes(int nch) { return (size_t)nch * 16; }
 constexpr size_t kLipRepPerWave = 8;
 
-__global__ __launch_bounds__(1024) void k_lipid_sweep(DevState st, int64_t s0, int64_t n, int has_grid) {
+template <bool GRID>
+__global__ __launch_bounds__(1024) void k_lipid_sweep(DevState st, int64_t s0, int64_t n) {
     if (*st.converged) return;
     const int w = blockIdx.x;
     const int k = w / st.m;
@@ -611,7 +614,7 @@ __global__ __launch_bounds__(1024) void k_lipid_sweep(DevState st, int64_t s0, i
         H[b] = st.H[row + b];
     }
     __syncthreads();
-    LipidMoves md;
+    LipidMoves<GRID> md;
     md.v = lip_view(st, smem);
     md.x = md.v.x;
     md.box = st.box;
@@ -621,8 +624,8 @@ __global__ __launch_bounds__(1024) void k_lipid_sweep(DevState st, int64_t s0, i
     md.mask1 = (unsigned long long *)rep;
     md.mask2 = md.mask1 + nch;
     md.wsum = (int64_t *)(md.mask2 + nch);
-    md.grid = has_grid ? (MoveGrid *)(md.wsum + nwave) : nullptr;
-    move_sweep<LipidMoves, 0>(st, md, w, s0, n, g, nullptr, nullptr, H, mv);
+    md.grid = GRID ? (MoveGrid *)(md.wsum + nwave) : nullptr;
+    move_sweep<LipidMoves<GRID>, 0>(st, md, w, s0, n, g, nullptr, nullptr, H, mv);
     const uint32_t *sx = (const uint32_t *)smem;
     uint32_t *ox = (uint32_t *)(st.spins + (size_t)w * st.Npad);
     for (int i = threadIdx.x; i < st.Npad / 4; i += blockDim.x) ox[i] = sx[i];
@@ -660,10 +663,13 @@ hipError_t launch_lipid_walkin(const DevState &st, int64_t chunk, int64_t budget
 
 hipError_t launch_lipid_sweep(const DevState &st, int64_t s0, int64_t n, hipStream_t s) {
     const MovePlan p = lipid_plan(st);
-    const hipError_t e = lip_allow((const void *)k_lipid_sweep, p.lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_lipid_sweep, dim3(st.nw), dim3(64 * p.waves), p.lds, s, st, s0, n, p.grid);
-    return hipGetLastError();
+    auto go = [&](auto kernel) -> hipError_t {
+        const hipError_t e = lip_allow((const void *)kernel, p.lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(st.nw), dim3(64 * p.waves), p.lds, s, st, s0, n);
+        return hipGetLastError();
+    };
+    return p.grid ? go(k_lipid_sweep<true>) : go(k_lipid_sweep<false>);
 }
 
 }  // namespace rewl_gpu

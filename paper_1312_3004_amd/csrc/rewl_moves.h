@@ -24,22 +24,25 @@
 // A wavefront screens its partners 64 at a time on places rounded down to box
 // / 65536 and held as 16-bit integers: the differences wrap at the periodic
 // boundary by themselves and two 16-bit dot products give the squared distance,
-// 5 operations where the binary32 minimum image takes 13.  Partners within the
-// cut-off plus the length of the move of the old place go to a list in LDS,
-// and the pair energies (binary64 divisions and roots) are evaluated for the
-// list alone, 32 partners x 2 places per pass.  In the N = 1000 lipid system
-// 6% of the partners pass the screen.
+// 5 operations where the binary32 minimum image takes 13; the next 64 places
+// are on their way meanwhile.  Partners within the cut-off plus the length of
+// the move of the old place go to a list in LDS, and the pair energies
+// (binary64 divisions and roots) are evaluated for the list alone, 32 partners
+// x 2 places per pass.  In the N = 1000 lipid system 6% of the partners pass
+// the screen.
 //
 // Decisions go from one accepted attempt to the next, all lanes at once, the
 // corrections in registers (a lane's 16, the column by a uniform index).
 //
 // Measured on 64 walkers (one workgroup each), us per attempt of a walker:
-// 64 trimers 1.45 -> 0.49 (six wavefronts sharing the partners of one attempt
-// before), N = 1000 lipids 4.06 -> 1.23 (sixteen).  A block of 14.5 trimer
-// attempts takes 1,350 cycles of proposals, 7,200 of evaluation (VALU issue,
-// four wavefronts per SIMD, 76% busy) and 5,200 of decisions (one wavefront,
+// 64 trimers 1.45 -> 0.48 (six wavefronts sharing the partners of one attempt
+// before), N = 1000 lipids 4.06 -> 1.17 (sixteen).  A block of 14.5 trimer
+// attempts takes 1,350 cycles of proposals, 7,100 of evaluation (VALU issue,
+// four wavefronts per SIMD, 76% busy) and 5,050 of decisions (one wavefront,
 // 6.7 accepted attempts; 8,000 with a read of the correction table and the
-// bin paid in the chain of each).
+// bin paid in the chain of each); one of 11.9 lipid attempts 2,650, 13,700
+// (14,300 with the partners that a bond or the bead itself rules out tested in
+// the screen) and 6,750, and every second block a reptation, 17,100.
 #pragma once
 
 #include "rewl_device.h"
@@ -207,12 +210,14 @@ __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &m
         if ((lane >> 1) < n) {
             const uint32_t ent = list[cnt - n + (lane >> 1)];
             const int j = (int)(ent & 0x7fffu);
-            const bool old = lane & 1;
+            const bool old = lane & 1, bond = (ent & 0x8000u) != 0;
             const float q[3] = {old ? p.o[0] : p.n[0], old ? p.o[1] : p.n[1], old ? p.o[2] : p.n[2]};
             int64_t t = 0;
-            const bool ok = fx_term(md.pair(b, j, q, md.x + 3 * j, (ent & 0x8000u) != 0), t);
-            nbad += (int)!ok;
-            acc += old ? -t : t;
+            const bool ok = fx_term(md.pair(b, j, q, md.x + 3 * j, bond), t);
+            // the screen lets the bead itself and its bonded partners through
+            const bool skip = !bond && (j == b || j == p0 || j == p1);
+            nbad += (int)(!ok && !skip);
+            acc += skip ? 0 : (old ? -t : t);
         }
         cnt -= n;
         move_wave_sync();
@@ -224,18 +229,21 @@ __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &m
     const uint32_t near2 = Model::kHeads ? move_grid_limit(1.1225f + p.reach, scale) : 0u;
     int r3 = lane % 3;                      // j mod 3
     const bool tail = b % 3 != 0;
+    auto place = [&](int j) -> MoveGrid { return Model::kGrid ? md.grid[j] : move_grid(md.x + 3 * j, scale); };
+    bool real = lane < st.nb;
+    MoveGrid ahead = place(real ? lane : 0);
     for (int c = 0; c < st.nb; c += 64) {
-        const int j = c + lane;
-        const int jj = j < st.nb ? j : 0;
-        const MoveGrid gj = md.grid ? md.grid[jj] : move_grid(md.x + 3 * jj, scale);
+        const MoveGrid gj = ahead;          // the next chunk's places are read while this one is screened
         uint32_t lim = far2;
         if constexpr (Model::kHeads) {
             lim = tail && r3 != 0 ? far2 : near2;
             r3 = r3 == 2 ? 0 : r3 + 1;      // 64 mod 3 = 1
         }
-        const bool near = j < st.nb && j != b && j != p0 && j != p1 && move_grid2(gj, go) <= lim;
-        const unsigned long long m = __ballot(near);
-        if (near) list[cnt + move_mbcnt(m)] = (uint16_t)j;
+        const unsigned long long m = __ballot(move_grid2(gj, go) <= lim) & __ballot(real);
+        const int jn = c + 64 + lane;
+        real = jn < st.nb;
+        ahead = place(real ? jn : 0);
+        if (__builtin_amdgcn_inverse_ballot_w64(m)) list[cnt + move_mbcnt(m)] = (uint16_t)(c + lane);
         cnt += __builtin_popcountll(m);
         while (cnt >= 32) pass(32);
     }
@@ -318,7 +326,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
     int bead = 0;
     uint32_t uw = 0;
     double lnu = 0.0;
-    if (md.grid) {
+    if constexpr (Model::kGrid) {
         for (int j = threadIdx.x; j < st.nb; j += blockDim.x) md.grid[j] = move_grid(md.x + 3 * j, md.scale);
     }
     for (;;) {
@@ -595,7 +603,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
             xo[0] = nx;
             xo[1] = ny;
             xo[2] = nz;
-            if (md.grid) md.grid[bead] = move_grid(xo, md.scale);
+            if constexpr (Model::kGrid) md.grid[bead] = move_grid(xo, md.scale);
         }
         t += i;
         move_wave_sync();

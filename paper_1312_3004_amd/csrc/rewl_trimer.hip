@@ -221,7 +221,9 @@ __global__ __launch_bounds__(64) void k_trimer_walkin(DevState st, int64_t chunk
 // One workgroup of 16 wavefronts per walker, an attempt per wavefront: blocks
 // of consecutive attempts evaluated side by side and decided in order
 // (rewl_moves.h).
+template <bool GRID>
 struct TrimerMoves {
+    static constexpr bool kGrid = GRID;    // 16-bit places in LDS
     static constexpr bool kReptation = false;
     static constexpr bool kHeads = true;   // pairs with a head reach 2^(1/6) only
     float *x;
@@ -238,8 +240,8 @@ struct TrimerMoves {
     }
 };
 
-template <int PREC>
-__global__ __launch_bounds__(1024) void k_trimer_sweep(DevState st, int64_t s0, int64_t n, int has_grid) {
+template <int PREC, bool GRID>
+__global__ __launch_bounds__(1024) void k_trimer_sweep(DevState st, int64_t s0, int64_t n) {
     if (*st.converged) return;
     const int w = blockIdx.x;
     const int k = w / st.m;
@@ -265,9 +267,9 @@ __global__ __launch_bounds__(1024) void k_trimer_sweep(DevState st, int64_t s0, 
     }
     __syncthreads();
     unsigned char *mv = smem + st.Npad + (size_t)Wpad * 12;
-    MoveGrid *grid = has_grid ? (MoveGrid *)(mv + move_lds_bytes((int)(blockDim.x >> 6))) : nullptr;
-    TrimerMoves md{(float *)smem, grid, st.box, 0.5f * st.box, 65536.0f / st.box};
-    move_sweep<TrimerMoves, PREC>(st, md, w, s0, n, g, gh, gl, H, mv);
+    MoveGrid *grid = GRID ? (MoveGrid *)(mv + move_lds_bytes((int)(blockDim.x >> 6))) : nullptr;
+    TrimerMoves<GRID> md{(float *)smem, grid, st.box, 0.5f * st.box, 65536.0f / st.box};
+    move_sweep<TrimerMoves<GRID>, PREC>(st, md, w, s0, n, g, gh, gl, H, mv);
     uint32_t *ox = (uint32_t *)(st.spins + (size_t)w * st.Npad);
     for (int i = threadIdx.x; i < st.Npad / 4; i += blockDim.x) ox[i] = ((uint32_t *)smem)[i];
     for (int b = threadIdx.x; b < W; b += blockDim.x) {
@@ -310,10 +312,11 @@ hipError_t launch_trimer_sweep(const DevState &st, int64_t s0, int64_t n, hipStr
     auto go = [&](auto kernel) -> hipError_t {
         const hipError_t e = allow((const void *)kernel, p.lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(st.nw), dim3(64 * p.waves), p.lds, s, st, s0, n, p.grid);
+        hipLaunchKernelGGL(kernel, dim3(st.nw), dim3(64 * p.waves), p.lds, s, st, s0, n);
         return hipGetLastError();
     };
-    return st.precision == 0 ? go(k_trimer_sweep<0>) : go(k_trimer_sweep<1>);
+    if (p.grid) return st.precision == 0 ? go(k_trimer_sweep<0, true>) : go(k_trimer_sweep<1, true>);
+    return st.precision == 0 ? go(k_trimer_sweep<0, false>) : go(k_trimer_sweep<1, false>);
 }
 
 }  // namespace rewl_gpu
