@@ -332,7 +332,7 @@ __device__ __forceinline__ void draw_block(const DevState &st, int w, uint64_t t
 // host relaunches until every walker is placed.
 //
 // Blocks of 64 attempts are decided from event to event as in the main phase
-// (sweep_walker): 32 x 32 sites, 64 walkers from random lattices, 130 -> 18.5 ms
+// (sweep_walker): 32 x 32 sites, 64 walkers from random lattices, 130 -> 12.7 ms
 // from creation to the last walker placed, against one attempt after the other.
 // Entries of its conflict-tag table: one per site up to 1,024 (hashed beyond:
 // a collision only has a proposal made again), as far as `lds` bytes hold them
@@ -387,46 +387,90 @@ __device__ __forceinline__ void walkin_walker(const DevState &st, int w, int64_t
         const unsigned long long livem = todo == 64 ? ~0ull : ((1ull << todo) - 1ull);
         unsigned long long W0, W1, W2, W3, W4;
         conflict_masks(p, lane < todo, tag, (uint32_t)ntag - 1u, lane, W0, W1, W2, W3, W4);
-        const unsigned long long conf = W0 | W1 | W2 | W3 | W4;
-        const unsigned long long anyconf = __ballot(conf != 0ull);
+        const bool live = lane < todo;
+        unsigned long long conf = live ? W0 | W1 | W2 | W3 | W4 : 0ull;
         int x0 = sp[p.site], x1 = sp[p.nb0], x2 = sp[p.nb1], x3 = sp[p.nb2], x4 = sp[p.nb3];
-        int nv = 0, dE = 0;
+        int nv = 0, dE4 = 0;                  // 4 dE: the unit of ds_bpermute
+        double A = 0.0;                       // (lane) - ln u, -inf for dE = 0 (accepted in passing)
         auto make = [&]() {
             nv = x0 + 1 + p.off;
             if (nv >= q) nv -= q;
-            dE = (int)(x0 == x1) + (int)(x0 == x2) + (int)(x0 == x3) + (int)(x0 == x4) - (int)(nv == x1) -
-                 (int)(nv == x2) - (int)(nv == x3) - (int)(nv == x4);
+            dE4 = 4 * ((int)(x0 == x1) + (int)(x0 == x2) + (int)(x0 == x3) + (int)(x0 == x4) - (int)(nv == x1) -
+                       (int)(nv == x2) - (int)(nv == x3) - (int)(nv == x4));
+            A = dE4 == 0 || !live ? -__builtin_inf() : (double)lane - lnu;
         };
         make();
-        unsigned long long accepted = 0ull, flushed = 0ull, seen = 0ull;
-        int i = 0;
-        while (i < todo) {
-            // counts are integers below 2^32: every sum and difference is exact,
-            // the margin covers ln u and exp alone
-            const unsigned long long from = livem & (~0ull << i);
-            const unsigned long long zero = __ballot(dE == 0) & from;
-            const int idx = erel + dE, En = ebase + idx;
-            const double cN = lane_read_d(c64, idx);
-            const double cE = readlane_d(c64, erel);
-            const double tt = ((cE + (double)(lane - i)) - cN) - lnu;
-            const bool inside = slack == 0 || (down ? En <= bound : En >= bound);
-            const bool maybe = inside && !(tt < -kMargin64);
-            unsigned long long S = __ballot(maybe) & ~zero, C = 0ull;
-            if (anyconf) {
-                C = __ballot((conf & (accepted | zero) & ~seen) != 0ull);
-                S |= C;
+        unsigned long long flushed = 0ull, rem = ~0ull;
+        unsigned long long may = __ballot(dE4 == 0);   // accepted attempts, and those with dE = 0 still ahead
+        int i = 0, e4 = 4 * erel, idx4 = 0;
+        double cE = readlane_d(c64, erel), cN = 0.0, tt = 0.0;   // visits at the walker's energy, at the lanes' new ones
+        // attempts that may be the event; conflicts; those under the lid; plain
+        // ones (no conflict, under the lid, the cache holds the energies four
+        // either side); the event, if plain and accepted for sure
+        unsigned long long S = 0ull, C = 0ull, I = 0ull, R = 0ull, first = 0ull;
+        auto read = [&]() {
+            idx4 = e4 + dE4;
+            const uint64_t bits = (uint64_t)__double_as_longlong(c64);
+            const uint32_t l0 = (uint32_t)__builtin_amdgcn_ds_bpermute(idx4, (int)(uint32_t)bits);
+            const uint32_t l1 = (uint32_t)__builtin_amdgcn_ds_bpermute(idx4, (int)(uint32_t)(bits >> 32));
+            cN = __longlong_as_double((long long)(((uint64_t)l1 << 32) | l0));
+        };
+        auto sort = [&]() {
+            C = __ballot((conf & may) != 0ull);
+            I = down ? __ballot(idx4 <= 4 * (bound - ebase)) : __ballot(idx4 >= 4 * (bound - ebase));
+            if (slack == 0) I = ~0ull;
+            R = __ballot((unsigned)(idx4 - 16) < 224u) & I & ~C;
+        };
+        // counts are integers below 2^32: every sum and difference is exact,
+        // the margin covers ln u and exp alone
+        auto weigh = [&]() {
+            tt = ((cE - (double)i) - cN) + A;
+            S = ((__ballot(!(tt < -kMargin64)) & I) | C) & rem;
+            first = __ballot(tt > kMargin64) & R & S & (0ull - S);
+        };
+        auto enter = [&]() {                  // the walker is at another energy
+            E = ebase + (e4 >> 2);
+            if (slack && down && E + slack < bound) bound = E + slack;
+            if (slack && !down && E - slack > bound) bound = E - slack;
+            done = E >= lo && E <= hi;
+        };
+        read();
+        sort();
+        weigh();
+        for (;;) {
+            // events accepted for sure, one after the other (see sweep_walker)
+            while (first != 0ull) {
+                const int j = (int)__builtin_ctzll(first);
+                const double to = readlane_d(cN, j);
+                const int from4 = e4;
+                e4 += __builtin_amdgcn_readlane(dE4, j);
+                read();
+                const double paid = cE + (double)(j - i);   // refused attempts count at the walker's energy
+                const bool back = idx4 == from4;
+                c64 = 4 * lane == from4 ? paid : c64;
+                cE = to + 1.0;
+                may |= first;
+                i = j + 1;
+                rem = ~1ull << j;
+                enter();
+                sort();
+                __builtin_amdgcn_sched_barrier(0);   // what does not need them comes before the wait for them
+                cN = back ? paid : cN;
+                weigh();
+                first = done ? 0ull : first;
             }
-            S &= from;
-            const int j = S ? (int)__builtin_ctzll(S) : todo;
-            accepted |= zero & (j >= 64 ? ~0ull : ((1ull << j) - 1ull));
-            double cNow = cE + (double)(j - i);     // refused attempts count at the walker's energy
+            if (done || S == 0ull) break;
+            const int j = (int)__builtin_ctzll(S);
+            if (j >= todo) break;
+            cE = cE + (double)(j - i);
+            c64 = 4 * lane == e4 ? cE : c64;
             i = j;
-            if (j < todo && ((C >> j) & 1ull)) {
-                c64 = lane == erel ? cNow : c64;
+            if ((C >> j) & 1ull) {
+                const unsigned long long ahead = ~0ull << j, accepted = may & ~ahead;
                 if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
                 flushed = accepted;
-                wave_lds_sync();
-                if (lane >= j && (conf & accepted & ~seen) != 0ull) {
+                asm volatile("" ::: "memory");   // a wavefront's LDS operations execute in order
+                if (lane >= j && (conf & accepted) != 0ull) {
                     x0 = sp[p.site];
                     x1 = sp[p.nb0];
                     x2 = sp[p.nb1];
@@ -434,42 +478,41 @@ __device__ __forceinline__ void walkin_walker(const DevState &st, int w, int64_t
                     x4 = sp[p.nb3];
                     make();
                 }
-                seen = accepted;
-                continue;
-            }
-            if (j >= todo) {
-                c64 = lane == erel ? cNow : c64;
-                break;
-            }
-            const int dj = __builtin_amdgcn_readlane(dE, j);
-            bool acc = (__ballot(tt > kMargin64) >> j) & 1ull;
-            if (!acc)
-                acc = __ballot(accept64(cNow - readlane_d(cN, j), __builtin_amdgcn_readlane(p.u, j))) != 0ull;
-            if (acc) {
-                c64 = lane == erel ? cNow : c64;
-                accepted |= 1ull << j;
-                erel += dj;
-                cNow = readlane_d(c64, erel);
-            }
-            c64 = lane == erel ? cNow + 1.0 : c64;
-            i = j + 1;
-            if (acc) {
-                E = ebase + erel;
-                if (slack && down && E + slack < bound) bound = E + slack;
-                if (slack && !down && E - slack > bound) bound = E - slack;
-                if (E >= lo && E <= hi) {
-                    done = true;
-                    break;
-                }
-                // proposals reach four energies either side of the walker
-                if ((unsigned)(erel - 4) >= 56u) {
-                    cache_store();
-                    ebase += erel - 32;
-                    erel = 32;
-                    cache_load();
+                conf &= ahead;                // what came before is in the proposals now
+                may = accepted | (__ballot(dE4 == 0) & ahead);
+            } else {
+                const int dj4 = __builtin_amdgcn_readlane(dE4, j);
+                const double to = readlane_d(cN, j);
+                const bool acc = ((__ballot(tt > kMargin64) >> j) & 1ull) ||
+                                 __ballot(accept64(cE - to, __builtin_amdgcn_readlane(p.u, j))) != 0ull;
+                i = j + 1;
+                rem = ~1ull << j;
+                cE = (acc ? to : cE) + 1.0;
+                if (acc) {
+                    may |= 1ull << j;
+                    e4 += dj4;
+                    enter();
+                    if (done) break;
+                    // proposals reach four energies either side of the walker
+                    if ((unsigned)(e4 - 16) >= 224u) {
+                        cache_store();
+                        ebase += (e4 >> 2) - 32;
+                        e4 = 4 * 32;
+                        cache_load();
+                    }
                 }
             }
+            read();
+            sort();
+            weigh();
         }
+        if (!done) {
+            cE = cE + (double)(todo - i);
+            i = todo;
+        }
+        c64 = 4 * lane == e4 ? cE : c64;
+        erel = e4 >> 2;
+        const unsigned long long accepted = may & (i >= 64 ? ~0ull : (1ull << i) - 1ull);
         t += i;
         if (((accepted & ~flushed) >> lane) & 1ull) sp[p.site] = (int8_t)nv;
         if ((unsigned)(erel - 16) >= 32u) {
