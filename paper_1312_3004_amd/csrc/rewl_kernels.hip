@@ -162,8 +162,8 @@ constexpr double kMargin64 = 1e-10;   // log-domain slack of the exact-mode test
 constexpr double kMargin32 = 1e-5;    // log-domain slack of the exact-mode test (binary32)
 // Blocks of a window whose ln f is at most this run the speculative phase.  Its
 // guesses hold longer the smaller ln f is; us per 10,000 attempts on 32 x 32
-// sites, 64 walkers, against the event phase: 1557 / 1028 at 2^-6, 963 / 1016
-// at 2^-7, 672 / 1009 at 2^-8; 8 x 8 1162 / 1096 at 2^-6.
+// sites, 64 walkers, against the event phase: 1445 / 1014 at 2^-6, 909 / 1000
+// at 2^-7, 634 / 992 at 2^-8; 8 x 8 1117 / 1072 at 2^-6.
 constexpr double kSpecLnf = 0x1p-7;
 
 __device__ __forceinline__ uint64_t readlane64(uint64_t v, int j) {
@@ -176,10 +176,6 @@ __device__ __forceinline__ double readlane_d(double v, int j) {
 }
 __device__ __forceinline__ float readlane_f(float v, int j) {
     return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), j));
-}
-// Set bits of m in the lanes below this one.
-__device__ __forceinline__ int mbcnt64(unsigned long long m) {
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 // v of lane src (a different lane per lane) by ds_bpermute; every lane active.
 __device__ __forceinline__ double lane_read_d(double v, int src) {
@@ -828,13 +824,18 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
             // it, so the fixed point is the sequential result, reached after at
             // most one round per attempt.  Per round, lane j takes
             //  * its energy before the attempt: E0 plus dE of the accepted
-            //    earlier lanes (bit counts over ballots of the dE bits),
+            //    earlier lanes (a prefix sum),
             //  * the spins of its site and neighbours: the new value of the last
             //    accepted earlier lane that flips that site, else the spin at
             //    segment start; from them its new value and dE,
             //  * its decision from the register cache's ln g at segment start,
             //    settled only outside a margin that bounds the ln g drift of
             //    the segment's earlier visits.
+            // A round is a chain of two reads from other lanes (the spins, then ln g;
+            // the second ahead of the first with the dE of the round before, and
+            // again only where a dE has changed) and the masks after it: 800 cycles,
+            // 2.7 rounds a block (32 x 32, ln f = 2^-21; 880 with bit counts for the
+            // energies and the dE at segment start for the read).
             // The first attempt that leaves unsettled is settled with the visits
             // of its two energies counted (see `settled`).
             // An attempt that cannot be settled even so (or an energy outside the
@@ -878,16 +879,13 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                     if constexpr (kFirst) {
                         pre = E0;
                     } else {
-                        const int de4 = dEi + 4;   // in [0, 8]
-                        const unsigned long long B0 = __ballot(de4 & 1), B1 = __ballot(de4 & 2);
-                        const unsigned long long B2 = __ballot(de4 & 4), B3 = __ballot(de4 & 8);
-                        pre = E0 - 4 * mbcnt64(Aa) + mbcnt64(B0 & Aa) + 2 * mbcnt64(B1 & Aa) +
-                              4 * mbcnt64(B2 & Aa) + 8 * mbcnt64(B3 & Aa);
+                        const int mine = __builtin_amdgcn_inverse_ballot_w64(Aa) ? dEi : 0;
+                        pre = E0 - mine + wave_scan(mine);
                     }
                     const int ip = pre - ebase;
-                    // ln g before the attempt, and after it for the segment-start dE
-                    // (read now; a lane whose dE changed reads again below)
-                    const int ib0 = ip + dE;
+                    // ln g before the attempt, and after it for the dE of the round
+                    // before (read now; a lane whose dE changed reads again below)
+                    const int ib0 = ip + dEi;
                     if (PREC == 0) {
                         a = lane_read_d(c64, ip & 63);
                         b = lane_read_d(c64, ib0 & 63);
@@ -903,11 +901,13 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                         int y0 = x0, y1 = x1, y2 = x2, y3 = x3, y4 = x4;
                         const unsigned long long a0 = W0 & Aa, a1 = W1 & Aa, a2 = W2 & Aa, a3 = W3 & Aa,
                                                  a4 = W4 & Aa;
-                        const int r0 = __builtin_amdgcn_ds_bpermute((a0 ? 63 - __builtin_clzll(a0) : lane) << 2, nvi);
-                        const int r1 = __builtin_amdgcn_ds_bpermute((a1 ? 63 - __builtin_clzll(a1) : lane) << 2, nvi);
-                        const int r2 = __builtin_amdgcn_ds_bpermute((a2 ? 63 - __builtin_clzll(a2) : lane) << 2, nvi);
-                        const int r3 = __builtin_amdgcn_ds_bpermute((a3 ? 63 - __builtin_clzll(a3) : lane) << 2, nvi);
-                        const int r4 = __builtin_amdgcn_ds_bpermute((a4 ? 63 - __builtin_clzll(a4) : lane) << 2, nvi);
+                        // new value of the latest of them (any lane's if there is none)
+                        auto latest = [&](unsigned long long m) {
+                            const uint32_t l = (uint32_t)m, h = (uint32_t)(m >> 32);
+                            const uint32_t fl = (l ? (uint32_t)__builtin_clz(l) : ~0u) + 32u, fh = h ? (uint32_t)__builtin_clz(h) : ~0u;
+                            return __builtin_amdgcn_ds_bpermute(-4 - 4 * (int)(fl < fh ? fl : fh), nvi);   // lane 63 - clz, modulo 64
+                        };
+                        const int r0 = latest(a0), r1 = latest(a1), r2 = latest(a2), r3 = latest(a3), r4 = latest(a4);
                         y0 = a0 ? r0 : y0;
                         y1 = a1 ? r1 : y1;
                         y2 = a2 ? r2 : y2;
@@ -919,15 +919,17 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                               (int)(nvn == y1) - (int)(nvn == y2) - (int)(nvn == y3) - (int)(nvn == y4);
                     }
                     const int inn = ip + dEn;
-                    if (!kFirst && (__ballot(dEn != dE) & act)) {
-                        if (PREC == 0) {
-                            const double b2 = lane_read_d(c64, inn & 63);
-                            b = dEn != dE ? b2 : b;
-                        } else {
-                            const float b2H = lane_read_f(ch, inn & 63), b2L = lane_read_f(cl, inn & 63);
-                            bH = dEn != dE ? b2H : bH;
-                            bL = dEn != dE ? b2L : bL;
+                    unsigned long long changed = 0ull;
+                    if constexpr (!kFirst) {
+                        const unsigned long long moved = __ballot(dEn != dEi) & act;
+                        if (moved) {
+                            if (PREC == 0) b = lane_read_d(c64, inn & 63);
+                            else {
+                                bH = lane_read_f(ch, inn & 63);
+                                bL = lane_read_f(cl, inn & 63);
+                            }
                         }
+                        changed = moved | (__ballot(nvn != nvi) & act);
                     }
                     // beyond the window ln g is +inf, a certain refusal; the margin
                     // needs no |b|: where d is small, |b| is near |a|, elsewhere the
@@ -949,7 +951,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                     Out = __ballot(out) & open;
                     const unsigned long long An = (yes & open & ~Out) | FA;
                     S = (open & ~(yes | no)) | Out;
-                    diff = (An ^ A) | (__ballot(nvn != nvi || dEn != dEi) & act);
+                    diff = (An ^ A) | changed;
                     A = An;
                     nvi = nvn;
                     dEi = dEn;
