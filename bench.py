@@ -54,12 +54,12 @@ LDS_BYTES_PER_ATTEMPT = 38
 LDS_PEAK_GBS = CU * 128 * CLOCK_HZ / 1e9
 # HBM bytes per k_sweep launch of the potts_q10_L32 workload in its timed (1/t)
 # phase, from rocprofv3 FETCH_SIZE and WRITE_SIZE runs scaled by a torch.neg
-# copy of known size (profiles/k_sweep_potts_q10_L32_pmc.md): 268.18 KiB x 2.000
-# + 390.0 KiB x 1.000.  Valid for the kernel as profiled.
-K_SWEEP_L32_HBM_BYTES = 948_600
-# VALU instructions (wave64) per attempt of the same kernel, rocprofv3 SQ_INSTS_VALU
-# over the same workload (same profile).
-K_SWEEP_L32_VALU_PER_ATTEMPT = 9.76
+# copy of known size: 304.25 KiB x 2.000 + 390.0 KiB x 1.000 at ln f = 2^-21
+# (profiles/cases_kernel_trace_pmc.md).  Valid for the kernel as profiled.
+K_SWEEP_L32_HBM_BYTES = 1_022_500
+# VALU instructions (wave64) per attempt of the same kernel, both wavefronts of a
+# walker, rocprofv3 SQ_INSTS_VALU at ln f = 2^-21 (profiles/cases_kernel_trace_pmc.md).
+K_SWEEP_L32_VALU_PER_ATTEMPT = 9.10
 # 1/t phase ends once W/t < 1e-8, i.e. after W/1e-8 attempts per walker.
 
 
@@ -372,15 +372,17 @@ TRIMER_FLOPS_PER_ATTEMPT = 2 * 191 * 5
 # minimum-image distance (3 mul + 2 add) to each of the 999 partners at the
 # old and the new position, and the Lennard-Jones / r^-9 term (1 div + 5
 # mul/add) of the ~52 partners inside the 2.5 cut-off at density 0.8, twice.
-# HBM bytes of one k_trimer_sweep launch of the trimer workload (64 walkers x
-# 20,000 attempts): FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (factors from a
-# 256 MiB torch.neg copy in the same program), 227.75 KiB and 308.0 KiB.
-TRIMER_SWEEP_HBM_BYTES = 781_800
+# HBM bytes of one k_trimer_sweep launch of the trimer workload: FETCH_SIZE x
+# 2.000 + WRITE_SIZE x 1.000 (factors from a 256 MiB torch.neg copy), 266.06 KiB
+# and 820.0 KiB, 512 of them two registers a thread saved at the kernel's start
+# (64 walkers; measured over 2,000 attempts, the rows go in and out once).
+TRIMER_SWEEP_HBM_BYTES = 1_384_600
 LIPID_FLOPS_PER_ATTEMPT = 2 * 999 * 5 + 2 * 52 * 6
-# HBM bytes of one k_lipid_sweep launch of the lipid workload (64 walkers x 2,000
-# attempts): FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (factors from a 256 MiB
-# torch.neg copy in the same program), 792.7 KiB and 1,302.0 KiB per launch.
-LIPID_SWEEP_HBM_BYTES = 2_956_600
+# HBM bytes of one k_lipid_sweep launch of the lipid workload: FETCH_SIZE x 2.000
+# + WRITE_SIZE x 1.000 (factors from a 256 MiB torch.neg copy), 711.5 KiB and
+# 2,326.0 KiB, 1,024 of them registers saved at the kernel's start (64 walkers;
+# measured over 1,000 attempts, the rows go in and out once).
+LIPID_SWEEP_HBM_BYTES = 3_839_000
 
 
 def trimer(args):
@@ -1150,7 +1152,7 @@ def main():
             raise RuntimeError("run converged inside a timed segment; the step count is not the work done")
         return el, sweep_ms / max(launches, 1), launches, sync_ms / max(syncs, 1)
 
-    # The first steps after walk-in (ln f = 1, every attempt on the exact serial path).
+    # The first steps after walk-in (ln f = 1, attempts decided from event to event).
     n_early = min(args.steps, 200)
     el, k_ms, _, _ = timed(n_early)
     early = {"steps": n_early, "attempts_per_s": nw * S * n_early / el, "k_sweep_avg_ms": k_ms,

@@ -26,7 +26,7 @@ namespace {
 // build compiles every call below to nothing.
 enum {
     kPcLaneCycles = 0,    // lane-parallel phase of a block (proposals, dE, conflicts)
-    kPcDecideCycles = 1,  // decision phase of a block (speculative or serial)
+    kPcDecideCycles = 1,  // decision phase of a block (guessing rounds or events)
     kPcSegments = 2,      // speculative segments
     kPcRounds = 3,        // speculative rounds
     kPcExact = 4,         // attempts through the exact (settling) path
