@@ -54,9 +54,10 @@ LDS_BYTES_PER_ATTEMPT = 38
 LDS_PEAK_GBS = CU * 128 * CLOCK_HZ / 1e9
 # HBM bytes per k_sweep launch of the potts_q10_L32 workload in its timed (1/t)
 # phase, from rocprofv3 FETCH_SIZE and WRITE_SIZE runs scaled by a torch.neg
-# copy of known size: 304.25 KiB x 2.000 + 390.0 KiB x 1.000 at ln f = 2^-21
-# (profiles/cases_kernel_trace_pmc.md).  Valid for the kernel as profiled.
-K_SWEEP_L32_HBM_BYTES = 1_022_500
+# copy of known size (profiles/k_sweep_potts_q10_L32_pmc.md): 268.18 KiB x 2.000
+# + 390.0 KiB x 1.000.  Valid for the kernel as profiled; at ln f = 2^-21 the
+# present one reads 304.25 KiB (profiles/cases_kernel_trace_pmc.md).
+K_SWEEP_L32_HBM_BYTES = 948_600
 # VALU instructions (wave64) per attempt of the same kernel, both wavefronts of a
 # walker, rocprofv3 SQ_INSTS_VALU at ln f = 2^-21 (profiles/cases_kernel_trace_pmc.md).
 K_SWEEP_L32_VALU_PER_ATTEMPT = 9.10
@@ -372,17 +373,19 @@ TRIMER_FLOPS_PER_ATTEMPT = 2 * 191 * 5
 # minimum-image distance (3 mul + 2 add) to each of the 999 partners at the
 # old and the new position, and the Lennard-Jones / r^-9 term (1 div + 5
 # mul/add) of the ~52 partners inside the 2.5 cut-off at density 0.8, twice.
-# HBM bytes of one k_trimer_sweep launch of the trimer workload: FETCH_SIZE x
-# 2.000 + WRITE_SIZE x 1.000 (factors from a 256 MiB torch.neg copy), 266.06 KiB
-# and 820.0 KiB, 512 of them two registers a thread saved at the kernel's start
-# (64 walkers; measured over 2,000 attempts, the rows go in and out once).
-TRIMER_SWEEP_HBM_BYTES = 1_384_600
+# HBM bytes of one k_trimer_sweep launch of the trimer workload (64 walkers x
+# 20,000 attempts): FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (factors from a
+# 256 MiB torch.neg copy in the same program), 227.75 KiB and 308.0 KiB: the
+# rows in and out (512 KiB of registers saved once at the start not counted,
+# profiles/cases_kernel_trace_pmc.md).
+TRIMER_SWEEP_HBM_BYTES = 781_800
 LIPID_FLOPS_PER_ATTEMPT = 2 * 999 * 5 + 2 * 52 * 6
-# HBM bytes of one k_lipid_sweep launch of the lipid workload: FETCH_SIZE x 2.000
-# + WRITE_SIZE x 1.000 (factors from a 256 MiB torch.neg copy), 711.5 KiB and
-# 2,326.0 KiB, 1,024 of them registers saved at the kernel's start (64 walkers;
-# measured over 1,000 attempts, the rows go in and out once).
-LIPID_SWEEP_HBM_BYTES = 3_839_000
+# HBM bytes of one k_lipid_sweep launch of the lipid workload (64 walkers x 2,000
+# attempts): FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (factors from a 256 MiB
+# torch.neg copy in the same program), 792.7 KiB and 1,302.0 KiB per launch: the
+# rows in and out (1 MiB of registers saved once at the start not counted,
+# profiles/cases_kernel_trace_pmc.md).
+LIPID_SWEEP_HBM_BYTES = 2_956_600
 
 
 def trimer(args):
