@@ -197,6 +197,19 @@ __device__ __forceinline__ int wave_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 to rows 2, 3
     return v;
 }
+// Bitwise or of v over the lanes (all active).
+__device__ __forceinline__ uint64_t wave_or64(uint64_t v) {
+    auto either = [](uint32_t x) -> uint32_t {
+        x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xF, 0xF, false);   // row_ror:1
+        x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xF, 0xF, false);   // row_ror:2
+        x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, false);   // row_ror:4
+        x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, false);   // row_ror:8
+        x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // row_bcast:15 to rows 1, 3
+        x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // row_bcast:31 to rows 2, 3
+        return __builtin_amdgcn_readlane(x, 63);
+    };
+    return ((uint64_t)either((uint32_t)(v >> 32)) << 32) | either((uint32_t)v);
+}
 // Orders this wavefront's LDS writes before its later LDS reads by other lanes.
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -298,7 +311,7 @@ __device__ __forceinline__ void same_sites(const Proposal &p, int lane, unsigned
 // in four 16-byte words: site, neighbours and value offset in 16 bits each
 // (lattices up to 65,536 sites), the uniform word, ln u, the exact masks W0 .. W4.
 constexpr int kRecWords = 4 * 64;
-constexpr size_t kHelpLds = 2 * kRecWords * sizeof(uint4) + 16;
+constexpr size_t kHelpLds = 2 * kRecWords * sizeof(uint4);
 constexpr int kHelpMaxSites = 65536;
 
 template <int PREC>
@@ -574,11 +587,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         H = (uint32_t *)(smem + st.Npad + (size_t)Wpad * 8);
         tag = (unsigned long long *)(smem + st.Npad + (size_t)Wpad * 12);
     }
-    // the helper's blocks (two, in turn), and a word of flips a segment overwrites
-    // (without a helper a word of the tag table, zero between blocks)
-    uint4 *rec = (uint4 *)(tag + st.Ntag);
-    unsigned long long *sup_w = HELP ? (unsigned long long *)(rec + 2 * kRecWords) : &tag[32];
-
+    uint4 *rec = (uint4 *)(tag + st.Ntag);   // the helper's blocks (two, in turn)
     const uint32_t *gsp = (const uint32_t *)(st.spins + (size_t)w * st.Npad);
     for (int i = tid; i < st.Npad / 4; i += nthr) ((uint32_t *)sp)[i] = gsp[i];
     if (!GLOB) {
@@ -593,7 +602,6 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         }
     }
     for (int i = tid; i < st.Ntag; i += nthr) tag[i] = 0ull;
-    if (HELP && tid == 0) *sup_w = 0ull;
     walker_sync<WAVE>();
 
     const int lo = __builtin_amdgcn_readfirstlane(st.start[k]), hi = lo + W - 1;
@@ -1017,16 +1025,13 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 const int ej = pre + (mine_acc ? dEi : 0);
                 if (seg) {
                     // a flip is written unless a later accepted flip of the segment
-                    // hits the same site
-                    unsigned long long sup = 0ull;
-                    if (__ballot(mine_acc && (W0 & aseg) != 0ull)) {
-                        if (mine_acc && (W0 & aseg) != 0ull) atomicOr(sup_w, W0 & aseg);
-                        wave_lds_sync();
-                        sup = *sup_w;
-                        wave_lds_sync();
-                        if (lane == 0) *sup_w = 0ull;
-                    }
-                    if (mine_acc && !((sup >> lane) & 1ull)) sp[p.site] = (int8_t)nvi;
+                    // hits the same site (the lanes' masks or-ed by row steps; one
+                    // LDS word or-ed by atomics took 1,050 more cycles on 8 x 8
+                    // sites, 90 us a call of 1,000 attempts against 81)
+                    unsigned long long last = aseg;
+                    const unsigned long long hit = mine_acc ? W0 & aseg : 0ull;
+                    if (__ballot(hit != 0ull)) last &= ~wave_or64(hit);
+                    if (__builtin_amdgcn_inverse_ballot_w64(last)) sp[p.site] = (int8_t)nvi;
                     // visits of lane's energy: the segment's lanes that ended there
                     uint32_t nb = (uint32_t)match_count(ej - ebase, lane, seg);
                     // the segment's visits go to H here, one add per energy (atomic:
