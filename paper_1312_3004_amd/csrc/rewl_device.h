@@ -304,7 +304,7 @@ __device__ __forceinline__ bool accept32(float d, uint32_t r) {
 
 // ln g(E) += ln f on a binary32 (hi, lo) pair by Knuth's TwoSum: the rounding
 // error of the high part is carried into the low part.
-__device__ __forceinline__ void two_sum_add(float &hi, float &lo, float x) {
+__host__ __device__ __forceinline__ void two_sum_add(float &hi, float &lo, float x) {
 #pragma clang fp contract(off)
     const float s = hi + x;
     const float bb = s - hi;

@@ -14,7 +14,7 @@
 // attempts in parallel and then walk through them in order.
 #include <type_traits>
 
-#include "rewl_device.h"
+#include "rewl_replay.h"
 
 namespace rewl_gpu {
 
@@ -244,31 +244,6 @@ __device__ __forceinline__ int match_count(int value, int v, unsigned long long 
         hi &= ~((uint32_t)(bits >> 32) ^ s);
     }
     return __builtin_popcount(lo) + __builtin_popcount(hi);
-}
-
-// Whether x and y are multiples of the binary32 spacing at magnitude m > 0
-// (normal range); sums and differences of theirs up to m are then exact.
-__device__ __forceinline__ bool on_grid32(double m, double x, double y) {
-#pragma clang fp contract(off)
-    int e;
-    (void)__builtin_frexp(m, &e);              // m < 2^e: spacing 2^(e - 24)
-    const double fx = __builtin_ldexp(x, 24 - e), fy = __builtin_ldexp(y, 24 - e);
-    return m > 0x1p-100 && m < 0x1p100 && __builtin_rint(fx) == fx && __builtin_rint(fy) == fy;
-}
-
-// How many of n further adds of l to x (itself the result of such an add) are
-// known to move it by the constant step (x + l) - x: those that stay inside
-// x's binade, counted four short; all of them if the step is zero.
-__device__ __forceinline__ uint32_t low_word_steps(float x, float l, uint32_t n) {
-#pragma clang fp contract(off)
-    const float d = (x + l) - x;
-    if (d == 0.0f) return n;
-    if (!(x > 0x1p-100f && x < 0x1p100f && d > 0.0f)) return 0u;
-    int e;
-    (void)__builtin_frexpf(x, &e);             // x < 2^e
-    const float room = (__builtin_ldexpf(1.0f, e) - x) / d - 4.0f;
-    const uint32_t k = room >= 64.0f ? 64u : (room >= 1.0f ? (uint32_t)room : 0u);
-    return k < n ? k : n;
 }
 
 // Earlier proposals of a block on the same (hashed) site as this lane's site
@@ -1037,56 +1012,15 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                     // the segment's visits go to H here, one add per energy (atomic:
                     // a later block may add to the bin from another lane)
                     if (nb != 0u) atomicAdd(&H[ebase + lane - lo], nb);
-                    if (PREC == 0 && nb != 0u) {
-                        // n sequential adds of ln f in closed form: after the first
-                        // add, every add moves x by the same exact step d2 while x
-                        // stays in one binade (also when the adds round half-way:
-                        // the parity that decides a tie is then fixed), so
-                        // x_n = x_1 + (n - 1) d2 exactly; otherwise the loop below
-                        const double x1 = c64 + lnf_v;
-                        const double d2 = (x1 + lnf_v) - x1;
-                        const double xn = x1 + (double)(nb - 1u) * d2, z = xn + 4.0 * lnf_v;
-                        const bool binade = (((uint32_t)((uint64_t)__double_as_longlong(x1) >> 32) ^
-                                              (uint32_t)((uint64_t)__double_as_longlong(z) >> 32)) >> 20) == 0u;
-                        if (d2 * 64.0 <= x1 && binade) {
-                            c64 = xn;
-                            nb = 0u;
-                        }
-                    }
                     if (PREC == 0) {
+                        if (nb != 0u && replay_binary64(c64, lnf_v, nb)) nb = 0u;
                         while (__ballot(nb != 0u)) {
                             const double x = c64 + lnf_v;
                             c64 = nb != 0u ? x : c64;
                             nb = nb != 0u ? nb - 1u : 0u;
                         }
                     } else {
-                        // n adds that round nowhere, all sums being multiples of the
-                        // binary32 spacing at the largest of them: in the high word
-                        // the low word then stays; where the high word ignores ln f
-                        // TwoSum hands it to the low word, which takes them all
-                        const bool low = ch + lnf32 == ch;
-                        if (nb != 0u) {
-                            const double l = (double)lnf32, sh = (double)ch + (double)nb * l, sl = (double)cl + (double)nb * l;
-                            if (on_grid32(fmax(fabs((double)ch), fabs(sh)), (double)ch, l)) {
-                                ch = (float)sh;
-                                nb = 0u;
-                            } else if (low && on_grid32(fmax(fabs((double)cl), fabs(sl)), (double)cl, l)) {
-                                cl = (float)sl;
-                                nb = 0u;
-                            }
-                        }
-                        // otherwise one add, then in the low word as many of its
-                        // constant steps (see above) as its binade holds
-                        while (__ballot(nb != 0u)) {
-                            float xh = ch, xl = cl;
-                            two_sum_add(xh, xl, lnf32);
-                            ch = nb != 0u ? xh : ch;
-                            cl = nb != 0u ? xl : cl;
-                            nb = nb != 0u ? nb - 1u : 0u;
-                            const uint32_t skip = low ? low_word_steps(cl, lnf32, nb) : 0u;
-                            cl = (float)((double)cl + (double)skip * (double)((cl + lnf32) - cl));
-                            nb -= skip;
-                        }
+                        replay_pair(ch, cl, lnf32, nb, [](bool more) { return __ballot(more) != 0ull; });
                     }
                     erel = __builtin_amdgcn_readlane(ej, c - 1) - ebase;
                 }

@@ -29,3 +29,24 @@ def rocrand_ref():
                        check=True, capture_output=True)
         os.replace(exe + ".tmp", exe)
     return exe
+
+
+@pytest.fixture(scope="session")
+def kernel_arith():
+    """Host build of arithmetic from the kernels' headers, as a ctypes library."""
+    import ctypes
+    import glob
+
+    src = os.path.join(ROOT, "tests", "helpers", "kernel_arith.cpp")
+    heads = glob.glob(os.path.join(ROOT, "paper_1312_3004_amd", "csrc", "*.h"))
+    out_dir = os.path.join(ROOT, "tests", "_build")
+    os.makedirs(out_dir, exist_ok=True)
+    lib = os.path.join(out_dir, "kernel_arith.so")
+    if not os.path.exists(lib) or os.path.getmtime(lib) < max(os.path.getmtime(p) for p in [src] + heads):
+        hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+        if not os.path.exists(hipcc):
+            pytest.skip("hipcc not available to build the kernels' headers for the host")
+        subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-O2", "-std=c++17", "-ffp-contract=off", "-fPIC",
+                        "-shared", src, "-o", lib + ".tmp"], check=True, capture_output=True)
+        os.replace(lib + ".tmp", lib)
+    return ctypes.CDLL(lib)

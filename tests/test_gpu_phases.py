@@ -54,3 +54,17 @@ def test_exchange_and_flatness_over_walkers_per_window(m):
     g.run(6000)
     o.run(6000)
     assert_same_state(g, o)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_lnf_of_the_one_over_t_schedule_bitexact(precision):
+    # ln f = W/t has a full significand; weights as a long run leaves them
+    g, o = make_pair(8, 10, 4, 8, lnf_init=461 / 1.6e9, fixed_lnf=1, sync_attempts=4000, precision=precision, seed=37)
+    rng = np.random.default_rng(37)
+    for w in range(32):
+        lng = rng.uniform(50.0, 3000.0) + np.cumsum(rng.uniform(-0.5, 0.7, g.W))
+        g.set_lng(w, lng)
+        o.set_lng(w, lng)
+    g.run(60_000)
+    o.run(60_000)
+    assert_same_state(g, o)
