@@ -14,6 +14,7 @@
 // attempts in parallel and then walk through them in order.
 #include <type_traits>
 
+#include "rewl_handover.h"
 #include "rewl_replay.h"
 
 namespace rewl_gpu {
@@ -587,18 +588,11 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     int E = __builtin_amdgcn_readfirstlane(st.E[w]);
     if (E < lo || E > hi) return;  // not walked in: leave the walker untouched
     if (HELP && threadIdx.x >= 64) {
-        // barrier i: blocks 0 .. i + 1 are drawn and block i has been read, so that
-        // the next one goes to its place
         auto draw = [&](int64_t base) {
             const int todo = (int)((n - base) < 64 ? (n - base) : 64);
-            if (todo > 0)
-                draw_block<PREC>(st, w, (uint64_t)(s0 + base), todo, tag, rec + ((base >> 6) & 1) * kRecWords, lane);
+            draw_block<PREC>(st, w, (uint64_t)(s0 + base), todo, tag, rec + handover_slot(base) * kRecWords, lane);
         };
-        draw(0);
-        for (int64_t base = 0; base < n; base += 64) {
-            draw(base + 64);
-            __syncthreads();
-        }
+        handover_draw(n, draw, [] { __syncthreads(); });
     } else {
     // ln g cache: lane b holds energy ebase + b (+inf outside the window)
     int ebase = E - 32;
@@ -655,19 +649,19 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
     // with a helper: the next block's record, read while the block before runs
     uint4 rn0{}, rn1{}, rn2{}, rn3{};
     auto fetch = [&](int64_t base) {
-        const uint4 *rb = rec + ((base >> 6) & 1) * kRecWords + lane;
+        const uint4 *rb = rec + handover_slot(base) * kRecWords + lane;
         rn0 = rb[0];
         rn1 = rb[64];
         rn2 = rb[128];
         rn3 = rb[192];
     };
     PhaseClock pc;
+    long long pc0 = 0;   // start of a block
 
     // one loop for each decision phase, so that neither carries the other's registers
     auto blocks = [&](auto phase) {
     constexpr bool kSpec = decltype(phase)::value;
-    for (int64_t base = 0; base < n; base += 64) {
-        const long long pc0 = pc.now();
+    auto block = [&](int64_t base) {
         const int todo = (int)((n - base) < 64 ? (n - base) : 64);
         const bool live = lane < todo;
         if ((unsigned)(erel - 16) >= 32u) {   // keep the walker near the cache centre
@@ -683,8 +677,6 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         double lnu;
         unsigned long long W0, W1, W2, W3, W4;
         if constexpr (HELP) {
-            __syncthreads();
-            if (base == 0) fetch(0);
             const uint4 r0 = rn0, r1 = rn1, r2 = rn2, r3 = rn3;
             p.site = (int)(r0.x & 0xffffu);
             p.nb0 = (int)(r0.x >> 16);
@@ -706,7 +698,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         }
         // spins of the site and its neighbours at block start
         int x0 = sp[p.site], x1 = sp[p.nb0], x2 = sp[p.nb1], x3 = sp[p.nb2], x4 = sp[p.nb3];
-        if constexpr (HELP) fetch(base + 64);   // (past the end: old words, not used)
+        if constexpr (HELP) fetch(base + 64);
         int nv = x0 + 1 + p.off;
         if (nv >= q) nv -= q;
         int dE = (int)(x0 == x1) + (int)(x0 == x2) + (int)(x0 == x3) + (int)(x0 == x4) - (int)(nv == x1) -
@@ -1292,6 +1284,14 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
         pc.add(kPcDecideCycles, pcd - pc1);
         pc.add(kPcBlocks, 1);
         pc.add(kPcAttempts, todo);
+    };
+    if constexpr (HELP) {
+        handover_decide(n, fetch, [&] { pc0 = pc.now(); __syncthreads(); }, block);
+    } else {
+        for (int64_t base = 0; base < n; base += 64) {
+            pc0 = pc.now();
+            block(base);
+        }
     }
     };
     if (spec) blocks(std::true_type{});
