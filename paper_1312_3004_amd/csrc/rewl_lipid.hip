@@ -511,7 +511,7 @@ struct LipidMoves {
             // list, evaluated 32 partners x (new, old) per pass.
             int64_t acc = 0;
             bool bad = false;
-            const uint32_t lim = move_grid_limit(2.5f + 1e-3f + box * 1e-6f, scale);
+            const uint32_t lim = move_grid_limit(2.5f + move_slack(box), scale);
             for (int task = wave; task < 16; task += nwave) {
                 const int i = task & 3;
                 const int ci = p.c[0] * (i == 0) + p.c[1] * (i == 1) + p.c[2] * (i == 2) + p.c[3] * (i == 3);

@@ -73,7 +73,7 @@ struct MoveGrid {
     uint32_t xy, z;
 };
 typedef short move_s2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ MoveGrid move_grid(const float *x, float scale) {
+__host__ __device__ __forceinline__ MoveGrid move_grid(const float *x, float scale) {
     MoveGrid g;
     g.xy = ((uint32_t)(x[0] * scale) & 0xffffu) | ((uint32_t)(x[1] * scale) << 16);
     g.z = (uint32_t)(x[2] * scale) & 0xffffu;
@@ -85,27 +85,36 @@ __device__ __forceinline__ uint32_t move_grid2(MoveGrid a, MoveGrid b) {
     const move_s2 dz = __builtin_bit_cast(move_s2, a.z) - __builtin_bit_cast(move_s2, b.z);
     return (uint32_t)__builtin_amdgcn_sdot2(dz, dz, __builtin_amdgcn_sdot2(dxy, dxy, 0, false), false);
 }
-// Square of a radius in grid units, rounded up by the grid's own error (below
-// one unit per axis and end, so 1.8 units of distance).
-__device__ __forceinline__ uint32_t move_grid_limit(float r, float scale) {
-    const float u = r * scale + 2.0f;
+// Square of a radius in grid units that no pair within the radius exceeds: the
+// places are rounded down, which moves a difference by less than a unit an axis
+// and a distance by less than sqrt(3) = 1.732; the binary32 products add less
+// than 0.02, and the conversion drops less than 1.
+__host__ __device__ __forceinline__ uint32_t move_grid_limit(float r, float scale) {
+    const float u = r * scale + 3.0f;
     const uint32_t v = u < 65535.0f ? (uint32_t)u : 65535u;
     return v * v;
 }
 
 // b - a moved by -+box when beyond +-box/2, in binary32.
-__device__ __forceinline__ double move_image(float a, float b, float box, float half) {
+__host__ __device__ __forceinline__ double move_image(float a, float b, float box, float half) {
 #pragma clang fp contract(off)
     const float x = b - a;
     const float y = x - __builtin_copysignf(box, x);
     return (double)(fabsf(x) > half ? y : x);
 }
-__device__ __forceinline__ double move_r2(const float *a, const float *b, float box, float half) {
+__host__ __device__ __forceinline__ double move_r2(const float *a, const float *b, float box, float half) {
 #pragma clang fp contract(off)
     const double dx = move_image(a[0], b[0], box, half);
     const double dy = move_image(a[1], b[1], box, half);
     const double dz = move_image(a[2], b[2], box, half);
     return (dx * dx + dy * dy) + dz * dz;
+}
+
+// Binary32 rounding of places and distances, a few units of box 2^-24, and more.
+__host__ __device__ __forceinline__ float move_slack(float box) { return 1e-3f + box * 1e-6f; }
+// Distance between the old and the new place of a displacement, with slack.
+__host__ __device__ __forceinline__ float move_reach(float d0, float d1, float d2, float box) {
+    return __builtin_sqrtf(d0 * d0 + d1 * d1 + d2 * d2) + move_slack(box);
 }
 
 // LDS behind the walker's state, ln g and H: block header, rows, proposals,
@@ -176,11 +185,11 @@ __device__ __forceinline__ uint32_t move_perm(uint32_t v, int l) {
 }
 
 // Displacement of one axis: 0.1 (2u - 1), u a 23-bit uniform; periodic wrap.
-__device__ __forceinline__ float move_disp(uint32_t r) {
+__host__ __device__ __forceinline__ float move_disp(uint32_t r) {
 #pragma clang fp contract(off)
     return 0.1f * ((float)(r >> 9) * 0x1p-22f - 1.0f);
 }
-__device__ __forceinline__ float move_wrap(float v, float box) {
+__host__ __device__ __forceinline__ float move_wrap(float v, float box) {
 #pragma clang fp contract(off)
     if (v < 0.0f) v = v + box;
     if (v >= box) v = v - box;
@@ -379,8 +388,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
                     MoveProp p;
                     p.n[0] = nx; p.n[1] = ny; p.n[2] = nz;
                     p.o[0] = o0; p.o[1] = o1; p.o[2] = o2;
-                    // binary32 rounding of places and distances: a few units of box 2^-24
-                    p.reach = __builtin_sqrtf(d0 * d0 + d1 * d1 + d2 * d2) + 1e-3f + box * 1e-6f;
+                    p.reach = move_reach(d0, d1, d2, box);
                     p.b = bead;
                     props[lane] = p;
                 }

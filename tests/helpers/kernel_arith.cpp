@@ -1,7 +1,21 @@
 // Host build of arithmetic that the kernels take from their headers, for CPU
 // tests: each function applies the header's own code to arrays of inputs.
 #include "../../paper_1312_3004_amd/csrc/rewl_handover.h"
+#include "../../paper_1312_3004_amd/csrc/rewl_moves.h"
 #include "../../paper_1312_3004_amd/csrc/rewl_replay.h"
+
+namespace {
+
+// Squared distance on the 16-bit grid, as the kernels' dot products of 16-bit
+// differences give it.
+uint32_t grid2(rewl_gpu::MoveGrid a, rewl_gpu::MoveGrid b)
+{
+    auto d = [](uint32_t x, uint32_t y) { return (int32_t)(int16_t)(uint16_t)(x - y); };
+    auto sq = [](int32_t v) { return (uint32_t)(v * v); };
+    return sq(d(a.xy & 0xffffu, b.xy & 0xffffu)) + sq(d(a.xy >> 16, b.xy >> 16)) + sq(d(a.z, b.z));
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -50,6 +64,38 @@ void handover_trace(int64_t n, size_t max, int64_t *written, int64_t *read, int6
     out[1] = got;
     out[2] = wsync;
     out[3] = rsync;
+}
+
+// The partner screens.  Bead i moves from o[i] by the displacement of the words
+// r[i] and the partner is at q[i] (3 numbers a place, in [0, box)).  Bits of
+// kept[i]: 0 / 1 the partner is within the cut-off of the old / new place,
+// 2 the screen of a displacement keeps it, 3 that of a reptation (old place)
+// keeps it, 4 the correction test of two displacements (the partner moves too,
+// by the words r2[i]) holds, 5 the moved partner is within the cut-off of
+// either place of the bead.
+void screen_all(size_t count, const float *o, const uint32_t *r, const float *q, const uint32_t *r2, float box,
+                uint8_t *kept)
+{
+    using namespace rewl_gpu;
+    const float scale = 65536.0f / box, half = 0.5f * box;
+    for (size_t i = 0; i < count; ++i) {
+        const float *a = o + 3 * i, *b = q + 3 * i;
+        float d[3], e[3], n[3], m[3];
+        for (int c = 0; c < 3; ++c) {
+            d[c] = move_disp(r[3 * i + c]);
+            e[c] = move_disp(r2[3 * i + c]);
+            n[c] = move_wrap(a[c] + d[c], box);
+            m[c] = move_wrap(b[c] + e[c], box);
+        }
+        const float reach = move_reach(d[0], d[1], d[2], box), reach2 = move_reach(e[0], e[1], e[2], box);
+        const uint32_t g = grid2(move_grid(b, scale), move_grid(a, scale));
+        const double cut2 = 6.25;
+        kept[i] = (uint8_t)((move_r2(a, b, box, half) < cut2) | (move_r2(n, b, box, half) < cut2) << 1 |
+                            (g <= move_grid_limit(2.5f + reach, scale)) << 2 |
+                            (g <= move_grid_limit(2.5f + move_slack(box), scale)) << 3 |
+                            (g <= move_grid_limit(2.5f + reach + reach2, scale)) << 4 |
+                            (move_r2(a, m, box, half) < cut2 || move_r2(n, m, box, half) < cut2) << 5);
+    }
 }
 
 }

@@ -89,3 +89,35 @@ def test_widest_bins_of_the_quick_decisions(bin_w, precision):
     o.run(900)
     assert_same_state(g, o)
     assert_same_energies(g, o)
+
+
+@pytest.mark.parametrize("box", [250.0, 1000.0])
+def test_droplets_in_large_boxes(box):
+    # a dense cluster in the middle of a box a hundred times its size: places
+    # 0.004 and 0.015 apart on the screens' 16-bit grid
+    import paper_1312_3004_amd as pk
+
+    x = workloads.init_trimers(64, 10.0, 3, 2).reshape(3, 64, 3, 3).astype(np.float64)
+    for b in (1, 2):                                   # molecules in one piece
+        d = x[:, :, b] - x[:, :, b - 1]
+        x[:, :, b] -= 10.0 * np.rint(d / 10.0)
+    x = (x.reshape(3, 192, 3) + box / 2).astype(np.float32)
+    opts = dict(lnf_init=0.05, fixed_lnf=1, sync_attempts=499, seed=9)
+    args = (64, box, -300.0, 0.5, 2400, 1, 0.75, 3, x)
+    print(f"[case] droplet of 64 trimers, box {box}", flush=True)
+    g, o = pk.Rewl.trimer(*args, **opts), oracle.Rewl.trimer(*args, threads=8, **opts)
+    g.run(4000)
+    o.run(4000)
+    assert_same_state(g, o)
+    assert_same_energies(g, o)
+
+    x = workloads.init_lipids(6, 106, 5.0, 3, 2).astype(np.float64)
+    x = (np.where(x > 4.5, x - 5.0, x) + box / 2).astype(np.float32)
+    start = oracle.Rewl.lipid(6, 106, box, 0.0, 1.0, 100, 1, 0.75, 3, x, rep_prob=0.4)
+    e = [start.energy(w) for w in range(3)]
+    args = (6, 106, box, min(e) - 200.0, 0.5, int(2 * (max(e) - min(e) + 400.0)), 1, 0.75, 3, x)
+    g, o = pk.Rewl.lipid(*args, rep_prob=0.4, **opts), oracle.Rewl.lipid(*args, rep_prob=0.4, threads=8, **opts)
+    g.run(3000)
+    o.run(3000)
+    assert_same_state(g, o)
+    assert_same_lipids(g, o)
