@@ -120,7 +120,7 @@ __host__ __device__ __forceinline__ float move_reach(float d0, float d1, float d
 // LDS behind the walker's state, ln g and H: block header, rows, proposals,
 // correction table and lists of `waves` wavefronts.
 __host__ __device__ inline size_t move_lds_bytes(int waves) {
-    return (size_t)waves * (sizeof(MoveRow) + sizeof(MoveProp) + (size_t)waves * 8 + kMoveList * 2) + 64;
+    return (size_t)waves * (sizeof(MoveRow) + sizeof(MoveProp) + kMoveMaxWaves * 8 + kMoveList * 2) + 64;
 }
 // Workgroup of a walker: 16 wavefronts and the 16-bit places (8 bytes a
 // particle) where they fit the LDS beside `used` bytes (state, ln g, H, the
@@ -200,7 +200,7 @@ __host__ __device__ __forceinline__ float move_wrap(float v, float box) {
 // block-start configuration and its corrections for the attempts before it.
 template <class Model>
 __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &md, const MoveProp *props, int l,
-                                              int waves, MoveRow *rows, int64_t *tab, uint16_t *list, int lane) {
+                                              MoveRow *rows, int64_t *tab, uint16_t *list, int lane) {
 #pragma clang fp contract(off)
     const float box = st.box;
     const MoveProp p = props[l];
@@ -282,7 +282,7 @@ __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &m
         c += __shfl_xor(c, 16, 64);
         c += __shfl_xor(c, 32, 64);
     }
-    if (lane < l) tab[l * waves + lane] = c;
+    if (lane < l) tab[l * kMoveMaxWaves + lane] = c;
     const unsigned long long badm = __ballot(bad);
     const int64_t de = wave_sum64(acc);
     // the lanes' overlap counts (new places only can have one)
@@ -297,6 +297,21 @@ __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &m
         r.pad = 0;
         rows[l] = r;
     }
+}
+
+// Lane `lane`'s corrections for attempts 0 .. 15 of a block (those for itself
+// and later ones, and of lanes past the block, are never looked at).  The table
+// has 16 entries a row and `waves` rows: every read stays inside it, at offsets
+// that are known beforehand (rows of `waves` entries, read to their end alone,
+// take 4% longer on 64 trimers).
+typedef long long move_l16 __attribute__((ext_vector_type(16)));
+template <class Table>
+__host__ __device__ __forceinline__ move_l16 move_corrections(Table tab, int lane, int waves) {
+    const int row = (lane < waves ? lane : waves - 1) * kMoveMaxWaves;
+    move_l16 corr;
+#pragma unroll
+    for (int r = 0; r < kMoveMaxWaves; ++r) corr[r] = tab[row + r];
+    return corr;
 }
 
 // Attempts s0 .. s0+n-1 of walker w (Sec. 2): propose, reject a new bin
@@ -314,7 +329,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
     MoveRow *rows = (MoveRow *)mv;
     MoveProp *props = (MoveProp *)(rows + waves);
     int64_t *tab = (int64_t *)(props + waves);
-    uint32_t *head = (uint32_t *)(tab + waves * waves);   // [16]: attempts of the block, kind, words
+    uint32_t *head = (uint32_t *)(tab + waves * kMoveMaxWaves);   // [16]: attempts of the block, kind, words
     uint16_t *list = (uint16_t *)(head + 16) + wave * kMoveList;
 
     const int k = w / st.m;
@@ -407,7 +422,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
             t += 1;
             continue;
         }
-        if (wave < cur) move_evaluate(st, md, props, wave, waves, rows, tab, list, lane);
+        if (wave < cur) move_evaluate(st, md, props, wave, rows, tab, list, lane);
         __syncthreads();
         if (wave != 0) {
             continue;
@@ -456,13 +471,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
         // to it take the paid value.
         const bool plain = st.binw_fx <= ((int64_t)1 << 44) && !__ballot(over != 0 || bad != 0u);
         if (plain) {
-            // the lane's corrections for attempts 0 .. 15 (those for itself and
-            // later ones, and of lanes past the block, are never looked at)
-            typedef long long move_l16 __attribute__((ext_vector_type(16)));
-            move_l16 corr;
-            const int64_t *row = tab + (lane < waves ? lane : waves - 1) * waves;
-#pragma unroll
-            for (int r = 0; r < kMoveMaxWaves; ++r) corr[r] = row[r];
+            const move_l16 corr = move_corrections((const int64_t *)tab, lane, waves);
             const double slope = PREC == 0 ? lnf : (double)lnf32;
             const double ls = (double)lane * slope, A = ls - lnu;
             // t is off by at most 64 roundings of values up to |ln g| + 64 ln f + |ln u|
@@ -598,7 +607,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
                 bE = bj;
                 hist = lane >= j ? bj : hist;
                 accm |= 1u << j;
-                if (mine && lane > j) tot += tab[lane * waves + j];   // the correction for attempt j
+                if (mine && lane > j) tot += tab[lane * kMoveMaxWaves + j];   // the correction for attempt j
             }
             add_lnf(1);
             i = j + 1;

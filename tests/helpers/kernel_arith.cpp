@@ -98,4 +98,20 @@ void screen_all(size_t count, const float *o, const uint32_t *r, const float *q,
     }
 }
 
+// Entry r of the corrections that `lane` of a workgroup of `waves` wavefronts
+// reads, from a table whose entry i is i + 1; *last: the furthest entry read.
+int64_t correction_read(int lane, int waves, int r, int64_t *last)
+{
+    struct Table {
+        int64_t *last;
+        int64_t operator[](int i) const
+        {
+            if (i > *last) *last = i;
+            return i + 1;
+        }
+    };
+    *last = -1;
+    return rewl_gpu::move_corrections(Table{last}, lane, waves)[r];
+}
+
 }

@@ -40,3 +40,15 @@ def test_no_partner_within_the_cut_off_is_screened_out(kernel_arith, box):
     assert not np.any((near_old | near_new) & ~kept), box
     assert not np.any(near_old & ~kept_rep), box
     assert not np.any((near_old | near_new | near_moved) & ~close), box
+
+
+@pytest.mark.parametrize("waves", [1, 2, 4, 8, 16])
+def test_corrections_are_read_inside_their_table(kernel_arith, waves):
+    last = ctypes.c_int64()
+    kernel_arith.correction_read.restype = ctypes.c_int64
+    for lane in range(64):
+        for r in range(16):
+            v = kernel_arith.correction_read(lane, waves, r, ctypes.byref(last))
+            assert last.value < 16 * waves
+            if lane < waves:
+                assert v == 16 * lane + r + 1
