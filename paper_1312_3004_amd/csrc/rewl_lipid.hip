@@ -643,7 +643,7 @@ hipError_t lip_allow(const void *fn, size_t bytes) {
 }  // namespace
 
 static MovePlan lipid_plan(const DevState &st) {
-    return move_plan((size_t)st.Npad + (size_t)st.Wpad * 12 + lip_rep_bytes((st.nb + 63) / 64), kLipRepPerWave, st.nb);
+    return move_plan((size_t)st.Npad + (size_t)st.Wpad * 12 + lip_rep_bytes((st.nb + 63) / 64), kLipRepPerWave, st.nb, st.nw);
 }
 size_t lipid_sweep_lds_bytes(const DevState &st) { return lipid_plan(st).lds; }
 size_t lipid_walkin_lds_bytes(const DevState &st) { return (size_t)st.Npad + (size_t)st.Bpad * 4; }

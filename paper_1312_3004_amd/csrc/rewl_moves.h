@@ -122,21 +122,45 @@ __host__ __device__ __forceinline__ float move_reach(float d0, float d1, float d
 __host__ __device__ inline size_t move_lds_bytes(int waves) {
     return (size_t)waves * (sizeof(MoveRow) + sizeof(MoveProp) + kMoveMaxWaves * 8 + kMoveList * 2) + 64;
 }
-// Workgroup of a walker: 16 wavefronts and the 16-bit places (8 bytes a
-// particle) where they fit the LDS beside `used` bytes (state, ln g, H, the
-// model's own) and `per_wave` more of the model for each wavefront; else the
-// places are taken from the coordinates each time (three conversions more per
-// partner), and then the largest power of two of wavefronts that fits.
+// Workgroup of a walker beside `used` bytes of LDS (state, ln g, H, the model's
+// own) and `per_wave` more of the model for each wavefront.
+//
+// Sixteen wavefronts are fastest for one walker a CU of 64 particles or more
+// and fill the CU's registers.  Fewer where they would do less or wait longer:
+// * blocks of few particles end early, on a particle that has moved;
+// * several walkers a CU run side by side, and one decides while another
+//   evaluates, if they have 16 wavefronts between them and the LDS holds them.
+// us per 1,000 attempts of every walker (300 for the lipids) with 16, 8, 4, 2
+// wavefronts, and with 6 (lipids 16) sharing the partners of one attempt:
+//    2 trimers,    64 walkers   1592  1241  1196  1499   1308
+//   16 trimers,    64            708   661   857  1291   1247
+//   32 trimers,    64            597   624   850  1317   1339
+//   64 trimers,   512            909   716   934  1467   1772
+//   64 trimers, 1,024           1778  1352  1193  1583   3143
+//   64 trimers, 2,048           3347  2471  2122  2020   6210
+//    4 trimers, 1,024           4636  2340  1437  1637   1984
+//   N = 1000 lipids,   512       798   608   767  1239   2311
+//   N = 1000 lipids, 1,024      1494  1117   974  1300   4547
+// The 16-bit places (8 bytes a particle) are kept where they fit, else taken
+// from the coordinates each time (three conversions more per partner); then
+// the wavefronts are halved until the LDS holds them.
 struct MovePlan {
     int waves, grid;
     size_t lds;
 };
-inline MovePlan move_plan(size_t used, size_t per_wave, int particles) {
-    for (int k = kMoveMaxWaves; k >= 1; k /= 2)
-        for (int grid = k == kMoveMaxWaves ? 1 : 0; grid >= 0; --grid) {
-            const size_t lds = used + k * per_wave + move_lds_bytes(k) + (grid ? (size_t)particles * sizeof(MoveGrid) : 0);
-            if (lds <= kLdsBytes || (k == 1 && !grid)) return MovePlan{k, grid, lds};
-        }
+inline MovePlan move_plan(size_t used, size_t per_wave, int particles, int walkers) {
+    constexpr int kCUs = 256;
+    auto bytes = [&](int k, int grid) {
+        return used + k * per_wave + move_lds_bytes(k) + (grid ? (size_t)particles * sizeof(MoveGrid) : 0);
+    };
+    const int per_cu = (walkers + kCUs - 1) / kCUs;
+    int most = kMoveMaxWaves;
+    while (most > 2 && kMoveMaxWaves / most < per_cu && kLdsBytes / bytes(most, 1) > (size_t)(kMoveMaxWaves / most)) most /= 2;
+    const int few = particles <= 8 ? 4 : (particles < 64 ? 8 : kMoveMaxWaves);
+    const int first = few < most ? few : most;
+    for (int k = first; k >= 1; k /= 2)
+        for (int grid = k == first ? 1 : 0; grid >= 0; --grid)
+            if (bytes(k, grid) <= kLdsBytes || (k == 1 && !grid)) return MovePlan{k, grid, bytes(k, grid)};
     return MovePlan{1, 0, 0};
 }
 

@@ -290,7 +290,7 @@ hipError_t allow(const void *fn, size_t bytes) {
 
 }  // namespace
 
-static MovePlan trimer_plan(const DevState &st) { return move_plan((size_t)st.Npad + (size_t)st.Wpad * 12, 0, st.nb); }
+static MovePlan trimer_plan(const DevState &st) { return move_plan((size_t)st.Npad + (size_t)st.Wpad * 12, 0, st.nb, st.nw); }
 size_t trimer_sweep_lds_bytes(const DevState &st) { return trimer_plan(st).lds; }
 size_t trimer_walkin_lds_bytes(const DevState &st) { return (size_t)st.Npad + (size_t)st.Bpad * 4; }
 

@@ -114,4 +114,13 @@ int64_t correction_read(int lane, int waves, int r, int64_t *last)
     return rewl_gpu::move_corrections(Table{last}, lane, waves)[r];
 }
 
+// Workgroup of the continuous models: wavefronts, 16-bit places kept, LDS bytes.
+void move_workgroup(size_t used, size_t per_wave, int particles, int walkers, int64_t *out)
+{
+    const rewl_gpu::MovePlan p = rewl_gpu::move_plan(used, per_wave, particles, walkers);
+    out[0] = p.waves;
+    out[1] = p.grid;
+    out[2] = (int64_t)p.lds;
+}
+
 }

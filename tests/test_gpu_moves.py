@@ -121,3 +121,28 @@ def test_droplets_in_large_boxes(box):
     o.run(3000)
     assert_same_state(g, o)
     assert_same_lipids(g, o)
+
+
+@pytest.mark.parametrize("nmol,box,h,m,attempts,precision", [
+    (1, 3.0, 1, 2, 3000, 0),          # four wavefronts
+    (4, 5.0, 1, 1024, 150, 0),        # four, as many walkers a CU
+    (16, 7.0, 1, 512, 150, 1),        # eight, two walkers a CU
+    (8, 5.0, 2, 650, 100, 0),         # two, up to eight walkers a CU
+])
+def test_trimer_workgroups_of_fewer_wavefronts(nmol, box, h, m, attempts, precision):
+    g, o = trimer_pair(nmol, box, -40.0, 0.5, 400, h, m, lnf_init=0.05, fixed_lnf=1, sync_attempts=49,
+                       precision=precision, seed=11)
+    g.run(attempts)
+    o.run(attempts)
+    assert_same_state(g, o)
+    assert_same_energies(g, o)
+
+
+@pytest.mark.parametrize("h,m", [(1, 300), (1, 700), (2, 550)])   # eight, four and two wavefronts
+def test_lipid_workgroups_of_fewer_wavefronts(h, m):
+    g, o = lipid_pair(6, 60, 5.0, 300.0, 0.5, 800, h, m, rep_prob=0.3, lnf_init=0.05, fixed_lnf=1, sync_attempts=49,
+                      seed=12)
+    g.run(100)
+    o.run(100)
+    assert_same_state(g, o)
+    assert_same_lipids(g, o)

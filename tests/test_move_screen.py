@@ -52,3 +52,47 @@ def test_corrections_are_read_inside_their_table(kernel_arith, waves):
             assert last.value < 16 * waves
             if lane < waves:
                 assert v == 16 * lane + r + 1
+
+
+LDS = 160 * 1024
+
+
+def workgroup(lib, used, per_wave, particles, walkers):
+    out = (ctypes.c_int64 * 3)()
+    lib.move_workgroup.argtypes = [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    lib.move_workgroup.restype = None
+    lib.move_workgroup(used, per_wave, particles, walkers, out)
+    return tuple(out)
+
+
+@pytest.mark.parametrize("particles,walkers,window,waves,grid", [
+    (192, 1, 267, 16, 1), (192, 64, 267, 16, 1), (192, 256, 267, 16, 1),
+    (192, 257, 267, 8, 1), (192, 512, 267, 8, 1), (192, 513, 267, 4, 1), (192, 1024, 267, 4, 1),
+    (192, 1025, 267, 2, 1), (192, 65535, 267, 2, 1),
+    (3, 64, 60, 4, 1), (9, 64, 60, 8, 1), (63, 64, 60, 8, 1), (64, 64, 60, 16, 1), (12, 1024, 60, 4, 1),
+    (192, 1024, 8000, 16, 1),             # the LDS holds one walker whatever its wavefronts
+    (192, 1024, 4500, 8, 1),              # two
+    (192, 64, 13000, 8, 0), (48, 64, 13440, 4, 0),
+])
+def test_workgroups_of_the_continuous_models(kernel_arith, particles, walkers, window, waves, grid):
+    used = -(-12 * particles // 256) * 256 + -(-window // 64) * 64 * 12
+    got = workgroup(kernel_arith, used, 0, particles, walkers)
+    assert got[:2] == (waves, grid) and got[2] <= LDS
+
+
+def test_every_accepted_size_has_a_workgroup_that_fits(kernel_arith):
+    # what creation accepts: state and window beside the buffers of one attempt
+    # shared by the wavefronts (512 bytes and more for 64 particles)
+    rng = np.random.default_rng(61)
+    for _ in range(20_000):
+        particles = int(np.exp(rng.uniform(np.log(3), np.log(4096))))
+        lipid = rng.random() < 0.5
+        chunks = (particles + 63) // 64
+        state = -(-((16 if lipid else 0) + (21 if lipid else 12) * particles) // 256) * 256
+        room = LDS - state - chunks * 64 * 8 * (1 if lipid else 2) - (chunks * 16 if lipid else 0)
+        if room < 768:
+            continue
+        window = (room // 768 if rng.random() < 0.5 else rng.integers(1, room // 768 + 1)) * 64
+        used = state + int(window) * 12 + (chunks * 16 if lipid else 0)
+        waves, grid, lds = workgroup(kernel_arith, used, 8 if lipid else 0, particles, int(rng.integers(1, 65536)))
+        assert waves in (1, 2, 4, 8, 16) and lds <= LDS, (particles, lipid, window)
