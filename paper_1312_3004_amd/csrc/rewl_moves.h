@@ -132,8 +132,7 @@ __host__ __device__ inline size_t move_lds_bytes(int waves) {
 //   evaluates, if they have 16 wavefronts between them and the LDS holds them.
 // us per 1,000 attempts of every walker (300 for the lipids) with 16, 8, 4, 2
 // wavefronts, and with 6 (lipids 16) sharing the partners of one attempt:
-//    2 trimers,    64 walkers   1592  1241  1196  1499   1308
-//   16 trimers,    64            708   661   857  1291   1247
+//   16 trimers,    64 walkers    708   661   857  1291   1247
 //   32 trimers,    64            597   624   850  1317   1339
 //   64 trimers,   512            909   716   934  1467   1772
 //   64 trimers, 1,024           1778  1352  1193  1583   3143
@@ -156,7 +155,7 @@ inline MovePlan move_plan(size_t used, size_t per_wave, int particles, int walke
     const int per_cu = (walkers + kCUs - 1) / kCUs;
     int most = kMoveMaxWaves;
     while (most > 2 && kMoveMaxWaves / most < per_cu && kLdsBytes / bytes(most, 1) > (size_t)(kMoveMaxWaves / most)) most /= 2;
-    const int few = particles <= 8 ? 4 : (particles < 64 ? 8 : kMoveMaxWaves);
+    const int few = particles < 64 ? 8 : kMoveMaxWaves;
     const int first = few < most ? few : most;
     for (int k = first; k >= 1; k /= 2)
         for (int grid = k == first ? 1 : 0; grid >= 0; --grid)

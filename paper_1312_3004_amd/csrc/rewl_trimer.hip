@@ -218,9 +218,9 @@ __global__ __launch_bounds__(64) void k_trimer_walkin(DevState st, int64_t chunk
 // accept with min[1, g(bin_old)/g(bin_new)]; then ln g += ln f and H += 1 at
 // the bin after the decision.
 //
-// One workgroup of 16 wavefronts per walker, an attempt per wavefront: blocks
-// of consecutive attempts evaluated side by side and decided in order
-// (rewl_moves.h).
+// One workgroup per walker, an attempt per wavefront: blocks of consecutive
+// attempts evaluated side by side and decided in order (rewl_moves.h, with the
+// choice of the workgroup); up to eight beads on one wavefront (trimer_few).
 template <bool GRID>
 struct TrimerMoves {
     static constexpr bool kGrid = GRID;    // 16-bit places in LDS
@@ -240,8 +240,99 @@ struct TrimerMoves {
     }
 };
 
-template <int PREC, bool GRID>
-__global__ __launch_bounds__(1024) void k_trimer_sweep(DevState st, int64_t s0, int64_t n) {
+// Attempts of a walker of at most eight beads, one after the other on one
+// wavefront: a block of them would end on a bead that has moved after two or
+// three.  Lane j holds bead j and evaluates it against the moved bead's new
+// place, lane 8 + j against the old one.  Bound by the chain of one attempt
+// (minimum image, division, sum, bin, ln g): us per 1,000 attempts of 64 and of
+// 1,024 walkers, one trimer 821 and 904, in blocks 1666 and 2310, with two
+// wavefronts sharing an attempt 1253 and 1646; two trimers 820 and 905, 1230 and
+// 1753, 1286 and 1675.
+constexpr int kFewBeads = 8;
+template <int PREC>
+__device__ __forceinline__ void trimer_few(const DevState &st, float *x, int w, int64_t s0, int64_t n, double *g,
+                                           float *gh, float *gl, uint32_t *H) {
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x;
+    const int j = lane & (kFewBeads - 1);
+    const bool old = lane >= kFewBeads, live = lane < 2 * kFewBeads && j < st.nb;
+    const int k = w / st.m;
+    const int lo = st.start[k], W = st.W;
+    const double lnf = st.lnf[k];
+    const float lnf32 = (float)lnf;
+    const float box = st.box, half = 0.5f * st.box;
+    float own[3] = {0.0f, 0.0f, 0.0f};
+    if (live)
+        for (int c = 0; c < 3; ++c) own[c] = x[3 * j + c];
+    int E = __builtin_amdgcn_readfirstlane(st.E[w]) - lo;   // bin in the window
+    int64_t Ef = move_uniform64(st.Efx[w]);
+    for (int64_t base = 0; base < n; base += 64) {
+        const int todo = (int)((n - base) < 64 ? (n - base) : 64);
+        const Draw dr = draw(st, kDomMove, kDomMoveU, (uint64_t)(s0 + base + lane), (uint32_t)w);
+        double lnu;
+        if (PREC == 0) lnu = dr.u == 0u ? -64.0 : log((double)dr.u * 0x1p-32);
+        else lnu = (dr.u >> 8) == 0u ? -64.0 : log((double)(dr.u >> 8) * 0x1p-24);
+        for (int a = 0; a < todo; ++a) {
+            const int b = __builtin_amdgcn_readlane(dr.bead, a);
+            const float o[3] = {move_readlane_f(own[0], b), move_readlane_f(own[1], b), move_readlane_f(own[2], b)};
+            const float nw[3] = {move_wrap(o[0] + move_readlane_f(dr.d0, a), box),
+                                 move_wrap(o[1] + move_readlane_f(dr.d1, a), box),
+                                 move_wrap(o[2] + move_readlane_f(dr.d2, a), box)};
+            const float q[3] = {old ? o[0] : nw[0], old ? o[1] : nw[1], old ? o[2] : nw[2]};
+            int64_t t = 0;
+            const bool with = live && j != b;
+            const bool bad = !fx_term(pair_energy(b, j, q, own, box, half), t) && with;
+            const int64_t de = wave_sum64(with ? (old ? -t : t) : 0);
+            int64_t e_new = 0;
+            const bool ok = __ballot(bad) == 0ull && fx_add(Ef, de, e_new);
+            const int bn = (ok ? energy_bin(st, e_new) : st.B) - lo;
+            bool acc = false;
+            if (ok && bn >= 0 && bn < W) {
+                const double luj = move_readlane_d(lnu, a);
+                const uint32_t u = __builtin_amdgcn_readlane(dr.u, a);
+                if (PREC == 0) {
+                    const double d = g[E] - g[bn], v = d - luj;
+                    acc = fabs(v) > 1e-10 ? v > 0.0 : accept64(d, u);
+                } else {
+                    const float d = (gh[E] - gh[bn]) + (gl[E] - gl[bn]);
+                    const double v = (double)d - luj;
+                    acc = fabs(v) > 1e-5 ? v > 0.0 : accept32(d, u);
+                }
+            }
+            if (__ballot(acc) != 0ull) {
+                Ef = e_new;
+                E = bn;
+                if (j == b)
+                    for (int c = 0; c < 3; ++c) own[c] = nw[c];
+            }
+            if (lane == 0) {
+                if (PREC == 0) {
+                    g[E] = g[E] + lnf;
+                } else {
+                    float h = gh[E], l = gl[E];
+                    two_sum_add(h, l, lnf32);
+                    gh[E] = h;
+                    gl[E] = l;
+                }
+                atomicAdd(&H[E], 1u);
+            }
+            move_wave_sync();
+        }
+    }
+    if (live && !old)
+        for (int c = 0; c < 3; ++c) x[3 * j + c] = own[c];
+    if (lane == 0) {
+        st.E[w] = E + lo;
+        st.Efx[w] = Ef;
+    }
+    __syncthreads();
+}
+
+// FORM: attempts one after the other (at most kFewBeads beads), blocks without
+// or with the 16-bit places.
+enum { kFormFew = 0, kFormBlocks = 1, kFormGrid = 2 };
+template <int PREC, int FORM>
+__global__ __launch_bounds__(FORM == kFormFew ? 64 : 1024) void k_trimer_sweep(DevState st, int64_t s0, int64_t n) {
     if (*st.converged) return;
     const int w = blockIdx.x;
     const int k = w / st.m;
@@ -266,10 +357,15 @@ __global__ __launch_bounds__(1024) void k_trimer_sweep(DevState st, int64_t s0, 
         H[b] = st.H[row + b];
     }
     __syncthreads();
-    unsigned char *mv = smem + st.Npad + (size_t)Wpad * 12;
-    MoveGrid *grid = GRID ? (MoveGrid *)(mv + move_lds_bytes((int)(blockDim.x >> 6))) : nullptr;
-    TrimerMoves<GRID> md{(float *)smem, grid, st.box, 0.5f * st.box, 65536.0f / st.box};
-    move_sweep<TrimerMoves<GRID>, PREC>(st, md, w, s0, n, g, gh, gl, H, mv);
+    if constexpr (FORM == kFormFew) {
+        trimer_few<PREC>(st, (float *)smem, w, s0, n, g, gh, gl, H);
+    } else {
+        constexpr bool kGrid = FORM == kFormGrid;
+        unsigned char *mv = smem + st.Npad + (size_t)Wpad * 12;
+        MoveGrid *grid = kGrid ? (MoveGrid *)(mv + move_lds_bytes((int)(blockDim.x >> 6))) : nullptr;
+        TrimerMoves<kGrid> md{(float *)smem, grid, st.box, 0.5f * st.box, 65536.0f / st.box};
+        move_sweep<TrimerMoves<kGrid>, PREC>(st, md, w, s0, n, g, gh, gl, H, mv);
+    }
     uint32_t *ox = (uint32_t *)(st.spins + (size_t)w * st.Npad);
     for (int i = threadIdx.x; i < st.Npad / 4; i += blockDim.x) ox[i] = ((uint32_t *)smem)[i];
     for (int b = threadIdx.x; b < W; b += blockDim.x) {
@@ -290,7 +386,11 @@ hipError_t allow(const void *fn, size_t bytes) {
 
 }  // namespace
 
-static MovePlan trimer_plan(const DevState &st) { return move_plan((size_t)st.Npad + (size_t)st.Wpad * 12, 0, st.nb, st.nw); }
+static MovePlan trimer_plan(const DevState &st) {
+    const size_t rows = (size_t)st.Npad + (size_t)st.Wpad * 12;
+    if (st.nb <= kFewBeads) return MovePlan{1, 0, rows};
+    return move_plan(rows, 0, st.nb, st.nw);
+}
 size_t trimer_sweep_lds_bytes(const DevState &st) { return trimer_plan(st).lds; }
 size_t trimer_walkin_lds_bytes(const DevState &st) { return (size_t)st.Npad + (size_t)st.Bpad * 4; }
 
@@ -315,8 +415,9 @@ hipError_t launch_trimer_sweep(const DevState &st, int64_t s0, int64_t n, hipStr
         hipLaunchKernelGGL(kernel, dim3(st.nw), dim3(64 * p.waves), p.lds, s, st, s0, n);
         return hipGetLastError();
     };
-    if (p.grid) return st.precision == 0 ? go(k_trimer_sweep<0, true>) : go(k_trimer_sweep<1, true>);
-    return st.precision == 0 ? go(k_trimer_sweep<0, false>) : go(k_trimer_sweep<1, false>);
+    if (st.nb <= kFewBeads) return st.precision == 0 ? go(k_trimer_sweep<0, kFormFew>) : go(k_trimer_sweep<1, kFormFew>);
+    if (p.grid) return st.precision == 0 ? go(k_trimer_sweep<0, kFormGrid>) : go(k_trimer_sweep<1, kFormGrid>);
+    return st.precision == 0 ? go(k_trimer_sweep<0, kFormBlocks>) : go(k_trimer_sweep<1, kFormBlocks>);
 }
 
 }  // namespace rewl_gpu

@@ -124,7 +124,6 @@ def test_droplets_in_large_boxes(box):
 
 
 @pytest.mark.parametrize("nmol,box,h,m,attempts,precision", [
-    (1, 3.0, 1, 2, 3000, 0),          # four wavefronts
     (4, 5.0, 1, 1024, 150, 0),        # four, as many walkers a CU
     (16, 7.0, 1, 512, 150, 1),        # eight, two walkers a CU
     (8, 5.0, 2, 650, 100, 0),         # two, up to eight walkers a CU
@@ -146,3 +145,25 @@ def test_lipid_workgroups_of_fewer_wavefronts(h, m):
     o.run(100)
     assert_same_state(g, o)
     assert_same_lipids(g, o)
+
+
+@pytest.mark.parametrize("nmol,box,m,attempts,precision", [
+    (1, 3.0, 2, 3001, 0), (1, 3.0, 2, 3001, 1), (2, 2.6, 3, 2000, 1), (2, 4.0, 1024, 130, 0), (2, 14.0, 2, 63, 0),
+    (2, 14.0, 2, 1, 1),
+])
+@pytest.mark.parametrize("infinite", [False, True])
+def test_trimers_of_few_beads(nmol, box, m, attempts, precision, infinite):
+    # one wavefront, attempts one after the other; unvisited bins at minus infinity
+    g, o = trimer_pair(nmol, box, -20.0, 0.5, 200, 1, m, lnf_init=0.25, fixed_lnf=1, sync_attempts=97,
+                       precision=precision, seed=13)
+    g.run(attempts)
+    o.run(attempts)
+    if infinite:
+        for w in range(min(m, 3)):
+            lng = np.where(g.walker(w)["H"] > 0, g.walker(w)["lng"], -np.inf)
+            g.set_lng(w, lng)
+            o.set_lng(w, lng)
+    g.run(attempts)
+    o.run(attempts)
+    assert_same_state(g, o)
+    assert_same_energies(g, o)

@@ -69,7 +69,7 @@ def workgroup(lib, used, per_wave, particles, walkers):
     (192, 1, 267, 16, 1), (192, 64, 267, 16, 1), (192, 256, 267, 16, 1),
     (192, 257, 267, 8, 1), (192, 512, 267, 8, 1), (192, 513, 267, 4, 1), (192, 1024, 267, 4, 1),
     (192, 1025, 267, 2, 1), (192, 65535, 267, 2, 1),
-    (3, 64, 60, 4, 1), (9, 64, 60, 8, 1), (63, 64, 60, 8, 1), (64, 64, 60, 16, 1), (12, 1024, 60, 4, 1),
+    (9, 64, 60, 8, 1), (63, 64, 60, 8, 1), (64, 64, 60, 16, 1), (12, 1024, 60, 4, 1),
     (192, 1024, 8000, 16, 1),             # the LDS holds one walker whatever its wavefronts
     (192, 1024, 4500, 8, 1),              # two
     (192, 64, 13000, 8, 0), (48, 64, 13440, 4, 0),
