@@ -11,7 +11,8 @@ SOURCES = [os.path.join(CSRC, "rewl_kernels.hip"), os.path.join(CSRC, "rewl_runt
            os.path.join(CSRC, "rewl_batch.hip"), os.path.join(CSRC, "rewl_trimer.hip"),
            os.path.join(CSRC, "rewl_lipid.hip"), os.path.join(CSRC, "rewl_structure.hip")]
 HEADERS = [os.path.join(CSRC, "rewl_device.h"), os.path.join(CSRC, "rewl_moves.h"), os.path.join(CSRC, "rewl_replay.h"),
-           os.path.join(CSRC, "rewl_handover.h"), os.path.join(CSRC, "rewl_host.h"),
+           os.path.join(CSRC, "rewl_handover.h"), os.path.join(CSRC, "rewl_slots.h"),
+           os.path.join(CSRC, "rewl_host.h"),
            os.path.join(os.path.dirname(HERE), "include", "rewl.h"),
            os.path.join(os.path.dirname(HERE), "include", "rewl_phase_clocks.h")]
 

@@ -8,6 +8,7 @@
 
 #include "../../include/rewl.h"
 #include "rewl_device.h"
+#include "rewl_slots.h"
 
 namespace rewl_host {
 
@@ -54,7 +55,16 @@ struct Layout {
 
 }  // namespace rewl_host
 
+// Pinned slots the runs of this process read their convergence flag into.
+namespace rewl_host {
+SlotBlock &pinned_slots();
+}
+
 struct rewl {
+    rewl() = default;
+    rewl(const rewl &) = delete;
+    rewl &operator=(const rewl &) = delete;
+    ~rewl() { rewl_host::pinned_slots().give(pin); }
     rewl_gpu::DevState st;
     rewl_host::Timer timer;
     rewl_host::Layout lay;
@@ -65,5 +75,5 @@ struct rewl {
     int64_t step = 0, round = 0;
     bool walked_in = false, converged = false, joined = false;
     bool in_batch = false;   // owned by a rewl_batch (rewl_destroy refuses it)
-    unsigned char *pin = nullptr;   // pinned copy of [converged .. stop], from the first run on
+    unsigned char *pin = nullptr;   // slot for a copy of [converged .. stop], from the first run on
 };

@@ -3,6 +3,12 @@
 #include "../../paper_1312_3004_amd/csrc/rewl_handover.h"
 #include "../../paper_1312_3004_amd/csrc/rewl_moves.h"
 #include "../../paper_1312_3004_amd/csrc/rewl_replay.h"
+#include "../../paper_1312_3004_amd/csrc/rewl_slots.h"
+
+#include <atomic>
+#include <cstdlib>
+#include <thread>
+#include <vector>
 
 namespace {
 
@@ -121,6 +127,58 @@ void move_workgroup(size_t used, size_t per_wave, int particles, int walkers, in
     out[0] = p.waves;
     out[1] = p.grid;
     out[2] = (int64_t)p.lds;
+}
+
+// The shared slots: 0 if a block that could not be allocated gives none, the
+// block is allocated once, its slots are distinct and all used before none is
+// left, and a slot given back is taken again; else the number of the failed step.
+int slots_in_order(void)
+{
+    rewl_host::SlotBlock block;
+    int calls = 0;
+    unsigned char *mem = nullptr;
+    block.reserve([&](size_t) -> void * { ++calls; return nullptr; });
+    if (block.take()) return 1;
+    for (int i = 0; i < 3; ++i)
+        block.reserve([&](size_t bytes) -> void * { ++calls; return mem = (unsigned char *)malloc(bytes); });
+    if (calls != 2) return 2;
+    std::vector<unsigned char *> slot;
+    while (unsigned char *s = block.take()) slot.push_back(s);
+    if (slot.size() != 64) return 3;
+    for (size_t i = 0; i < slot.size(); ++i)
+        if (slot[i] != mem + i * rewl_host::SlotBlock::kBytes) return 4;
+    block.give(nullptr);
+    block.give(slot[17]);
+    block.give(slot[40]);
+    if (block.take() != slot[17] || block.take() != slot[40] || block.take()) return 5;
+    free(mem);
+    return 0;
+}
+
+// Threads that take and give slots: how often one was found taken twice.
+int slots_shared(int threads, int rounds)
+{
+    rewl_host::SlotBlock block;
+    std::vector<unsigned char> mem(64 * rewl_host::SlotBlock::kBytes);
+    std::atomic<int> owner[64] = {}, clashes{0};
+    std::vector<std::thread> pool;
+    for (int t = 0; t < threads; ++t)
+        pool.emplace_back([&] {
+            for (int i = 0; i < rounds; ++i) {
+                block.reserve([&](size_t) -> void * { return mem.data(); });
+                unsigned char *held[12];
+                for (auto &s : held) {
+                    s = block.take();
+                    if (s && owner[(s - mem.data()) / rewl_host::SlotBlock::kBytes].exchange(1)) ++clashes;
+                }
+                for (auto &s : held) {
+                    if (s) owner[(s - mem.data()) / rewl_host::SlotBlock::kBytes] = 0;
+                    block.give(s);
+                }
+            }
+        });
+    for (auto &t : pool) t.join();
+    return clashes;
 }
 
 }

@@ -68,3 +68,17 @@ def test_lnf_of_the_one_over_t_schedule_bitexact(precision):
     g.run(60_000)
     o.run(60_000)
     assert_same_state(g, o)
+
+
+def test_more_runs_at_once_than_slots_for_their_flags():
+    # 70 runs of different lengths, alive together: each reads its own flag and
+    # stop point, with a pinned slot or without; destroyed runs' slots are used again
+    for turn in range(2):
+        pairs = [make_pair(3, 2, 1, 1, lnf_init=1.0, lnf_final=2.0**-(1 + i % 7), flat=(0, 1), sync_attempts=50 + i,
+                           seed=turn * 100 + i) for i in range(70)]
+        for g, o in pairs:
+            assert g.run(400) == o.run(400)
+        for g, o in pairs:
+            assert g.run(300) == o.run(300)
+            assert g.progress()[:2] == (o.step, o.round)
+            assert_same_state(g, o)
