@@ -1143,7 +1143,7 @@ __device__ __forceinline__ void sweep_walker(const DevState &st, int w, int64_t 
                 } else {
                     const double d = gb - ((double)gNh + (double)gNl);
                     t = d + A;
-                    Mt = M + (fabs(d) + (double)fabsf(gNl)) * 0x1p-18;
+                    Mt = pair_margin(M, d, gNl);
                 }
                 S = (__ballot(!(t < -Mt)) | C) & rem;
                 first = __ballot(t > Mt) & R & S & (0ull - S);

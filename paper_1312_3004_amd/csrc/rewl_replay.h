@@ -1,4 +1,5 @@
-// rewl_replay.h -- repeated additions of ln f to one ln g value in closed form.
+// rewl_replay.h -- repeated additions of ln f to one ln g value in closed form,
+// and the margin of a decision on (hi, lo) pairs.
 //
 // A committed segment adds ln f to a bin once per visit.  Each addition is
 // rounded on its own, so the sum is not n ln f; but while the value stays in
@@ -53,6 +54,15 @@ __host__ __device__ __forceinline__ uint32_t low_word_steps(float x, float l, ui
     const float room = (__builtin_ldexpf(1.0f, e) - x) / d - 4.0f;
     const uint32_t k = room >= 64.0f ? 64u : (room >= 1.0f ? (uint32_t)room : 0u);
     return k < n ? k : n;
+}
+
+// Margin of a decision on the difference d of two pairs, the second with low
+// word lo: M and what the binary32 difference may be off.  An infinite ln g of the
+// new energy (outside the window, d = -inf) is refused for sure, so d counts up to
+// a bound; where ln g of the current energy is infinite, M is.
+__host__ __device__ __forceinline__ double pair_margin(double M, double d, float lo) {
+#pragma clang fp contract(off)
+    return M + (__builtin_fmin(__builtin_fabs(d), 0x1p100) + (double)__builtin_fabsf(lo)) * 0x1p-18;
 }
 
 // n additions of l to the pair (hi, lo) by TwoSum.  `any` says whether the loop

@@ -181,4 +181,6 @@ int slots_shared(int threads, int rounds)
     return clashes;
 }
 
+double pair_decision_margin(double M, double d, float lo) { return rewl_gpu::pair_margin(M, d, lo); }
+
 }

@@ -90,3 +90,13 @@ def test_binary64(kernel_arith, kind):
     bad = np.flatnonzero(got != ref)
     assert len(bad) == 0, (len(bad), x[bad[0]].hex(), f[bad[0]].hex(), n[bad[0]])
     assert closed > 0.3 * count
+
+
+def test_margin_of_pairs_refuses_what_lies_outside_the_window(kernel_arith):
+    f = kernel_arith.pair_decision_margin
+    f.restype, f.argtypes = ctypes.c_double, [ctypes.c_double, ctypes.c_double, ctypes.c_float]
+    inf = float("inf")
+    assert f(0.01, -40.0, -0.5) == 0.01 + 40.5 * 2.0**-18
+    assert -inf < -f(0.01, -inf, 0.0)        # t = d = -inf lies below the margin: no exact evaluation
+    assert not -inf < -f(inf, -inf, 0.0)     # ln g of the current energy infinite: evaluated exactly
+    assert not -inf < -f(0.01, -inf, inf)
