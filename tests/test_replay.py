@@ -45,18 +45,31 @@ def test_pair(kernel_arith, kind):
     hi = g.astype(np.float32)
     lo = (g - hi.astype(np.float64)).astype(np.float32)
     f = steps(kind, bins, rng, np.float32)
-    single = total = 0
     for _ in range(60):
         n = rng.integers(1, 13, bins).astype(np.uint32)
         rh, rl = hi, lo
         for k in range(12):
             h, l = two_sum(rh, rl, f)
             rh, rl = np.where(k < n, h, rh), np.where(k < n, l, rl)
-        single += call(kernel_arith.replay_pair_all, n, hi, lo, f)
-        total += int(n.sum())
+        call(kernel_arith.replay_pair_all, n, hi, lo, f)
         bad = np.flatnonzero((hi.view(np.int32) != rh.view(np.int32)) | (lo.view(np.int32) != rl.view(np.int32)))
         assert len(bad) == 0, (len(bad), hi[bad[0]], lo[bad[0]], rl[bad[0]], f[bad[0]], n[bad[0]])
-    assert single < (0.7 if kind == "W/t" else 1.0) * total
+
+
+@pytest.mark.parametrize("lnf", [461 / 1.18e9, 461 / 4.3e10, 2.0**-21])
+def test_pair_late_in_a_run_takes_closed_forms(kernel_arith, lnf):
+    # low words of either sign against an ln f that the high word ignores
+    rng = np.random.default_rng(43)
+    g = rng.uniform(200.0, 3000.0, 20_000)
+    hi = g.astype(np.float32)
+    lo = (g - hi.astype(np.float64)).astype(np.float32)
+    f = np.full(len(g), lnf, dtype=np.float32)
+    single = total = 0
+    for _ in range(40):
+        n = rng.integers(1, 13, len(g)).astype(np.uint32)
+        single += call(kernel_arith.replay_pair_all, n, hi, lo, f)
+        total += int(n.sum())
+    assert single < 0.2 * total
 
 
 def test_pair_that_enters_a_binade_on_an_odd_value(kernel_arith):
