@@ -117,10 +117,13 @@ __host__ __device__ __forceinline__ float move_reach(float d0, float d1, float d
     return __builtin_sqrtf(d0 * d0 + d1 * d1 + d2 * d2) + move_slack(box);
 }
 
+// Entries of the correction table of `waves` wavefronts: their rows, and room
+// for the entries read behind the last one.
+__host__ __device__ inline int move_table(int waves) { return waves * waves + kMoveMaxWaves; }
 // LDS behind the walker's state, ln g and H: block header, rows, proposals,
 // correction table and lists of `waves` wavefronts.
 __host__ __device__ inline size_t move_lds_bytes(int waves) {
-    return (size_t)waves * (sizeof(MoveRow) + sizeof(MoveProp) + kMoveMaxWaves * 8 + kMoveList * 2) + 64;
+    return (size_t)waves * (sizeof(MoveRow) + sizeof(MoveProp) + kMoveList * 2) + (size_t)move_table(waves) * 8 + 64;
 }
 // Workgroup of a walker beside `used` bytes of LDS (state, ln g, H, the model's
 // own) and `per_wave` more of the model for each wavefront.
@@ -223,7 +226,7 @@ __host__ __device__ __forceinline__ float move_wrap(float v, float box) {
 // block-start configuration and its corrections for the attempts before it.
 template <class Model>
 __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &md, const MoveProp *props, int l,
-                                              MoveRow *rows, int64_t *tab, uint16_t *list, int lane) {
+                                              int waves, MoveRow *rows, int64_t *tab, uint16_t *list, int lane) {
 #pragma clang fp contract(off)
     const float box = st.box;
     const MoveProp p = props[l];
@@ -305,7 +308,7 @@ __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &m
         c += __shfl_xor(c, 16, 64);
         c += __shfl_xor(c, 32, 64);
     }
-    if (lane < l) tab[l * kMoveMaxWaves + lane] = c;
+    if (lane < l) tab[l * waves + lane] = c;
     const unsigned long long badm = __ballot(bad);
     const int64_t de = wave_sum64(acc);
     // the lanes' overlap counts (new places only can have one)
@@ -323,14 +326,11 @@ __device__ __forceinline__ void move_evaluate(const DevState &st, const Model &m
 }
 
 // Lane `lane`'s corrections for attempts 0 .. 15 of a block (those for itself
-// and later ones, and of lanes past the block, are never looked at).  The table
-// has 16 entries a row and `waves` rows: every read stays inside it, at offsets
-// that are known beforehand (rows of `waves` entries, read to their end alone,
-// take 4% longer on 64 trimers).
+// and later ones, and of lanes past the block, are never looked at).
 typedef long long move_l16 __attribute__((ext_vector_type(16)));
 template <class Table>
 __host__ __device__ __forceinline__ move_l16 move_corrections(Table tab, int lane, int waves) {
-    const int row = (lane < waves ? lane : waves - 1) * kMoveMaxWaves;
+    const int row = (lane < waves ? lane : waves - 1) * waves;
     move_l16 corr;
 #pragma unroll
     for (int r = 0; r < kMoveMaxWaves; ++r) corr[r] = tab[row + r];
@@ -352,7 +352,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
     MoveRow *rows = (MoveRow *)mv;
     MoveProp *props = (MoveProp *)(rows + waves);
     int64_t *tab = (int64_t *)(props + waves);
-    uint32_t *head = (uint32_t *)(tab + waves * kMoveMaxWaves);   // [16]: attempts of the block, kind, words
+    uint32_t *head = (uint32_t *)(tab + move_table(waves));   // [16]: attempts of the block, kind, words
     uint16_t *list = (uint16_t *)(head + 16) + wave * kMoveList;
 
     const int k = w / st.m;
@@ -445,7 +445,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
             t += 1;
             continue;
         }
-        if (wave < cur) move_evaluate(st, md, props, wave, rows, tab, list, lane);
+        if (wave < cur) move_evaluate(st, md, props, wave, waves, rows, tab, list, lane);
         __syncthreads();
         if (wave != 0) {
             continue;
@@ -630,7 +630,7 @@ __device__ __forceinline__ void move_sweep(const DevState &st, Model &md, int w,
                 bE = bj;
                 hist = lane >= j ? bj : hist;
                 accm |= 1u << j;
-                if (mine && lane > j) tot += tab[lane * kMoveMaxWaves + j];   // the correction for attempt j
+                if (mine && lane > j) tot += tab[lane * waves + j];   // the correction for attempt j
             }
             add_lnf(1);
             i = j + 1;

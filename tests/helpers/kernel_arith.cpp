@@ -183,4 +183,6 @@ int slots_shared(int threads, int rounds)
 
 double pair_decision_margin(double M, double d, float lo) { return rewl_gpu::pair_margin(M, d, lo); }
 
+int correction_entries(int waves) { return rewl_gpu::move_table(waves); }
+
 }
