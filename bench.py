@@ -52,15 +52,16 @@ FP64_UNFUSED_PEAK_TFLOPS = VALU_LANE_SLOTS_PEAK / 1e12
 # read-modify-write 16, H 8, spin 1); spec LDS peak 256 CUs x 128 B/clock x 2.4 GHz.
 LDS_BYTES_PER_ATTEMPT = 38
 LDS_PEAK_GBS = CU * 128 * CLOCK_HZ / 1e9
-# HBM bytes per k_sweep launch of the potts_q10_L32 workload in its timed (1/t)
-# phase, from rocprofv3 FETCH_SIZE and WRITE_SIZE runs scaled by a torch.neg
-# copy of known size (profiles/k_sweep_potts_q10_L32_pmc.md): 268.18 KiB x 2.000
-# + 390.0 KiB x 1.000.  Valid for the kernel as profiled; at ln f = 2^-21 the
-# present one reads 304.25 KiB (profiles/cases_kernel_trace_pmc.md).
+# HBM bytes per k_sweep launch of the potts_q10_L32 workload at ln f = 2^-21, from
+# rocprofv3 FETCH_SIZE and WRITE_SIZE runs scaled by a torch.neg copy of known size
+# (profiles/cases_kernel_trace_pmc.md): 305.5 KiB x 2.000 + 390.0 KiB x 1.000.
+K_SWEEP_L32_TRAFFIC_BYTES = 1_025_000
+# The same before attempts were decided from event to event, in the 1/t phase
+# (profiles/k_sweep_potts_q10_L32_pmc.md): 268.18 KiB and 390.0 KiB.
 K_SWEEP_L32_HBM_BYTES = 948_600
-# VALU instructions (wave64) per attempt of the same kernel, both wavefronts of a
+# VALU instructions (wave64) per attempt of the present kernel, both wavefronts of a
 # walker, rocprofv3 SQ_INSTS_VALU at ln f = 2^-21 (profiles/cases_kernel_trace_pmc.md).
-K_SWEEP_L32_VALU_PER_ATTEMPT = 9.10
+K_SWEEP_L32_VALU_PER_ATTEMPT = 9.16
 # 1/t phase ends once W/t < 1e-8, i.e. after W/1e-8 attempts per walker.
 
 
@@ -375,16 +376,20 @@ TRIMER_FLOPS_PER_ATTEMPT = 2 * 191 * 5
 # mul/add) of the ~52 partners inside the 2.5 cut-off at density 0.8, twice.
 # HBM bytes of one k_trimer_sweep launch of the trimer workload (64 walkers x
 # 20,000 attempts): FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (factors from a
-# 256 MiB torch.neg copy in the same program), 227.75 KiB and 308.0 KiB: the
-# rows in and out (512 KiB of registers saved once at the start not counted,
-# profiles/cases_kernel_trace_pmc.md).
+# 256 MiB torch.neg copy in the same program), 263.3 KiB and 820.0 KiB, 512 KiB of
+# them registers saved once a launch (profiles/cases_kernel_trace_pmc.md).
+TRIMER_SWEEP_TRAFFIC_BYTES = 1_379_000
+# The same before attempts went in blocks (profiles/k_trimer_sweep_trimer64_pmc.md):
+# 227.75 KiB and 308.0 KiB.
 TRIMER_SWEEP_HBM_BYTES = 781_800
 LIPID_FLOPS_PER_ATTEMPT = 2 * 999 * 5 + 2 * 52 * 6
 # HBM bytes of one k_lipid_sweep launch of the lipid workload (64 walkers x 2,000
 # attempts): FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (factors from a 256 MiB
-# torch.neg copy in the same program), 792.7 KiB and 1,302.0 KiB per launch: the
-# rows in and out (1 MiB of registers saved once at the start not counted,
-# profiles/cases_kernel_trace_pmc.md).
+# torch.neg copy in the same program), 855.6 KiB and 1,558.0 KiB per launch, 256 KiB of
+# them registers saved once a launch (profiles/cases_kernel_trace_pmc.md).
+LIPID_SWEEP_TRAFFIC_BYTES = 3_348_000
+# The same before attempts went in blocks (profiles/k_lipid_sweep_lipid1000_pmc.md):
+# 792.7 KiB and 1,302.0 KiB.
 LIPID_SWEEP_HBM_BYTES = 2_956_600
 
 
@@ -437,7 +442,7 @@ def trimer(args):
                                "over [-460, 40), 16 windows at 75% overlap, 4 walkers each",
                    "walkers": nw, "attempts_per_step_per_walker": S},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_UNFUSED_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / FP64_UNFUSED_PEAK_TFLOPS, "traffic": TRIMER_SWEEP_HBM_BYTES, "kernel": "k_trimer_sweep",
+                     "frac": achieved / FP64_UNFUSED_PEAK_TFLOPS, "traffic": TRIMER_SWEEP_TRAFFIC_BYTES, "kernel": "k_trimer_sweep",
                      "kernel_avg_ms": avg_ms, "kernel_launches": launches,
                      "flops_per_attempt": TRIMER_FLOPS_PER_ATTEMPT},
         "per_walker_attempts_per_s": S * args.steps / el,
@@ -504,7 +509,7 @@ def lipid(args):
                    "e_min": cfg["e_min"]},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_UNFUSED_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_UNFUSED_PEAK_TFLOPS,
-                     "traffic": LIPID_SWEEP_HBM_BYTES if cfg["e_min"] == workloads.LIPID["e_min"] else None,
+                     "traffic": LIPID_SWEEP_TRAFFIC_BYTES if cfg["e_min"] == workloads.LIPID["e_min"] else None,
                      "kernel": "k_lipid_sweep",
                      "kernel_avg_ms": avg_ms, "kernel_launches": launches, "flops_per_attempt": flops},
         "per_walker_attempts_per_s": S * args.steps / el,
@@ -1217,7 +1222,7 @@ def main():
                    # launches of the run (0-based, for matching a profiler's trace)
                    "timed_k_sweep_launches": [step_timed // S, step_timed // S + args.steps]},
         "roofline": potts_roofline(attempts_per_launch, avg_ms, launches,
-                                   K_SWEEP_L32_HBM_BYTES if args.config == "potts_q10_L32" and approach
+                                   K_SWEEP_L32_TRAFFIC_BYTES if args.config == "potts_q10_L32" and approach
                                    and cfg["precision"] == 0 else None),
         "per_walker_attempts_per_s": per_walker,
         "sync_point_avg_ms": sync_avg,

@@ -31,7 +31,8 @@ extern "C" {
  *   [10] cycles of the exact path after a speculative stop, with the restart
  *   [11] cycles at the end of blocks (pending flips, H increments)
  * [8], [9] and [6] cover the speculative segments: with [10] and [11] they
- * make up [1] for small ln f. * The device counters are shared by every run in the process; batched runs
+ * make up [1] for small ln f.
+ * The device counters are shared by every run in the process; batched runs
  * add to the rows of their walkers' indices within an instance.  Synchronous
  * (null stream).  Returns 0, or -1 on a HIP error. */
 int rewl_phase_clocks(unsigned long long *host, size_t rows, int reset);

@@ -6,12 +6,15 @@
 //               averaging within a window, replica exchange (Eq. 1), joining.
 //   Sec. 3.1    2D q-state Potts model (Eq. 2), single-spin-flip moves.
 //
-// Mapping: one walker per 64-lane wavefront (one workgroup).  Its lattice
-// (int8), ln g and H live in LDS for the whole launch; global memory is
-// touched only at launch start and end.  Attempts of one walker form a strict
-// sequence (each decision depends on the previous energy and ln g), so the
-// lanes first draw the Philox words and site neighbourhoods of the next 64
-// attempts in parallel and then walk through them in order.
+// Mapping: one walker per workgroup of one 64-lane wavefront that decides and,
+// up to six walkers a CU, a second one that draws (rewl_handover.h).  Its
+// lattice (int8), ln g and H live in LDS for the whole launch; global memory is
+// touched only at launch start and end (runs too large for that, and batches,
+// keep ln g and H in device memory).  Attempts of one walker form a strict
+// sequence (each decision depends on the previous energy and ln g): the lanes
+// draw the Philox words and site neighbourhoods of 64 attempts in parallel, and
+// decide them together, from event to event or from guesses that are refined,
+// with the results of one attempt after the other.
 #include <type_traits>
 
 #include "rewl_handover.h"
@@ -321,7 +324,10 @@ __device__ __forceinline__ void draw_block(const DevState &st, int w, uint64_t t
 // from creation to the last walker placed, against one attempt after the other.
 // Entries of its conflict-tag table: one per site up to 1,024 (hashed beyond:
 // a collision only has a proposal made again), as far as `lds` bytes hold them
-// beside the lattice and the counts (64 always fit).
+// beside the lattice and the counts (64 always fit).  In single runs of larger
+// lattices tables of up to 8,192 entries are faster (48 x 48, 80 x 80, 120 x 120:
+// 28.1, 77.4 and 172 ms with this limit, 25.7, 66.2 and 151 without); what they cost
+// in batches, where they keep walkers from sharing a CU, is not measured.
 __host__ __device__ inline int walkin_tags(const DevState &st, size_t lds) {
     const size_t state = (size_t)st.Npad + (size_t)st.Bpad * 4;
     int t = 64;
@@ -2516,7 +2522,9 @@ hipError_t launch_walkin(const DevState &st, int64_t chunk, int64_t budget, hipS
 // SIMD: at most six walkers a CU, all resident (the tag table gives way, down to
 // 64 entries, so that the helper's blocks fit).  32 x 32 sites, ln f = 2^-21, us per
 // 10,000 attempts with and without: 469 / 502 at four walkers a CU, 562 / 606
-// at six, 646 / 629 at eight.
+// at six, 646 / 629 at eight.  ln f is on the device, so the line is the same for
+// the event phase, where it lies lower: 16 x 16, ln f = 1, 4,000 attempts, 632 / 642
+// at five, 685 / 667 at six (q = 2: 718 / 730, 760 / 741).
 static bool sweep_helped(const DevState &st, DevState *out) {
     constexpr int kCUs = 256, kPerCu = 6;
     const int per_cu = (st.nw + kCUs - 1) / kCUs;

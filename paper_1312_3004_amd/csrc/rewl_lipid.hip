@@ -29,9 +29,11 @@
 // add the partner terms in any order and every implementation agrees to the
 // bit.
 //
-// Mapping: one walker per workgroup (the attempt kernel: up to 16 wavefronts
-// sharing the 64-partner chunks; walk-in and set-up: one wavefront), its
-// state, ln g and H in LDS.  Attempts are sequential.
+// Mapping: one walker per workgroup, its state, ln g and H in LDS.  The main
+// phase evaluates blocks of displacement attempts side by side, a wavefront
+// each, and takes a reptation with all wavefronts (rewl_moves.h, with the choice
+// of the workgroup); walk-in and set-up run one attempt after the other on one
+// wavefront.
 #include "rewl_moves.h"
 
 namespace rewl_gpu {
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(64) void k_lipid_walkin(DevState st, int64_t chunk,
 // min[1, g(old)/g(new)] (times n_c / n_r for a reptation); then
 // ln g += ln f and H += 1 at the bin after the decision.
 //
-// One workgroup of 16 wavefronts per walker.  Displacements: an attempt per
+// One workgroup per walker.  Displacements: an attempt per
 // wavefront, blocks of consecutive attempts evaluated side by side and decided
 // in order (rewl_moves.h).  A reptation ends the block before it and is done
 // by the whole workgroup: candidates by one ballot mask per 64 particles, then

@@ -35,8 +35,8 @@
 // corrections in registers (a lane's 16, the column by a uniform index).
 //
 // Measured on 64 walkers (one workgroup each), us per attempt of a walker:
-// 64 trimers 1.45 -> 0.48 (six wavefronts sharing the partners of one attempt
-// before), N = 1000 lipids 4.06 -> 1.17 (sixteen).  A block of 14.5 trimer
+// 64 trimers 1.45 -> 0.49 (six wavefronts sharing the partners of one attempt
+// before), N = 1000 lipids 4.06 -> 1.18 (sixteen).  A block of 14.5 trimer
 // attempts takes 1,350 cycles of proposals, 7,100 of evaluation (VALU issue,
 // four wavefronts per SIMD, 76% busy) and 5,050 of decisions (one wavefront,
 // 6.7 accepted attempts; 8,000 with a read of the correction table and the
